@@ -37,6 +37,7 @@
 #include "scan.h"
 #include "store_view.h"
 #include "xdrop_device.h"
+#include "lane_device.h"
 #include "pair2_device.h"
 #include "pair4_device.h"
 #include "pair_device.h"
@@ -56,7 +57,7 @@ __device__ unsigned long long* g_buf;
 __device__ uint32_t g_cap;
 __device__ uint32_t g_n;
 // kernel tags (k_ext_tier<CPL, ...> records kTier + CPL)
-enum : uint32_t { kFirst = 1, kPair = 0x20, kPair2 = 0x21, kPair4 = 0x22, kTier = 0x40, kBand = 0x80 };
+enum : uint32_t { kFirst = 1, kPair = 0x20, kPair2 = 0x21, kPair4 = 0x22, kLane = 0x30, kTier = 0x40, kBand = 0x80 };
 __device__ __forceinline__ uint64_t now() { return (uint64_t)wall_clock64(); }
 __device__ __forceinline__ void record(uint32_t tag, uint64_t t0, uint32_t items) {
   if ((threadIdx.x & 63) != 0) return;
@@ -86,8 +87,11 @@ namespace {
 
 constexpr uint32_t kWideBlocks = 2048;
 constexpr uint64_t kChunkBlocks = 1ull << 24;  // one-wave blocks per launch of a per-item grid
-constexpr int kCostBins = 128;          // per tier
-constexpr int kBins = 4 * kCostBins;    // tier-major
+// queue classes (ext_key), 73 length bins each, in 512 bins (the last class
+// is the invalid tasks', whose length does not matter)
+constexpr int kCostBins = 73;
+constexpr int kBins = 512;
+enum { kClsNarrow = 0, kClsLane, kCls64, kClsWide, kCls128, kCls256, kClsInvalid };
 constexpr int kBandWaves = 16;          // waves per band-tier workgroup
 constexpr uint32_t kBandBlocksMax = 16;
 constexpr uint64_t kBandBudget = 64ull << 20;  // default band area per batch
@@ -96,10 +100,13 @@ struct StoreDev {
   const uint32_t* words;
   const uint64_t* word_off;
   const uint32_t* len;
+  const xd::lane::Chunk* planes;  // the same bases in bit planes (lane_core.h)
+  const uint64_t* plane_off;      // first chunk of each read in planes
   uint32_t n_reads;
 };
 
-struct BatchArgs {
+// what the extension kernels read of a batch
+struct TaskArgs {
   StoreDev st;
   const uint32_t* pairs;
   const uint32_t* seeds;
@@ -109,12 +116,15 @@ struct BatchArgs {
   int32_t k;
   xd::Scoring sc;
   ExtOut* ext;  // [2n]
+  const uint8_t* flags;  // per task, may be null: bit 0 = B reverse-complemented
+};
+
+struct BatchArgs : TaskArgs {
   int32_t* score;
   uint32_t* beg;
   uint32_t* end;
   int32_t* status;
   uint64_t* cells;
-  const uint8_t* flags;  // per task, may be null: bit 0 = B reverse-complemented
 };
 
 // Band tier geometry: each workgroup owns three rows of cap words, cap >
@@ -169,11 +179,18 @@ struct Scratch {
 // ctr layout
 constexpr int kOvfCount = 0;   // [0..4] sizes of ovf[0..4]
 constexpr int kHead = 5;       // [5..9] work heads of tiers 0..4
-constexpr int kSeg = 10;       // [10..14] queue start of segments 0..3, then 2n
-constexpr int kBandHead = 15;  // work head of the band tier
-constexpr int kResumed = 16;   // [16..19] moves out of windows 0..3 that carried their state
-constexpr int kSegHead1 = 20;  // work head of the 128-cell window's queue segment (batched form)
-constexpr int kCtrWords = 32;
+constexpr int kSeg = 10;       // [10..18] queue starts of the segments (k_bin_scan), then 2n
+constexpr int kBandHead = 19;  // work head of the band tier
+constexpr int kResumed = 20;   // [20..23] moves out of windows 0..3 that carried their state
+constexpr int kSegHead1 = 24;  // work head of the 128-cell window's queue segment (batched form)
+constexpr int kLaneHead = 25;  // [25..27] work heads of the lane tiers
+constexpr int kLongHead = 28;  // work head of segment kSegLong
+constexpr int kCtrWords = 64;
+// queue segments, in queue order
+// (with lane tiers kSeg64 holds the longest extensions of the narrow and the
+// 64-row class, and kSegLong those of the 96-row class)
+enum { kSeg64 = 0, kSegLane, kSegNarrow, kSegLong, kSegWide, kSeg128, kSeg256, kSegInvalid,
+       kSegEnd };
 constexpr int kTierArgsBytes = 8 * 256;  // >= sizeof(TierPack), checked below
 constexpr uint64_t kFixedBytes = (kBins * 4 + kCtrWords * 4 + kTierArgsBytes + 255) & ~255ull;
 
@@ -220,7 +237,7 @@ Scratch scratch_carve(char* base, uint64_t n, const BandGeom& g) {
 
 // Arguments of a persistent tier.
 struct TierArgs {
-  BatchArgs A;
+  TaskArgs A;
   const uint32_t* queue;
   const uint32_t* seg;      // [2]: this tier's queue segment, or null
   const uint32_t* in_list;  // overflow of the previous tier, or null
@@ -237,13 +254,16 @@ static_assert(xd::kBandedMaxW == XD_BAND_MAX, "band limit");
 static_assert(sizeof(TierArgs) % 4 == 0, "tier arguments copied by words");
 
 struct TierPack {
-  TierArgs t[7];  // [6]: the 128-cell window's queue segment alone (batched form)
+  // [6]: the 128-cell window's queue segment alone, or with lane tiers the
+  // longest extensions of the 96-row one (batched form); [7..9]: the lane
+  // tiers of 64, 32 and 96 rows
+  TierArgs t[10];
   xd::pair::Shared pz;  // scalars of the packed 64-cell tier
 };
 static_assert(sizeof(TierPack) <= kTierArgsBytes, "tier argument area");
 
 // ---- per-task validation (shared by the extension and combine kernels) ----
-__device__ __forceinline__ int32_t task_status(const BatchArgs& A, uint32_t t, uint32_t& ra,
+__device__ __forceinline__ int32_t task_status(const TaskArgs& A, uint32_t t, uint32_t& ra,
                                                uint32_t& rb, uint32_t& pa, uint32_t& pb,
                                                int32_t& X) {
   ra = A.pairs[2 * (uint64_t)t];
@@ -260,7 +280,7 @@ __device__ __forceinline__ int32_t task_status(const BatchArgs& A, uint32_t t, u
 }
 
 // Characters available to extension e (even: left of the seed, odd: right).
-__device__ __forceinline__ void ext_lengths(const BatchArgs& A, uint32_t e, uint32_t pa,
+__device__ __forceinline__ void ext_lengths(const TaskArgs& A, uint32_t e, uint32_t pa,
                                             uint32_t pb, int32_t la, int32_t lb, int32_t& m,
                                             int32_t& n) {
   if (e & 1) {
@@ -273,7 +293,7 @@ __device__ __forceinline__ void ext_lengths(const BatchArgs& A, uint32_t e, uint
 }
 
 // Inputs of extension e (wave-uniform); false if its task is invalid.
-__device__ __forceinline__ bool make_ext(const BatchArgs& A, uint32_t e, xd::Ext& ex) {
+__device__ __forceinline__ bool make_ext(const TaskArgs& A, uint32_t e, xd::Ext& ex) {
   const uint32_t t = e >> 1;
   uint32_t ra, rb, pa, pb;
   int32_t X;
@@ -350,7 +370,7 @@ __device__ __forceinline__ void overflow_to(ExtOut* ext, uint32_t* list, uint32_
 // narrower window's state (resume non-null).  Returns false if it overflowed
 // this tier's window (SAVE: its state is then at the start of ring).
 template <int CPL, int GS, bool UNIT, bool SAVE, bool RESUME>
-__device__ __forceinline__ bool run_ext(const BatchArgs& A, uint32_t e, uint32_t* ring,
+__device__ __forceinline__ bool run_ext(const TaskArgs& A, uint32_t e, uint32_t* ring,
                                         const uint8_t* resume) {
   xd::Ext ex;
   if (!make_ext(A, e, ex)) {
@@ -364,6 +384,26 @@ __device__ __forceinline__ bool run_ext(const BatchArgs& A, uint32_t e, uint32_t
   if (!xd::extend<CPL, GS, UNIT, SAVE, RESUME>(ex, A.sc, ring, o, resume)) return false;
   if (xd::lane_id() == 0) A.ext[e] = o;
   return true;
+}
+
+// One block per read: its bases in bit planes (lane_core.h).
+__global__ __launch_bounds__(256) void k_planes(StoreDev st, xd::lane::Chunk* planes) {
+  const uint32_t r = blockIdx.x;
+  const uint32_t len = st.len[r], n_words = (len + 15) / 16;
+  const uint32_t* w = st.words + st.word_off[r];
+  xd::lane::Chunk* dst = planes + st.plane_off[r];
+  // every other bit of v, packed into the low half
+  auto even = [](uint32_t v) -> uint32_t {
+    v &= 0x55555555u;
+    v = (v | v >> 1) & 0x33333333u;
+    v = (v | v >> 2) & 0x0f0f0f0fu;
+    v = (v | v >> 4) & 0x00ff00ffu;
+    return (v | v >> 8) & 0xffffu;
+  };
+  for (uint32_t c = threadIdx.x; 32 * c < len; c += 256) {
+    const uint32_t x = w[2 * c], y = 2 * c + 1 < n_words ? w[2 * c + 1] : 0u;
+    dst[c] = xd::lane::Chunk{even(x) | even(y) << 16, even(x >> 1) | even(y >> 1) << 16};
+  }
 }
 
 // zero the counters and the histogram (a kernel rather than a memset so that
@@ -402,14 +442,8 @@ __global__ __launch_bounds__(64) void k_ext_first(BatchArgs A, uint32_t e0, uint
 // VGPRs, 6 waves per SIMD; its list, which resumes and saves, and the
 // 256-cell window to 96, 5 waves; the 512-cell window, in groups of 2
 // antidiagonals, to 128, 4 waves; none of them spills a vector register)
-template <int CPL, int GS, bool UNIT, int WAVES, bool SAVE, bool RESUME>
-__global__ __launch_bounds__(64 * WAVES)
-__attribute__((amdgpu_waves_per_eu(CPL == 2 ? (SAVE ? 5 : 6) : CPL == 4 ? 5 : CPL == 8 ? 4 : 1)))
-void k_ext_tier(const TierArgs* __restrict__ P) {
-  static_assert(WAVES * xd::Tier<CPL, GS>::LDS_WORDS * 4 <= 64 * 1024, "LDS per block");
-  __shared__ uint32_t rings[WAVES][xd::Tier<CPL, GS>::LDS_WORDS];
-  const int w = threadIdx.x >> 6;
-  const TierArgs* pp = P;
+template <int CPL, int GS, bool UNIT, bool SAVE, bool RESUME>
+__device__ __forceinline__ void run_tier(const TierArgs* pp, uint32_t* ring) {
   XD_STAMP_T0();
 #ifdef XD_WAVE_STAMPS
   uint32_t taken = 0;
@@ -435,14 +469,23 @@ void k_ext_tier(const TierArgs* __restrict__ P) {
 #ifdef XD_WAVE_STAMPS
     ++taken;
 #endif
-    if (!run_ext<CPL, GS, UNIT, SAVE, RESUME>(Q.A, e, rings[w], resume)) {
+    if (!run_ext<CPL, GS, UNIT, SAVE, RESUME>(Q.A, e, ring, resume)) {
       const TierArgs& R = *pp;
       // (a kernel that saves nothing leaves no state to keep)
       overflow_to(R.A.ext, R.out_list, R.out_count, SAVE ? R.out_state : nullptr, R.out_cap,
-                  R.out_rec, e, rings[w]);
+                  R.out_rec, e, ring);
     }
   }
   XD_STAMP(stamps::kTier + CPL, taken);
+}
+
+template <int CPL, int GS, bool UNIT, int WAVES, bool SAVE, bool RESUME>
+__global__ __launch_bounds__(64 * WAVES)
+__attribute__((amdgpu_waves_per_eu(CPL == 2 ? (SAVE ? 5 : 6) : CPL == 4 ? 5 : CPL == 8 ? 4 : 1)))
+void k_ext_tier(const TierArgs* __restrict__ P) {
+  static_assert(WAVES * xd::Tier<CPL, GS>::LDS_WORDS * 4 <= 64 * 1024, "LDS per block");
+  __shared__ uint32_t rings[WAVES][xd::Tier<CPL, GS>::LDS_WORDS];
+  run_tier<CPL, GS, UNIT, SAVE, RESUME>(P, rings[threadIdx.x >> 6]);
 }
 
 // The batched form's 64-cell tier for match = 1 with two extensions per wave
@@ -585,6 +628,95 @@ void k_pair4_tier(const TierArgs* __restrict__ P,
   XD_STAMP(stamps::kPair4, W.taken);
 }
 
+// Work of the lane tiers: a queue segment, claimed a few entries at a time.
+struct LaneWork {
+  const TierArgs* pp;
+  uint32_t seg_lo, seg_len;
+
+  __device__ uint32_t grab(uint32_t n, uint32_t& idx) {
+    uint32_t i = 0;
+    if (xd::lane_id() == 0) i = atomicAdd(pp->head, n);
+    i = __builtin_amdgcn_readfirstlane(__shfl(i, 0, 64));
+    if (i >= seg_len) return 0u;
+    idx = seg_lo + i;
+    return min(n, seg_len - i);
+  }
+  // (queue segments hold valid tasks only)
+  __device__ void describe(uint32_t idx, xd::lane::Item& it) {
+    const TaskArgs& A = pp->A;
+    const uint32_t e = pp->queue[idx], t = e >> 1;
+    const uint32_t ra = A.pairs[2 * (uint64_t)t], rb = A.pairs[2 * (uint64_t)t + 1];
+    const uint32_t pa = A.seeds[2 * (uint64_t)t], pb = A.seeds[2 * (uint64_t)t + 1];
+    const int32_t la = (int32_t)A.st.len[ra], lb = (int32_t)A.st.len[rb];
+    const bool rc = A.flags && (A.flags[t] & 1u);
+    it.e = e;
+    it.t.X = A.x ? A.x[t] : A.x_scalar;
+    it.t.ra = A.st.planes + A.st.plane_off[ra];
+    it.t.rb = A.st.planes + A.st.plane_off[rb];
+    it.t.ca = (la + 31) >> 5;
+    it.t.cb = (lb + 31) >> 5;
+    ext_lengths(A, e, pa, pb, la, lb, it.t.m, it.t.n);
+    const bool right = (e & 1) != 0;
+    it.t.oa = right ? (int32_t)pa + A.k : (int32_t)pa - 1;
+    it.t.ob = right ? (int32_t)pb + A.k : (int32_t)pb - 1;
+    it.t.flags = (right ? 0u : xd::lane::kBackA) | (right != rc ? 0u : xd::lane::kBackB) |
+                 (rc ? xd::lane::kComp : 0u);
+    // B reverse-complemented: walked the other way from the mirrored start
+    if (rc) it.t.ob = lb - 1 - it.t.ob;
+  }
+  __device__ void done(uint32_t e, const ExtOut& o) { pp->A.ext[e] = o; }
+  // a place in the next tier's list, and where the state goes if it is kept
+  __device__ uint8_t* overflow(uint32_t& slot) {
+    const TierArgs& R = *pp;
+    slot = 0;
+    if (xd::lane_id() == 0) slot = atomicAdd(R.out_count, 1u);
+    slot = __builtin_amdgcn_readfirstlane(__shfl(slot, 0, 64));
+    if (slot >= R.out_cap) return nullptr;
+    if (xd::lane_id() == 0) atomicAdd(R.out_count + (kResumed - kOvfCount), 1u);
+    return R.out_state + (uint64_t)slot * R.out_rec;
+  }
+  __device__ void list(uint32_t slot, uint32_t e, bool kept) {
+    if (xd::lane_id() == 0) pp->out_list[slot] = e | (kept ? kResumeFlag : 0u);
+  }
+};
+
+// The lane tiers (xd::lane, W * 32 rows) in the first lane_blocks workgroups.
+// Bound by vector issue: 129 instructions a step for 64 extensions of 64 rows
+// (P = 6), 65 for 32 rows (P = 5), 208 for 96 rows (P = 7), against 6.2 a step
+// and extension in the packed 64-cell kernel.  100,000 pairs of 10 kbp at X = 25:
+// 13.48 -> 5.85 ms; 400,000 seeds at X of 7, 25 and 50: 83.3 -> 28.2 ms.  One
+// workgroup per CU: a lane's step then takes about 0.24 us, and with two it
+// takes twice that for the same rate, so the longest extensions end later
+// (12.0 ms against 7.9 for the 100,000 pairs).
+// The others (W >= 2) run the class's longest extensions (k_bin_scan), one
+// per wavefront: a lane takes several times longer for a step.
+template <int P, int W>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W == 3 ? 3 : 4)))
+void k_lane_tier(const TierArgs* __restrict__ LP, const TierArgs* __restrict__ PP,
+                 uint32_t lane_blocks) {
+  constexpr int kCpl = W == 3 ? 2 : 1, kGs = W == 3 ? 8 : 16;
+  constexpr int kRing = W >= 2 ? xd::Tier<kCpl, kGs>::LDS_WORDS : 0;
+  constexpr int kWords = kRing > xd::lane::LDS_WORDS ? kRing : xd::lane::LDS_WORDS;
+  __shared__ uint32_t lds[4][kWords];
+  const int w = threadIdx.x >> 6;
+  if (blockIdx.x < lane_blocks) {
+    const TierArgs& Q = *LP;
+    LaneWork wk;
+    wk.pp = LP;
+    wk.seg_lo = __builtin_amdgcn_readfirstlane(Q.seg[0]);
+    wk.seg_len = __builtin_amdgcn_readfirstlane(Q.seg[1]) - wk.seg_lo;
+    if (wk.seg_len == 0) return;
+    XD_STAMP_T0();
+    xd::lane::run<P, W>(wk, lds[w], LP->A.st.planes + xd::lane::kGuard);
+    XD_STAMP(stamps::kLane + W, 1u);
+    return;
+  }
+  if constexpr (W >= 2) {
+    __builtin_amdgcn_s_setprio(3);
+    run_tier<kCpl, kGs, true, true, false>(PP, lds[w]);
+  }
+}
+
 // Band tier: persistent workgroups of kBandWaves waves, each taking the next
 // extension of in_list (what overflowed the 1024-cell window) and running it
 // with its rows in its own part of band.
@@ -623,28 +755,44 @@ __global__ __launch_bounds__(64 * kBandWaves) void k_ext_band(const TierArgs* __
 struct BinRule {
   int32_t x_tier1, x_tier2;  // X limits of the 64- and 128-cell first tiers
   int32_t by_cost;           // 0: keep task order inside a tier
+  uint32_t lanes;            // lanes of a lane tier's launch (0: no lane tiers)
 };
 
-// Sort key of extension e, ascending = processing order: first tier from X,
-// then 8 bins per octave of the estimated antidiagonal count (a true overlap
-// extends along the diagonal until the shorter side runs out, about
-// 2*min(m, n) antidiagonals), longest first.  Invalid tasks sort last, into
-// a segment that is never run.
-__device__ __forceinline__ uint32_t ext_key(const BatchArgs& A, const BinRule& R, uint32_t e) {
+// Length bin of an estimated antidiagonal count, 6 per octave from 64 on.
+__device__ __forceinline__ uint32_t cost_bin(uint32_t cost) {
+  if (cost < 64u) return 0u;
+  const uint32_t ex = 31u - __builtin_clz(cost);
+  const uint32_t sub = (((cost >> (ex - 3)) & 7u) * 6u) >> 3;
+  return min(1u + (ex - 6u) * 6u + sub, (uint32_t)kCostBins - 1u);
+}
+// the middle of a length bin
+__device__ __forceinline__ uint32_t bin_cost(uint32_t cb) {
+  if (cb == 0) return 32u;
+  const uint32_t ex = (cb - 1) / 6, sub = (cb - 1) % 6;
+  return ((64u << ex) / 12u) * (13u + 2u * sub);
+}
+
+// Sort key of extension e: class from X (its first tier), then the length
+// bin of the estimated antidiagonal count (a true overlap extends along the
+// diagonal until the shorter side runs out, about 2*min(m, n)
+// antidiagonals), longest first.  k_bin_scan places the keys in the queue;
+// invalid tasks sort last, into a segment that is never run.
+__device__ __forceinline__ uint32_t ext_key(const TaskArgs& A, const BinRule& R, uint32_t e) {
   uint32_t ra, rb, pa, pb;
   int32_t X;
-  // invalid tasks go to segment 3, which no tier runs: the combine writes
-  // their status without reading extension results
+  // invalid tasks go to the last segment, which no tier runs: the combine
+  // writes their status without reading extension results
   if (task_status(A, e >> 1, ra, rb, pa, pb, X) != XD_TASK_OK) return kBins - 1;
-  const uint32_t tier = X <= R.x_tier1 ? 0u : X <= R.x_tier2 ? 1u : 2u;
-  if (!R.by_cost) return tier * kCostBins;
+  uint32_t cls = X <= R.x_tier1 ? kCls64 : X <= R.x_tier2 ? kCls128 : kCls256;
+  if (R.lanes && X <= xd::lane::x_limit(7))  // the planes a lane needs
+    cls = X <= xd::lane::x_limit(5) ? kClsNarrow : X <= xd::lane::x_limit(6) ? kClsLane : kClsWide;
+  else if (R.lanes && cls == kCls64)
+    cls = kCls128;
+  if (!R.by_cost) return cls * kCostBins;
   int32_t m, n;
   ext_lengths(A, e, pa, pb, (int32_t)A.st.len[ra], (int32_t)A.st.len[rb], m, n);
-  const uint32_t cost = 2u * (uint32_t)min(m, n) + 2u;
-  const uint32_t ex = 31u - __builtin_clz(cost);
-  const uint32_t mant = ex >= 3 ? (cost >> (ex - 3)) & 7u : 0u;
-  const uint32_t cb = min(ex * 8u + mant, (uint32_t)kCostBins - 1);
-  return tier * kCostBins + (kCostBins - 1 - cb);
+  const uint32_t cb = cost_bin(2u * (uint32_t)min(m, n) + 2u);
+  return cls * kCostBins + (kCostBins - 1 - cb);
 }
 
 __global__ __launch_bounds__(256) void k_bin_hist(BatchArgs A, BinRule R, uint32_t n_ext,
@@ -659,21 +807,100 @@ __global__ __launch_bounds__(256) void k_bin_hist(BatchArgs A, BinRule R, uint32
     if (h[b]) atomicAdd(&hist[b], h[b]);
 }
 
-// hist[b] <- number of extensions with a smaller key (queue start of key b);
-// seg[t] <- queue start of segment t (segments 0..2: first tiers from X;
-// segment 3: invalid tasks, never run), seg[4] = n_ext
-__global__ __launch_bounds__(256) void k_bin_scan(uint32_t* hist, uint32_t* seg,
+// hist[b] <- queue start of key b; seg[t] <- queue start of segment t
+// (seg[kSegEnd] = n_ext).
+//
+// A lane class's longest extensions run one per wavefront beside the lanes
+// (segments kSeg64 and kSegLong): a lane takes kLaneSlots vector instructions
+// for a step and shares them with 63 others, a wavefront of its own kSolo of
+// them, with a chain of about kSoloChain issue slots.  The split is the one
+// with the smallest estimate of when the last of these ends: the lanes'
+// longest extension, the longest of all, and the instructions of both.
+constexpr uint32_t kStall = 10;  // eighths: a lane's step against its issue slots
+struct LaneCost {
+  uint32_t lane, solo, chain;  // issue slots a step
+};
+__device__ __forceinline__ LaneCost lane_cost(uint32_t cls) {
+  return cls == kClsNarrow ? LaneCost{72, 9, 25} : cls == kClsLane ? LaneCost{140, 9, 25}
+                                                                   : LaneCost{230, 16, 45};
+}
+
+__device__ __forceinline__ uint32_t lane_split(const uint32_t* count, uint32_t cls,
+                                               uint32_t lanes) {
+  const LaneCost c = lane_cost(cls);
+  uint64_t rest = 0;
+  for (uint32_t q = 0; q < kCostBins; ++q)
+    rest += (uint64_t)count[q] * bin_cost(kCostBins - 1 - q);
+  uint64_t solo = 0, best = ~0ull, longest = 0;
+  uint32_t at = 0;
+  for (uint32_t s = 0;; ++s) {  // the first s bins run alone
+    const uint64_t next = s < kCostBins ? bin_cost(kCostBins - 1 - s) : 0u;
+    const uint64_t alone = solo * c.solo * 64 / lanes;  // slots of the wavefronts of their own
+    const uint64_t chain = max(rest / lanes, rest ? next : 0ull) * c.lane * kStall / 8 + alone / 2;
+    const uint64_t t = max(max(chain, alone + rest * c.lane / lanes), longest * c.chain);
+    if (t < best && (s == kCostBins || count[s] || !rest)) {
+      best = t;
+      at = s;
+    }
+    if (s == kCostBins) break;
+    const uint64_t w = (uint64_t)count[s] * next;
+    if (w && !longest) longest = next;
+    solo += w;
+    rest -= w;
+  }
+  return at;
+}
+
+__global__ __launch_bounds__(512) void k_bin_scan(uint32_t* hist, uint32_t* seg, BinRule R,
                                                   uint32_t n_ext) {
   __shared__ uint32_t h[kBins];
-  for (int b = threadIdx.x; b < kBins; b += 256) h[b] = hist[b];
+  __shared__ uint32_t split[4];  // bins of a lane class that run one per wavefront
+  const uint32_t b = threadIdx.x;
+  const uint32_t mine = hist[b];
+  h[b] = mine;
   __syncthreads();
-  for (int b = threadIdx.x; b < kBins; b += 256) {
-    uint32_t below = 0;
-    for (int q = 0; q < b; ++q) below += h[q];
-    hist[b] = below;
-    if (b % kCostBins == 0) seg[b / kCostBins] = below;
+  if (b < 4) {
+    uint32_t s = 0;
+    if (R.lanes && (b == kClsNarrow || b == kClsLane || b == kClsWide))
+      s = lane_split(h + b * kCostBins, b, R.lanes);
+    split[b] = s;
   }
-  if (threadIdx.x == 0) seg[4] = n_ext;
+  __syncthreads();
+  // the bins in queue order
+  const uint32_t s0 = split[kClsNarrow], s1 = split[kClsLane], s3 = split[kClsWide];
+  const uint32_t cls = min(b / kCostBins, (uint32_t)kClsInvalid), q = b - cls * kCostBins;
+  constexpr uint32_t N = kCostBins;
+  uint32_t at = b;  // the classes from 256 cells on keep their place
+  if (cls == kCls64) at = q;
+  else if (cls == kClsLane) at = q < s1 ? N + q : N + s1 + s0 + (q - s1);
+  else if (cls == kClsNarrow) at = q < s0 ? N + s1 + q : 2 * N + s0 + (q - s0);
+  else if (cls == kClsWide) at = 3 * N + q;  // (its longest come first already)
+  else if (cls == kCls128) at = 4 * N + q;
+  __syncthreads();
+  h[at] = mine;
+  __syncthreads();
+  // inclusive scan of the 512 counts
+  uint32_t v = h[b];
+  for (uint32_t o = 1; o < kBins; o <<= 1) {
+    const uint32_t a = b >= o ? h[b - o] : 0u;
+    __syncthreads();
+    v += a;
+    h[b] = v;
+    __syncthreads();
+  }
+  hist[b] = h[at] - mine;
+  auto start = [&](uint32_t slot) { return slot ? h[slot - 1] : 0u; };
+  if (b == 0) {
+    seg[kSeg64] = 0;
+    seg[kSegLane] = start(N + s1 + s0);
+    seg[kSegNarrow] = start(2 * N + s0);
+    seg[kSegLong] = start(3 * N);
+    seg[kSegWide] = start(3 * N + s3);
+    seg[kSeg128] = start(4 * N);
+    seg[kSeg256] = start(5 * N);
+    seg[kSegInvalid] = start(6 * N);
+    seg[kSegEnd] = n_ext;
+  }
 }
 
 // Each block places kScatterItems extensions: it counts its keys in LDS,
@@ -1124,6 +1351,9 @@ bool pair_ok(const xd::Scoring& sc) {
   return sc.M == 1 && sc.MM + 2 * g >= 0 && g <= xd::pair::kGapMax;
 }
 
+// The lane tiers are written for match = 1, mismatch = -1, gap = -1.
+bool lane_ok(const xd::Scoring& sc) { return sc.M == 1 && sc.MM == -1 && sc.G == -1; }
+
 xd::pair::Shared pair_shared(const xd::Scoring& sc) {
   const int32_t g = -sc.G;
   const uint32_t C = (uint32_t)(sc.MM + 2 * g);
@@ -1136,30 +1366,66 @@ xd::pair::Shared pair_shared(const xd::Scoring& sc) {
   return z;
 }
 
+// Which kernels a batch runs in.
+struct Route {
+  bool queue;            // the device queue (batched form)
+  bool packed;           // two extensions per wavefront in the 64-, 128- and 256-cell windows
+  uint32_t lane_blocks;  // workgroups of the lane tiers (0: none)
+};
+
+// Extensions from which the lane tiers run: they hold 65,536 at once, and a
+// batch of half as many leaves most of them to wavefronts of their own.  Read
+// pairs of 10 kbp at X = 25, one per wavefront / packed / lanes: 8,000 pairs
+// 3.03 / 4.11 / 2.90 ms, 16,000 3.24 / 4.30 / 3.11, 32,000 5.83 / 4.86 / 4.40.
+constexpr uint64_t kLaneMin = 32768;
+
+Route batch_route(const xd::Scoring& sc, uint64_t n_ext, bool queue) {
+  Route r = {queue, false, 0u};
+  if (!queue) return r;
+  if (lane_ok(sc) && n_ext >= kLaneMin) r.lane_blocks = (uint32_t)device_cus();
+  r.packed = pair_ok(sc);
+  return r;
+}
+
 // tier arguments: tier 0 (64 cells, batched form), tiers 1..4 (128, 256, 512,
 // 1024 cells) and the band tier, each with its queue segment (batched form;
 // segments 0..2 hold the extensions whose X picks that first tier) and the
 // overflow list of the tier below
-TierPack make_pack(const BatchArgs& A, const Scratch& S, bool segs) {
+TierPack make_pack(const BatchArgs& A, const Scratch& S, const Route& R) {
   uint32_t* c = S.ctr;
-  TierPack p;
-  p.t[0] = {A, S.queue, c + kSeg + 0, nullptr, nullptr, c + kHead + 0, S.ovf[0],
+  const bool segs = R.queue;
+  TierPack p = {};
+  p.t[0] = {A, S.queue, c + kSeg + kSeg64, nullptr, nullptr, c + kHead + 0, S.ovf[0],
             c + kOvfCount + 0};
-  // the 128-cell window's list (what outgrew 64 cells, resumable onwards)
-  // and its queue segment (batched form: X in (x_tier1, x_tier2], started
-  // here; they leave no state, so that the kernel that runs them keeps the
-  // register budget of one without saving) run as two launches
-  p.t[1] = {A, S.queue, nullptr, S.ovf[0], c + kOvfCount + 0, c + kHead + 1, S.ovf[1],
-            c + kOvfCount + 1};
-  p.t[6] = {A, S.queue, segs ? c + kSeg + 1 : nullptr, nullptr, nullptr, c + kSegHead1,
-            S.ovf[1], c + kOvfCount + 1};
-  p.t[2] = {A, S.queue, segs ? c + kSeg + 2 : nullptr, S.ovf[1], c + kOvfCount + 1,
+  // the 128-cell window's queue segment (batched form: X in (x_tier1, x_tier2],
+  // started here) and its list (what outgrew 64 cells, resumable onwards) run
+  // as one launch of the packed kernel, or as two of the 32-bit ones, whose
+  // first leaves no state and so keeps the register budget of one without
+  // saving
+  p.t[1] = {A, S.queue, segs && R.packed ? c + kSeg + kSeg128 : nullptr, S.ovf[0],
+            c + kOvfCount + 0, c + kHead + 1, S.ovf[1], c + kOvfCount + 1};
+  p.t[6] = {A, S.queue, nullptr, nullptr, nullptr, c + kSegHead1, S.ovf[1], c + kOvfCount + 1};
+  if (R.lane_blocks) {
+    p.t[6].seg = c + kSeg + kSegLong;
+    p.t[6].head = c + kLongHead;
+  } else if (segs) {
+    p.t[6].seg = c + kSeg + kSeg128;
+  }
+  p.t[2] = {A, S.queue, segs ? c + kSeg + kSeg256 : nullptr, S.ovf[1], c + kOvfCount + 1,
             c + kHead + 2, S.ovf[2], c + kOvfCount + 2};
   p.t[3] = {A, S.queue, nullptr, S.ovf[2], c + kOvfCount + 2, c + kHead + 3, S.ovf[3],
             c + kOvfCount + 3};
   p.t[4] = {A, S.queue, nullptr, S.ovf[3], c + kOvfCount + 3, c + kHead + 4, S.ovf[4],
             c + kOvfCount + 4};
   p.t[5] = {A, S.queue, nullptr, S.ovf[4], c + kOvfCount + 4, c + kBandHead, nullptr, nullptr};
+  // the lane tiers: what outgrows 64 or 32 rows goes to the 128-cell list,
+  // what outgrows 96 rows to the 256-cell one
+  p.t[7] = {A, S.queue, c + kSeg + kSegLane, nullptr, nullptr, c + kLaneHead + 0, S.ovf[0],
+            c + kOvfCount + 0};
+  p.t[8] = {A, S.queue, c + kSeg + kSegNarrow, nullptr, nullptr, c + kLaneHead + 1, S.ovf[0],
+            c + kOvfCount + 0};
+  p.t[9] = {A, S.queue, c + kSeg + kSegWide, nullptr, nullptr, c + kLaneHead + 2, S.ovf[1],
+            c + kOvfCount + 1};
   // resume states: window t leaves them in pool t, window t + 1 reads them;
   // the band tier re-runs what outgrows the 1024-cell window
   for (int t = 0; t < 7; ++t) {
@@ -1171,14 +1437,22 @@ TierPack make_pack(const BatchArgs& A, const Scratch& S, bool segs) {
     T.out_rec = t <= 3 ? (uint32_t)resume_rec(t) : 0u;
     T.pad = 0;
   }
-  // the 128-cell queue segment starts its extensions; the packed kernel that
-  // runs it (match = 1) leaves the state of what outgrows it in pool 1, as
-  // the 128-cell list does (the two share that list and its slots)
+  // these start their extensions; what outgrows 128 cells shares a list and
+  // its state slots with what outgrows the 128-cell list
   p.t[6].in_state = nullptr;
   p.t[6].in_rec = 0u;
   p.t[6].out_state = S.state[1];
   p.t[6].out_cap = S.state_cap[1];
   p.t[6].out_rec = (uint32_t)resume_rec(1);
+  for (int t = 7; t < 10; ++t) {
+    const int pool = t == 9 ? 1 : 0;
+    p.t[t].in_state = nullptr;
+    p.t[t].in_rec = 0u;
+    p.t[t].out_state = S.state[pool];
+    p.t[t].out_cap = S.state_cap[pool];
+    p.t[t].out_rec = (uint32_t)resume_rec(pool);
+    p.t[t].pad = 0;
+  }
   p.pz = pair_shared(A.sc);
   return p;
 }
@@ -1189,13 +1463,13 @@ TierPack make_pack(const BatchArgs& A, const Scratch& S, bool segs) {
 // and save, 1024 resumes; the 128-cell queue segment starts its extensions
 // and saves nothing.
 template <bool UNIT>
-void launch_wide(const Scratch& S, uint32_t blocks, hipStream_t stream, bool segs,
-                 bool packed) {
+void launch_wide(const Scratch& S, uint32_t blocks, hipStream_t stream, const Route& R) {
   const TierArgs* ta = (const TierArgs*)S.targs;
-  if (segs && packed)
-    hipLaunchKernelGGL((k_pair2_tier<4>), dim3(blocks), dim3(256), 0, stream, ta + 6,
-                       &((const TierPack*)S.targs)->pz);
-  else if (segs)
+  const bool packed = R.packed;
+  if (R.lane_blocks)
+    hipLaunchKernelGGL((k_lane_tier<7, 3>), dim3(R.lane_blocks + blocks), dim3(256), 0, stream,
+                       ta + 9, ta + 6, R.lane_blocks);
+  else if (R.queue && !packed)
     hipLaunchKernelGGL((k_ext_tier<2, 8, UNIT, 4, false, false>), dim3(blocks), dim3(256), 0,
                        stream, ta + 6);
   if (packed)
@@ -1226,9 +1500,17 @@ void launch_pair(const Scratch& S, uint32_t blocks, hipStream_t stream) {
                      &tp->t[0], &tp->pz);
 }
 
+void launch_lane(const Scratch& S, uint32_t lane_blocks, uint32_t blocks, hipStream_t stream) {
+  const TierArgs* ta = (const TierArgs*)S.targs;
+  hipLaunchKernelGGL((k_lane_tier<6, 2>), dim3(lane_blocks + blocks), dim3(256), 0, stream,
+                     ta + 7, ta + 0, lane_blocks);
+  hipLaunchKernelGGL((k_lane_tier<5, 1>), dim3(lane_blocks), dim3(256), 0, stream, ta + 8,
+                     ta + 0, lane_blocks);
+}
+
 template <bool UNIT>
-void launch_plain_ext(const BatchArgs& A, const Scratch& S, uint64_t n_ext, hipEvent_t* ev,
-                      hipStream_t stream) {
+void launch_plain_ext(const BatchArgs& A, const Scratch& S, uint64_t n_ext, const Route& R,
+                      hipEvent_t* ev, hipStream_t stream) {
   // a grid holds at most 2^32 - 1 work-items: launch in chunks of 2^24 waves
   for (uint64_t e0 = 0; e0 < n_ext; e0 += kChunkBlocks) {
     const uint64_t nb = std::min<uint64_t>(kChunkBlocks, n_ext - e0);
@@ -1236,31 +1518,33 @@ void launch_plain_ext(const BatchArgs& A, const Scratch& S, uint64_t n_ext, hipE
                        (uint32_t)e0, S.ovf[0], S.ctr + kOvfCount + 0);
   }
   if (ev) (void)hipEventRecord(ev[1], stream);
-  launch_wide<UNIT>(S, kWideBlocks / 4, stream, false, false);
+  launch_wide<UNIT>(S, kWideBlocks / 4, stream, R);
   if (ev) (void)hipEventRecord(ev[2], stream);
 }
 
 template <bool UNIT, int GS>
 void launch_tier0(const Scratch& S, uint32_t blocks, hipStream_t stream) {
   hipLaunchKernelGGL((k_ext_tier<1, GS, UNIT, 4, false, false>), dim3(blocks), dim3(256), 0,
-                     stream,
-                     (const TierArgs*)S.targs);
+                     stream, (const TierArgs*)S.targs);
 }
 
 template <bool UNIT>
 void launch_persistent_ext(const BatchArgs& A, const Scratch& S, uint64_t n_ext,
-                           const Tuned& tu, hipEvent_t* ev, hipStream_t stream) {
+                           const Tuned& tu, const Route& Rt, hipEvent_t* ev,
+                           hipStream_t stream) {
   const uint32_t grid = (uint32_t)((n_ext + 255) / 256);
-  BinRule R = {tu.x_tier1, tu.x_tier2, tu.order == 1 ? 1 : 0};
+  BinRule R = {tu.x_tier1, tu.x_tier2, tu.order == 1 ? 1 : 0, Rt.lane_blocks * 256u};
   hipLaunchKernelGGL(k_bin_hist, dim3(grid), dim3(256), 0, stream, A, R, (uint32_t)n_ext,
                      S.hist);
-  hipLaunchKernelGGL(k_bin_scan, dim3(1), dim3(256), 0, stream, S.hist, S.ctr + kSeg,
+  hipLaunchKernelGGL(k_bin_scan, dim3(1), dim3(kBins), 0, stream, S.hist, S.ctr + kSeg, R,
                      (uint32_t)n_ext);
   hipLaunchKernelGGL(k_bin_scatter, dim3((uint32_t)((n_ext + kScatterItems - 1) / kScatterItems)),
                      dim3(256), 0, stream, A, R, (uint32_t)n_ext, S.hist, S.queue);
   uint32_t blocks = (uint32_t)device_cus() * (uint32_t)tu.waves_per_cu / 4u;
   if (blocks < 1) blocks = 1;
-  if (UNIT && pair_ok(A.sc))
+  if (Rt.lane_blocks)
+    launch_lane(S, Rt.lane_blocks, blocks, stream);
+  else if (Rt.packed)
     launch_pair(S, blocks, stream);
   else if (tu.group_steps == 4)
     launch_tier0<UNIT, 4>(S, blocks, stream);
@@ -1269,7 +1553,7 @@ void launch_persistent_ext(const BatchArgs& A, const Scratch& S, uint64_t n_ext,
   else
     launch_tier0<UNIT, 8>(S, blocks, stream);
   if (ev) (void)hipEventRecord(ev[1], stream);
-  launch_wide<UNIT>(S, blocks, stream, true, UNIT && pair_ok(A.sc));
+  launch_wide<UNIT>(S, blocks, stream, Rt);
   if (ev) (void)hipEventRecord(ev[2], stream);
 }
 
@@ -1374,6 +1658,9 @@ struct xd_store {
   uint32_t* words = nullptr;
   uint64_t* word_off = nullptr;
   uint32_t* len = nullptr;
+  xd::lane::Chunk* planes = nullptr;  // the bases again, in bit planes
+  uint64_t* plane_off = nullptr;
+  uint64_t n_chunks = 0;
   uint64_t n_words = 0;
   uint32_t n_reads = 0;
   uint32_t max_len = 0;
@@ -1435,7 +1722,8 @@ int make_args(const xd_store* store, const uint32_t* pairs, const uint32_t* seed
     return fail(XD_EINVAL, "null task or result array");
   rc = check_score_range(store->max_len, match);
   if (rc) return rc;
-  A.st = {store->words, store->word_off, store->len, store->n_reads};
+  A.st = {store->words, store->word_off, store->len, store->planes, store->plane_off,
+          store->n_reads};
   A.pairs = pairs;
   A.seeds = seeds;
   A.x = x;
@@ -1466,20 +1754,21 @@ int enqueue(BatchArgs A, const Scratch& S, bool persistent, const Tuned& tu,
                           hipHostMallocDefault));
     rec.n_ext = n_ext;
   }
+  const Route R = batch_route(A.sc, n_ext, persistent);
   hipLaunchKernelGGL(k_reset, dim3(1), dim3(256), 0, stream, S.ctr, S.hist,
-                     make_pack(A, S, persistent), (uint32_t*)S.targs);
+                     make_pack(A, S, R), (uint32_t*)S.targs);
   if (persistent) {
     if (prof) HIP_TRY(hipEventRecord(rec.ev[0], stream));
     if (unit_scoring(A.sc))
-      launch_persistent_ext<true>(A, S, n_ext, tu, prof ? rec.ev : nullptr, stream);
+      launch_persistent_ext<true>(A, S, n_ext, tu, R, prof ? rec.ev : nullptr, stream);
     else
-      launch_persistent_ext<false>(A, S, n_ext, tu, prof ? rec.ev : nullptr, stream);
+      launch_persistent_ext<false>(A, S, n_ext, tu, R, prof ? rec.ev : nullptr, stream);
   } else {
     if (prof) HIP_TRY(hipEventRecord(rec.ev[0], stream));
     if (unit_scoring(A.sc))
-      launch_plain_ext<true>(A, S, n_ext, prof ? rec.ev : nullptr, stream);
+      launch_plain_ext<true>(A, S, n_ext, R, prof ? rec.ev : nullptr, stream);
     else
-      launch_plain_ext<false>(A, S, n_ext, prof ? rec.ev : nullptr, stream);
+      launch_plain_ext<false>(A, S, n_ext, R, prof ? rec.ev : nullptr, stream);
   }
   hipLaunchKernelGGL(k_combine, dim3((uint32_t)((A.n + 255) / 256)), dim3(256), 0, stream, A);
   if (prof) {
@@ -1649,7 +1938,14 @@ int xd_store_create(const uint32_t* words, uint64_t n_words, const uint64_t* wor
                   (unsigned long long)need, (unsigned long long)n_words);
     if (len[r] > max_len) max_len = len[r];
   }
+  std::vector<uint64_t> plane_off(n_reads ? n_reads : 1);
+  uint64_t n_chunks = xd::lane::kGuard;
+  for (uint32_t r = 0; r < n_reads; ++r) {
+    plane_off[r] = n_chunks;
+    n_chunks += ((uint64_t)len[r] + 31) / 32 + xd::lane::kGuard;
+  }
   xd_store* s = new xd_store();
+  s->n_chunks = n_chunks;
   s->n_words = n_words;
   s->n_reads = n_reads;
   s->max_len = max_len;
@@ -1665,6 +1961,17 @@ int xd_store_create(const uint32_t* words, uint64_t n_words, const uint64_t* wor
     e = hipMemcpy(s->word_off, word_off, n_reads * 8ull, hipMemcpyHostToDevice);
   if (e == hipSuccess && n_reads)
     e = hipMemcpy(s->len, len, n_reads * 4ull, hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = hipMalloc((void**)&s->planes, n_chunks * sizeof(xd::lane::Chunk));
+  if (e == hipSuccess) e = hipMalloc((void**)&s->plane_off, (n_reads ? n_reads : 1) * 8ull);
+  if (e == hipSuccess && n_reads)
+    e = hipMemcpy(s->plane_off, plane_off.data(), n_reads * 8ull, hipMemcpyHostToDevice);
+  if (e == hipSuccess && n_reads) {
+    hipLaunchKernelGGL(k_planes, dim3(n_reads), dim3(256), 0, (hipStream_t) nullptr,
+                       StoreDev{s->words, s->word_off, s->len, s->planes, s->plane_off, n_reads},
+                       s->planes);
+    e = hipGetLastError();
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+  }
   if (e != hipSuccess) {
     int rc = hip_fail(e, "xd_store_create");
     xd_store_destroy(s);
@@ -1694,6 +2001,8 @@ void xd_store_destroy(xd_store* s) {
   (void)hipFree(s->words);
   (void)hipFree(s->word_off);
   (void)hipFree(s->len);
+  (void)hipFree(s->planes);
+  (void)hipFree(s->plane_off);
   (void)hipSetDevice(cur);
   delete s;
 }
@@ -1701,7 +2010,9 @@ void xd_store_destroy(xd_store* s) {
 int xd_store_info(const xd_store* s, uint64_t* device_bytes, uint32_t* n_reads,
                   uint32_t* max_len) {
   if (!s) return fail(XD_EINVAL, "xd_store_info: store is null");
-  if (device_bytes) *device_bytes = s->n_words * 4 + (uint64_t)s->n_reads * 12;
+  if (device_bytes)
+    *device_bytes = s->n_words * 4 + (uint64_t)s->n_reads * 20 +
+                    s->n_chunks * sizeof(xd::lane::Chunk);
   if (n_reads) *n_reads = s->n_reads;
   if (max_len) *max_len = s->max_len;
   return XD_OK;
@@ -1871,7 +2182,8 @@ int xd_banded_batch(const xd_store* store, const uint32_t* pairs, const uint32_t
     return fail(XD_EINVAL, "xd_banded_batch: null task or result array");
   if (n == 0) return XD_OK;
   BandedArgs A;
-  A.st = {store->words, store->word_off, store->len, store->n_reads};
+  A.st = {store->words, store->word_off, store->len, store->planes, store->plane_off,
+          store->n_reads};
   A.pairs = pairs;
   A.seeds = seeds;
   A.w = w;
@@ -1919,7 +2231,8 @@ int xd_banded_traceback(const xd_store* store, const uint32_t* pairs, const uint
     return fail(XD_EINVAL, "xd_banded_traceback: null task or result array");
   if (n == 0) return XD_OK;
   BandedArgs A;
-  A.st = {store->words, store->word_off, store->len, store->n_reads};
+  A.st = {store->words, store->word_off, store->len, store->planes, store->plane_off,
+          store->n_reads};
   A.pairs = pairs;
   A.seeds = seeds;
   A.w = w;
