@@ -1370,6 +1370,7 @@ xd::pair::Shared pair_shared(const xd::Scoring& sc) {
 struct Route {
   bool queue;            // the device queue (batched form)
   bool packed;           // two extensions per wavefront in the 64-, 128- and 256-cell windows
+  bool solo;             // match = 1, too few extensions for that: one per wavefront
   uint32_t lane_blocks;  // workgroups of the lane tiers (0: none)
 };
 
@@ -1378,12 +1379,20 @@ struct Route {
 // pairs of 10 kbp at X = 25, one per wavefront / packed / lanes: 8,000 pairs
 // 3.03 / 4.11 / 2.90 ms, 16,000 3.24 / 4.30 / 3.11, 32,000 5.83 / 4.86 / 4.40.
 constexpr uint64_t kLaneMin = 32768;
+// Extensions up to which the batched form runs one per wavefront: their time
+// is the longest one's chain of steps, about 40 ns a step with a wavefront to
+// itself and 90 ns in a packed one.  64 pairs at X of 7 and 25: 1.59 -> 1.15 ms
+// as a plan; the figures above cross at about 24,000 pairs.
+constexpr uint64_t kSoloMax = 32767;
 
 Route batch_route(const xd::Scoring& sc, uint64_t n_ext, bool queue) {
-  Route r = {queue, false, 0u};
+  Route r = {queue, false, false, 0u};
   if (!queue) return r;
   if (lane_ok(sc) && n_ext >= kLaneMin) r.lane_blocks = (uint32_t)device_cus();
-  r.packed = pair_ok(sc);
+  if (pair_ok(sc)) {
+    r.solo = n_ext <= kSoloMax;
+    r.packed = !r.solo;
+  }
   return r;
 }
 
@@ -1522,9 +1531,9 @@ void launch_plain_ext(const BatchArgs& A, const Scratch& S, uint64_t n_ext, cons
   if (ev) (void)hipEventRecord(ev[2], stream);
 }
 
-template <bool UNIT, int GS>
+template <bool UNIT, int GS, bool SAVE>
 void launch_tier0(const Scratch& S, uint32_t blocks, hipStream_t stream) {
-  hipLaunchKernelGGL((k_ext_tier<1, GS, UNIT, 4, false, false>), dim3(blocks), dim3(256), 0,
+  hipLaunchKernelGGL((k_ext_tier<1, GS, UNIT, 4, SAVE, false>), dim3(blocks), dim3(256), 0,
                      stream, (const TierArgs*)S.targs);
 }
 
@@ -1546,12 +1555,14 @@ void launch_persistent_ext(const BatchArgs& A, const Scratch& S, uint64_t n_ext,
     launch_lane(S, Rt.lane_blocks, blocks, stream);
   else if (Rt.packed)
     launch_pair(S, blocks, stream);
+  else if (UNIT && Rt.solo)
+    launch_tier0<UNIT, 16, true>(S, blocks, stream);
   else if (tu.group_steps == 4)
-    launch_tier0<UNIT, 4>(S, blocks, stream);
+    launch_tier0<UNIT, 4, false>(S, blocks, stream);
   else if (tu.group_steps == 16)
-    launch_tier0<UNIT, 16>(S, blocks, stream);
+    launch_tier0<UNIT, 16, false>(S, blocks, stream);
   else
-    launch_tier0<UNIT, 8>(S, blocks, stream);
+    launch_tier0<UNIT, 8, false>(S, blocks, stream);
   if (ev) (void)hipEventRecord(ev[1], stream);
   launch_wide<UNIT>(S, blocks, stream, Rt);
   if (ev) (void)hipEventRecord(ev[2], stream);
