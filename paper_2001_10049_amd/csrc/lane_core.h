@@ -37,6 +37,11 @@
 // and the diagonal neighbour, two antidiagonals back, is always the same bit.
 // A third plane per sequence says which of its positions exist (rows <= m,
 // columns <= n), which keeps cells outside the grid dead.
+//
+// Wider windows.  S neighbouring lanes (a power of two) may share an extension,
+// lane s holding rows base + 32*W*s on; bits cross from lane to lane with one
+// more instruction a plane.  Each lane keeps its own base, so everything above
+// holds lane by lane.
 #pragma once
 
 #include <stdint.h>
@@ -113,6 +118,37 @@ XD_HD uint32_t low_bits(int32_t n) {
 XD_HD int32_t lowest(uint32_t v) { return __builtin_ctz(v); }
 XD_HD int32_t highest(uint32_t v) { return 31 - __builtin_clz(v); }
 
+// ---- lanes that share an extension ------------------------------------------------
+
+#if defined(__HIP_DEVICE_COMPILE__)
+template <int kCtrl>
+__device__ __forceinline__ uint32_t dpp(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int32_t)v, kCtrl, 0xF, 0xF, true);
+}
+__device__ __forceinline__ uint32_t lane_above(uint32_t v) { return dpp<0x130>(v); }  // wave_shl:1
+__device__ __forceinline__ uint32_t lane_below(uint32_t v) { return dpp<0x138>(v); }  // wave_shr:1
+// nonzero in every lane of a group of S when any of them is
+template <int S>
+__device__ __forceinline__ uint32_t any_of(uint32_t v) {
+  if constexpr (S >= 2) v |= dpp<0xB1>(v);   // quad_perm 1,0,3,2
+  if constexpr (S >= 4) v |= dpp<0x4E>(v);   // quad_perm 2,3,0,1
+  if constexpr (S >= 8) v |= dpp<0x141>(v);  // row_half_mirror
+  if constexpr (S >= 16) v |= dpp<0x140>(v); // row_mirror
+  if constexpr (S >= 32) {
+    auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = r[0] | r[1];
+  }
+  return v;
+}
+#else
+XD_HD uint32_t lane_above(uint32_t) { return 0; }
+XD_HD uint32_t lane_below(uint32_t) { return 0; }
+template <int S>
+XD_HD uint32_t any_of(uint32_t v) { return v; }
+template <int kCtrl>
+XD_HD uint32_t dpp(uint32_t v) { return v; }
+#endif
+
 // ---- the planar read store ------------------------------------------------------
 
 // A read's bases 32 at a time, two words each: bit t of the first (second) word
@@ -126,21 +162,25 @@ struct alignas(8) Chunk {
   uint32_t p0, p1;
 };
 
-// 32*N positions of a read in each plane, element t at position first + t (up)
-// or first - t (!up).  Elements outside the read are arbitrary.
+// 32*N positions of a read, element t at position first + t (up) or first - t
+// (!up): the chunks that hold them, and the two planes taken from these.
+// Elements outside the read are arbitrary.
 template <int N>
-XD_HD void gather(const Chunk* read, int32_t n_chunks, int32_t first, bool up,
-                  uint32_t (&o0)[N], uint32_t (&o1)[N]) {
+XD_HD void load_chunks(const Chunk* read, int32_t n_chunks, int32_t first, bool up,
+                       Chunk (&w)[N + 1]) {
   static_assert(N + 1 <= kMaxReach, "guard chunks");
-  const int32_t lo = up ? first : first - (32 * N - 1);
-  const uint32_t sh = (uint32_t)lo & 31u;
-  int32_t c = lo >> 5;
+  int32_t c = (up ? first : first - (32 * N - 1)) >> 5;
   // a start clamped here has no element inside the read
   c = c < -kMaxReach ? -kMaxReach : c;
   c = c > n_chunks ? n_chunks : c;
-  Chunk w[N + 1];
 #pragma unroll
   for (int k = 0; k <= N; ++k) w[k] = read[c + k];
+}
+
+template <int N>
+XD_HD void take_planes(const Chunk (&w)[N + 1], int32_t first, bool up, uint32_t (&o0)[N],
+                       uint32_t (&o1)[N]) {
+  const uint32_t sh = (uint32_t)(up ? first : first - (32 * N - 1)) & 31u;
   uint32_t f0[N], f1[N];
 #pragma unroll
   for (int k = 0; k < N; ++k) {
@@ -154,6 +194,31 @@ XD_HD void gather(const Chunk* read, int32_t n_chunks, int32_t first, bool up,
     o1[k] = up ? f1[k] : r1;
   }
 }
+
+template <int N>
+XD_HD void gather(const Chunk* read, int32_t n_chunks, int32_t first, bool up,
+                  uint32_t (&o0)[N], uint32_t (&o1)[N]) {
+  Chunk w[N + 1];
+  load_chunks<N>(read, n_chunks, first, up, w);
+  take_planes<N>(w, first, up, o0, o1);
+}
+
+// State of an extension that outgrew its window: the last antidiagonal, the
+// window's first row, threshold, arg-max and cells so far, then for each 32
+// rows the planes and live rows of the last antidiagonal (U, L) and of the
+// one before (D, LD).  Seven planes, whatever the tier's count.
+constexpr int kStatePlanes = 7;
+struct StateHead {
+  int32_t d, base, thr, bi, dstar;
+  uint32_t cells, words, pad;
+};
+struct StateWord {
+  uint32_t U[kStatePlanes], D[kStatePlanes], L, LD;
+};
+constexpr uint32_t state_bytes(int words) {
+  return (uint32_t)(sizeof(StateHead) + words * sizeof(StateWord));
+}
+static_assert(sizeof(StateHead) == 32 && sizeof(StateWord) == 64, "state layout");
 
 // ---- one extension ---------------------------------------------------------------
 
@@ -171,9 +236,11 @@ constexpr uint32_t kBackA = 1, kBackB = 2, kComp = 4;  // A, B walked backwards;
 // largest X that P planes tell apart
 constexpr int32_t x_limit(int P) { return (1 << (P - 1)) - 2; }
 
-template <int P, int W>
+// W: words of 32 rows a lane; S: lanes an extension (on the host, 1).
+template <int P, int W, int S = 1>
 struct Core {
-  static constexpr int Q = 32 * W;
+  static constexpr int Q = 32 * W * S;   // window rows
+  static constexpr int kLaneRows = 32 * W;
   static constexpr int kGroup = 4;       // steps between edge tests: the band grows by
                                          // kGroup / 2 rows at either end
   static constexpr int kMaxSteps = 64;   // steps between refills of the base windows
@@ -192,8 +259,27 @@ struct Core {
   uint32_t cnt;       // evaluated cells
   uint32_t bm[W];     // improving rows of the last improving step since the refill
   int32_t bk;         // that step
+  uint32_t inner_top, inner_low;  // all ones except in the group's last / first lane (S > 1)
 
-  XD_HD void clear() {
+  // the word that borders the lane's last / first one, 0 at the window's ends
+  XD_HD uint32_t above(uint32_t first) const {
+    return S > 1 ? lane_above(first) & inner_top : 0u;
+  }
+  XD_HD uint32_t below(uint32_t last) const {
+    return S > 1 ? lane_below(last) & inner_low : 0u;
+  }
+  // the same for the base windows, fed at the window's ends
+  XD_HD uint32_t above(uint32_t first, uint32_t feed) const {
+    return S > 1 ? sel(inner_top, lane_above(first), feed) : feed;
+  }
+  XD_HD uint32_t below(uint32_t last, uint32_t feed) const {
+    return S > 1 ? sel(inner_low, lane_below(last), feed) : feed;
+  }
+
+  // s: this lane's place in its group
+  XD_HD void clear(int s) {
+    inner_top = s == S - 1 ? 0u : ~0u;
+    inner_low = s == 0 ? 0u : ~0u;
 #pragma unroll
     for (int w = 0; w < W; ++w) {
 #pragma unroll
@@ -208,10 +294,11 @@ struct Core {
     bk = 0;
   }
 
-  // the origin alone is live, in the middle of the window (base = -Q / 2)
-  XD_HD void start(int32_t X) {
-    constexpr int w0 = Q / 2 / 32;
-    constexpr uint32_t bit = 1u << (Q / 2 % 32);
+  // the origin alone is live, in the middle of the window (base = -Q / 2);
+  // s: this lane's place in its group
+  XD_HD void start(int32_t X, int s) {
+    constexpr int w0 = S > 1 ? 0 : Q / 2 / 32;
+    const uint32_t bit = S > 1 ? (s == S / 2 ? 1u : 0u) : 1u << (Q / 2 % 32);
 #pragma unroll
     for (int w = 0; w < W; ++w) {
 #pragma unroll
@@ -238,21 +325,24 @@ struct Core {
   template <bool DOWN>
   XD_HD void step(int32_t k) {
     if (DOWN) {
+      const uint32_t e0 = above(a0[0], fa0), e1 = above(a1[0], fa1), ev = above(va[0], fva);
 #pragma unroll
       for (int w = 0; w < W; ++w) {
-        a0[w] = alignbit(w + 1 < W ? a0[w + 1] : fa0, a0[w], 1);
-        a1[w] = alignbit(w + 1 < W ? a1[w + 1] : fa1, a1[w], 1);
-        va[w] = alignbit(w + 1 < W ? va[w + 1] : fva, va[w], 1);
+        a0[w] = alignbit(w + 1 < W ? a0[w + 1] : e0, a0[w], 1);
+        a1[w] = alignbit(w + 1 < W ? a1[w + 1] : e1, a1[w], 1);
+        va[w] = alignbit(w + 1 < W ? va[w + 1] : ev, va[w], 1);
       }
       fa0 >>= 1;
       fa1 >>= 1;
       fva >>= 1;
     } else {
+      const uint32_t e0 = below(b0[W - 1], fb0), e1 = below(b1[W - 1], fb1),
+                     ev = below(vb[W - 1], fvb);
 #pragma unroll
       for (int w = W - 1; w >= 0; --w) {
-        b0[w] = alignbit(b0[w], w > 0 ? b0[w - 1] : fb0, 31);
-        b1[w] = alignbit(b1[w], w > 0 ? b1[w - 1] : fb1, 31);
-        vb[w] = alignbit(vb[w], w > 0 ? vb[w - 1] : fvb, 31);
+        b0[w] = alignbit(b0[w], w > 0 ? b0[w - 1] : e0, 31);
+        b1[w] = alignbit(b1[w], w > 0 ? b1[w - 1] : e1, 31);
+        vb[w] = alignbit(vb[w], w > 0 ? vb[w - 1] : ev, 31);
       }
       fb0 <<= 1;
       fb1 <<= 1;
@@ -266,15 +356,18 @@ struct Core {
     uint32_t NU[P][W], NL[W], NI[W];
 #pragma unroll
     for (int w = 0; w < W; ++w) {
-      // the gap neighbour that is a bit away
-      auto moved = [&](const uint32_t* x) -> uint32_t {
-        return DOWN ? (w + 1 < W ? alignbit(x[w + 1], x[w], 1) : x[w] >> 1)
-                    : (w > 0 ? alignbit(x[w], x[w - 1], 31) : x[w] << 1);
-      };
+      // the gap neighbour that is a bit away; at the window's end it is dead,
+      // whatever its value planes take from the next group of lanes
       uint32_t N[P];
 #pragma unroll
-      for (int p = 0; p < P; ++p) N[p] = moved(U[p]);
-      const uint32_t LN = moved(L), LU = L[w], LX = LD[w];
+      for (int p = 0; p < P; ++p) {
+        const uint32_t* x = U[p];
+        N[p] = DOWN ? alignbit(w + 1 < W ? x[w + 1] : S > 1 ? lane_above(x[0]) : 0u, x[w], 1)
+                    : alignbit(x[w], w > 0 ? x[w - 1] : S > 1 ? lane_below(x[W - 1]) : 0u, 31);
+      }
+      const uint32_t LN = DOWN ? alignbit(w + 1 < W ? L[w + 1] : above(L[0]), L[w], 1)
+                               : alignbit(L[w], w > 0 ? L[w - 1] : below(L[W - 1]), 31);
+      const uint32_t LU = L[w], LX = LD[w];
       // M: the larger gap neighbour (three bits decide)
       uint32_t bw = ~U[0][w] & N[0];
       bw = borrow(U[1][w], N[1], bw);
@@ -320,7 +413,7 @@ struct Core {
       NI[w] = imp;
       cnt += (uint32_t)__builtin_popcount(ev);
     }
-    const bool up = any != 0;
+    const bool up = any_of<S>(any) != 0;
 #pragma unroll
     for (int w = 0; w < W; ++w) {
 #pragma unroll
@@ -344,15 +437,19 @@ struct Core {
     step<false>(k + 3);
   }
 
-  // nonzero: the band reached the margin the next group needs
+  // nonzero: the band reached the margin the next group needs (in one lane)
   XD_HD uint32_t edge() const {
+    if (S > 1)
+      return ((L[0] | LD[0]) & kLowEdge & ~inner_low) |
+             ((L[W - 1] | LD[W - 1]) & kHighEdge & ~inner_top);
     if (W == 1) return (L[0] | LD[0]) & (kLowEdge | kHighEdge);
     return ((L[0] | LD[0]) & kLowEdge) | ((L[W - 1] | LD[W - 1]) & kHighEdge);
   }
 
-  // lowest and highest live bit of the last two antidiagonals; false: none
+  // this lane's lowest and highest live bit of the last two antidiagonals;
+  // false: none (lo is then large and hi negative)
   XD_HD bool extent(int32_t& lo, int32_t& hi) const {
-    lo = Q;
+    lo = 1 << 20;
     hi = -1;
 #pragma unroll
     for (int w = W - 1; w >= 0; --w) {
@@ -368,11 +465,12 @@ struct Core {
     const bool neg = s < 0;
     const uint32_t sh = (uint32_t)s & 31u;
     auto mv = [&](uint32_t (&x)[W]) {
+      const uint32_t first = below(x[W - 1]), last = above(x[0]);
       uint32_t y[W + 1];
 #pragma unroll
       for (int w = 0; w <= W; ++w) {
-        const uint32_t below = w > 0 ? x[w - 1] : 0u, at = w < W ? x[w] : 0u;
-        y[w] = neg ? below : at;
+        const uint32_t under = w > 0 ? x[w - 1] : first, at = w < W ? x[w] : last;
+        y[w] = neg ? under : at;
       }
 #pragma unroll
       for (int w = 0; w < W; ++w) x[w] = alignbit(y[w + 1], y[w], sh);
@@ -386,68 +484,141 @@ struct Core {
     mv(LD);
   }
 
-  // fills the base windows and feeds for the steps after antidiagonal d,
-  // whose window starts at row base
-  XD_HD void refill(const Task& t, int32_t d, int32_t base) {
-    uint32_t x0[W + 1], x1[W + 1], y0[W + 1], y1[W + 1];
-    // a: element q is row base + q
-    gather<W + 1>(t.ra, t.ca, (t.flags & kBackA) ? t.oa - (base - 1) : t.oa + (base - 1),
-                  !(t.flags & kBackA), x0, x1);
-    // b: element q is column d - base + 32 - q
-    const int32_t j0 = d - base + 31;  // that column minus 1, for q = 0
-    gather<W + 1>(t.rb, t.cb, (t.flags & kBackB) ? t.ob - j0 : t.ob + j0,
-                  (t.flags & kBackB) != 0, y0, y1);
+  // The bases a window needs after antidiagonal d, when the lane's rows start
+  // at base: 32 * (W + 1) of each sequence, a's element q being row base + q
+  // and b's column d - base + 32 - q.
+  struct Bases {
+    uint32_t a0[W + 1], a1[W + 1], b0[W + 1], b1[W + 1];
+  };
+  static XD_HD int32_t a_first(const Task& t, int32_t row) {
+    return (t.flags & kBackA) ? t.oa - (row - 1) : t.oa + (row - 1);
+  }
+  static XD_HD int32_t b_first(const Task& t, int32_t column) {
+    return (t.flags & kBackB) ? t.ob - (column - 1) : t.ob + (column - 1);
+  }
+  static XD_HD void bases(const Task& t, int32_t d, int32_t base, Bases& x) {
+    gather<W + 1>(t.ra, t.ca, a_first(t, base), !(t.flags & kBackA), x.a0, x.a1);
+    gather<W + 1>(t.rb, t.cb, b_first(t, d - base + 32), (t.flags & kBackB) != 0, x.b0, x.b1);
     const uint32_t cm = (t.flags & kComp) ? ~0u : 0u;
+#pragma unroll
+    for (int w = 0; w <= W; ++w) {
+      x.b0[w] ^= cm;
+      x.b1[w] ^= cm;
+    }
+  }
+
+  // fills the base windows and feeds from them
+  XD_HD void refill(const Task& t, int32_t d, int32_t base, const Bases& x) {
     const int32_t na = t.m - base + 1;        // elements of a that exist
     const int32_t nb = d - base + 32 - t.n;   // elements of b that do not
 #pragma unroll
     for (int w = 0; w < W; ++w) {
-      a0[w] = x0[w];
-      a1[w] = x1[w];
+      a0[w] = x.a0[w];
+      a1[w] = x.a1[w];
       va[w] = low_bits(na - 32 * w);
-      b0[w] = y0[w + 1] ^ cm;
-      b1[w] = y1[w + 1] ^ cm;
+      b0[w] = x.b0[w + 1];
+      b1[w] = x.b1[w + 1];
       vb[w] = ~low_bits(nb - 32 * (w + 1));
     }
-    fa0 = x0[W];
-    fa1 = x1[W];
+    fa0 = x.a0[W];
+    fa1 = x.a1[W];
     fva = low_bits(na - 32 * W);
-    fb0 = y0[0] ^ cm;
-    fb1 = y1[0] ^ cm;
+    fb0 = x.b0[0];
+    fb1 = x.b1[0];
     fvb = ~low_bits(nb);
   }
 
-  // the feeds alone, when the windows have moved kMaxSteps steps since the
-  // last refill and nowhere else
-  XD_HD void feed(const Task& t, int32_t d, int32_t base) {
+  // The feeds alone, when the windows have moved kMaxSteps steps since the
+  // last refill and nowhere else: the chunks they come from, which may be
+  // read one period ahead, and the feeds.
+  struct Ahead {
+    Chunk a[2], b[2];
+  };
+  static XD_HD void look_ahead(const Task& t, int32_t d, int32_t base, Ahead& x) {
+    load_chunks<1>(t.ra, t.ca, a_first(t, base + kLaneRows), !(t.flags & kBackA), x.a);
+    load_chunks<1>(t.rb, t.cb, b_first(t, d - base + 32), (t.flags & kBackB) != 0, x.b);
+  }
+  XD_HD void feed(const Task& t, int32_t d, int32_t base, const Ahead& x) {
     uint32_t x0[1], x1[1], y0[1], y1[1];
-    const int32_t i0 = base + Q - 1;  // the first row to enter, minus 1
-    const int32_t j0 = d - base + 31;
-    gather<1>(t.ra, t.ca, (t.flags & kBackA) ? t.oa - i0 : t.oa + i0, !(t.flags & kBackA), x0,
-              x1);
-    gather<1>(t.rb, t.cb, (t.flags & kBackB) ? t.ob - j0 : t.ob + j0, (t.flags & kBackB) != 0,
-              y0, y1);
+    take_planes<1>(x.a, a_first(t, base + kLaneRows), !(t.flags & kBackA), x0, x1);
+    take_planes<1>(x.b, b_first(t, d - base + 32), (t.flags & kBackB) != 0, y0, y1);
     const uint32_t cm = (t.flags & kComp) ? ~0u : 0u;
     fa0 = x0[0];
     fa1 = x1[0];
-    fva = low_bits(t.m - i0);
+    fva = low_bits(t.m - base - kLaneRows + 1);
     fb0 = y0[0] ^ cm;
     fb1 = y1[0] ^ cm;
-    fvb = ~low_bits(j0 + 1 - t.n);
+    fvb = ~low_bits(d - base + 32 - t.n);
   }
 
-  // the improving row and antidiagonal recorded since the refill (which was
-  // at antidiagonal d, window base), into bi and dstar
-  XD_HD void settle(int32_t d, int32_t base, int32_t& bi, int32_t& dstar) {
-    int32_t q = -1;
+  // this lane's lowest improving row of the last improving step since the
+  // refill (step bk), which found the lane's rows at base; none: a large number
+  XD_HD int32_t settle(int32_t base) {
+    int32_t q = 1 << 30;
 #pragma unroll
-    for (int w = W - 1; w >= 0; --w) q = bm[w] ? 32 * w + lowest(bm[w]) : q;
-    if (q >= 0) {
-      bi = base + (bk >> 1) + 1 + q;
-      dstar = d + bk + 1;
-    }
+    for (int w = W - 1; w >= 0; --w)
+      q = bm[w] ? base + (bk >> 1) + 1 + 32 * w + lowest(bm[w]) : q;
 #pragma unroll
     for (int w = 0; w < W; ++w) bm[w] = 0;
+    return q;
+  }
+
+  // Planes P and up of the values x[.][w]: a live value is thr plus the signed
+  // P-bit difference to it, so it lies in thr's block of 2^P, in the next one
+  // (plus) or in the one before (minus).
+  XD_HD void save_planes(const uint32_t (&x)[P][W], int w, uint32_t (&o)[kStatePlanes]) const {
+    uint32_t t[P];
+    planes(t, thr);
+    uint32_t bw = ~x[0][w] & t[0];
+#pragma unroll
+    for (int p = 1; p < P - 1; ++p) bw = borrow(x[p][w], t[p], bw);
+    const uint32_t neg = xor3(x[P - 1][w], t[P - 1], bw);      // V - thr < 0
+    const uint32_t lower = borrow(x[P - 1][w], t[P - 1], bw);  // V's low bits below thr's
+    uint32_t plus = lower & ~neg, minus = neg & ~lower;
+#pragma unroll
+    for (int p = 0; p < kStatePlanes; ++p) {
+      if (p < P) {
+        o[p] = x[p < P ? p : 0][w];
+        continue;
+      }
+      const uint32_t b = 0u - (((uint32_t)thr >> p) & 1u);
+      o[p] = b ^ (plus | minus);
+      plus &= b;
+      minus &= ~b;
+    }
+  }
+
+  // this lane's words (s: its place in the group) of the state at dst
+  XD_HD void save_words(int s, uint8_t* dst) const {
+    StateWord* out = (StateWord*)(dst + sizeof(StateHead)) + s * W;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      StateWord x;
+      save_planes(U, w, x.U);
+      save_planes(D, w, x.D);
+      x.L = L[w];
+      x.LD = LD[w];
+      out[w] = x;
+    }
+  }
+
+  // this lane's rows from a state of `words` words; rows above them are dead
+  XD_HD void load_words(int s, int32_t words, const uint8_t* src) {
+    static_assert(P <= kStatePlanes, "planes kept");
+    const StateWord* in = (const StateWord*)(src + sizeof(StateHead));
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      StateWord x = {};
+      if (s * W + w < words) x = in[s * W + w];
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        U[p][w] = x.U[p];
+        D[p][w] = x.D[p];
+      }
+      L[w] = x.L;
+      LD[w] = x.LD;
+      bm[w] = 0;
+    }
   }
 };
 

@@ -57,7 +57,7 @@ __device__ unsigned long long* g_buf;
 __device__ uint32_t g_cap;
 __device__ uint32_t g_n;
 // kernel tags (k_ext_tier<CPL, ...> records kTier + CPL)
-enum : uint32_t { kFirst = 1, kPair = 0x20, kPair2 = 0x21, kPair4 = 0x22, kLane = 0x30, kTier = 0x40, kBand = 0x80 };
+enum : uint32_t { kFirst = 1, kPair = 0x20, kPair2 = 0x21, kPair4 = 0x22, kLane = 0x30, kTier = 0x40, kLaneList = 0x60, kBand = 0x80 };
 __device__ __forceinline__ uint64_t now() { return (uint64_t)wall_clock64(); }
 __device__ __forceinline__ void record(uint32_t tag, uint64_t t0, uint32_t items) {
   if ((threadIdx.x & 63) != 0) return;
@@ -159,9 +159,12 @@ uint64_t band_bytes(const BandGeom& b) { return (uint64_t)b.blocks * 12ull * (ui
 constexpr uint32_t kResumeFlag = 0x80000000u;
 constexpr uint32_t kResumeDiv[4] = {8, 16, 32, 256};
 constexpr uint64_t resume_rec(int t) { return xd::resume_bytes(64 << t); }
+constexpr uint64_t lane_rec(int t) { return xd::lane::state_bytes(2 << t); }
 uint32_t resume_cap(uint64_t n, int t) {
   return kResumeDiv[t] ? (uint32_t)((2 * n + kResumeDiv[t] - 1) / kResumeDiv[t]) : 0u;
 }
+
+struct TierPack;
 
 // Device scratch of one batch.
 struct Scratch {
@@ -169,28 +172,33 @@ struct Scratch {
   uint32_t* queue;    // [2n] extension ids: tier-major, longest first
   uint32_t* ovf[5];   // [2n] each: overflow of tier t into tier t+1 (4: band)
   uint32_t* hist;     // [kBins] histogram, then running cursors
-  uint32_t* ctr;      // [32] counters, see below
-  void* targs;        // [6] TierArgs of the five windows and the band tier
+  uint32_t* ctr;      // [kCtrWords] counters, see below
+  TierPack* targs;    // what the persistent tiers read
   uint8_t* state[4];  // resume states of windows 0..3 (resume_cap x resume_rec)
   uint32_t state_cap[4];
+  uint64_t lane_state[4];  // with lane tiers: their share of each pool, in bytes
   int32_t* band;      // [blocks][3][cap] rows of the band tier
   BandGeom geom;
 };
 // ctr layout
 constexpr int kOvfCount = 0;   // [0..4] sizes of ovf[0..4]
 constexpr int kHead = 5;       // [5..9] work heads of tiers 0..4
-constexpr int kSeg = 10;       // [10..18] queue starts of the segments (k_bin_scan), then 2n
-constexpr int kBandHead = 19;  // work head of the band tier
-constexpr int kResumed = 20;   // [20..23] moves out of windows 0..3 that carried their state
-constexpr int kSegHead1 = 24;  // work head of the 128-cell window's queue segment (batched form)
-constexpr int kLaneHead = 25;  // [25..27] work heads of the lane tiers
-constexpr int kLongHead = 28;  // work head of segment kSegLong
+constexpr int kSeg = 10;       // [10..20] queue starts of the segments (k_bin_scan), then 2n
+                               // and [21..22] the workgroups of split extensions
+constexpr int kBandHead = 23;  // work head of the band tier
+constexpr int kResumed = 24;   // [24..27] moves out of windows 0..3 that carried their state
+constexpr int kSegHead1 = 28;  // work head of the 128-cell window's queue segment (batched form)
+constexpr int kLaneOvf = 29;   // [29..32] sizes of the lane tiers' lists 0..3
+constexpr int kLaneHead = 33;  // [33..41] work heads of tiers kTLane on
+constexpr int kLaneResumed = kLaneOvf + kResumed;  // [53..56] as kResumed, out of lane tiers
 constexpr int kCtrWords = 64;
-// queue segments, in queue order
-// (with lane tiers kSeg64 holds the longest extensions of the narrow and the
-// 64-row class, and kSegLong those of the 96-row class)
-enum { kSeg64 = 0, kSegLane, kSegNarrow, kSegLong, kSegWide, kSeg128, kSeg256, kSegInvalid,
-       kSegEnd };
+// queue segments, in queue order (with lane tiers kSeg64 holds the
+// extensions of the narrow and the 64-row class that run one per wavefront
+// and kSegLong those of the 96-row class; kSegSplit and kSegWideSplit those
+// that run in several lanes each)
+enum { kSeg64 = 0, kSegSplit, kSegLane, kSegNarrow, kSegLong, kSegWideSplit, kSegWide, kSeg128,
+       kSeg256, kSegInvalid, kSegEnd };
+static_assert(kSeg + kSegEnd + 2 < kBandHead && kLaneResumed + 4 <= kCtrWords, "counters");
 constexpr int kTierArgsBytes = 8 * 256;  // >= sizeof(TierPack), checked below
 constexpr uint64_t kFixedBytes = (kBins * 4 + kCtrWords * 4 + kTierArgsBytes + 255) & ~255ull;
 
@@ -223,11 +231,13 @@ Scratch scratch_carve(char* base, uint64_t n, const BandGeom& g) {
   char* fixed = base + ext + 6 * list;
   s.hist = (uint32_t*)fixed;
   s.ctr = (uint32_t*)(fixed + kBins * 4);
-  s.targs = fixed + kBins * 4 + kCtrWords * 4;
+  s.targs = (TierPack*)(fixed + kBins * 4 + kCtrWords * 4);
   uint8_t* st = (uint8_t*)(fixed + kFixedBytes);
   for (int t = 0; t < 4; ++t) {
     s.state[t] = st;
     s.state_cap[t] = resume_cap(n, t);
+    // (their records are a quarter as large)
+    s.lane_state[t] = (state_bytes(n, t) * 3 / 10) & ~63ull;
     st += state_bytes(n, t);
   }
   s.band = (int32_t*)st;
@@ -235,9 +245,16 @@ Scratch scratch_carve(char* base, uint64_t n, const BandGeom& g) {
   return s;
 }
 
-// Arguments of a persistent tier.
+// Persistent tiers: the windows of 64 to 1024 cells and the band tier, the
+// 128-cell window's queue segment on its own, and the lane tiers, named after
+// their queue segments or the rows of the window that takes a list.
+enum { kT64 = 0, kT128, kT256, kT512, kT1024, kTBand, kTSeg128, kTLane, kTNarrow, kTWide,
+       kTSplit, kTWideSplit, kTL128, kTL256, kTL512, kTL1024, kTiers };
+
+// Arguments of a persistent tier.  A list's entry k is at list[k * step]: with
+// lane tiers theirs fill a list array from the front and the other tiers'
+// from the back.
 struct TierArgs {
-  TaskArgs A;
   const uint32_t* queue;
   const uint32_t* seg;      // [2]: this tier's queue segment, or null
   const uint32_t* in_list;  // overflow of the previous tier, or null
@@ -247,17 +264,16 @@ struct TierArgs {
   uint32_t* out_count;
   const uint8_t* in_state;  // resume states of in_list's flagged entries
   uint8_t* out_state;       // where this tier leaves states (null: none)
-  uint32_t in_rec, out_rec, out_cap, pad;
+  uint32_t in_rec, out_rec, out_cap;
+  int32_t in_step, out_step;
 };
 
 static_assert(xd::kBandedMaxW == XD_BAND_MAX, "band limit");
 static_assert(sizeof(TierArgs) % 4 == 0, "tier arguments copied by words");
 
 struct TierPack {
-  // [6]: the 128-cell window's queue segment alone, or with lane tiers the
-  // longest extensions of the 96-row one (batched form); [7..9]: the lane
-  // tiers of 64, 32 and 96 rows
-  TierArgs t[10];
+  TaskArgs A;
+  TierArgs t[kTiers];
   xd::pair::Shared pz;  // scalars of the packed 64-cell tier
 };
 static_assert(sizeof(TierPack) <= kTierArgsBytes, "tier argument area");
@@ -332,38 +348,79 @@ __device__ __forceinline__ bool make_ext(const TaskArgs& A, uint32_t e, xd::Ext&
   return true;
 }
 
-__device__ __forceinline__ void push_list(uint32_t* list, uint32_t* count, uint32_t e) {
+__device__ __forceinline__ void push_list(uint32_t* list, int32_t step, uint32_t* count,
+                                          uint32_t e) {
   if (xd::lane_id() == 0) {
     const uint32_t slot = atomicAdd(count, 1u);
-    list[slot] = e;
+    list[(int64_t)slot * step] = e;
   }
 }
 
-// Extension e overflowed its window (its state, when the window saves one,
-// at the start of ring): it goes on list, the next window's work; when its
-// slot has room in pool (cap states of rec bytes) the state is copied there
-// and the entry marked with kResumeFlag.  A null list means there is no
-// wider window: the extension is marked unresolved.
-__device__ __forceinline__ void overflow_to(ExtOut* ext, uint32_t* list, uint32_t* count,
-                                            uint8_t* pool, uint32_t cap, uint32_t rec,
+// A window's state as it lies in LDS (ResumeHead, rows of U on the last
+// antidiagonal, then of the one before moved up a row) in the lane tiers'
+// layout at dst (global memory).  Q rows.
+template <int Q>
+__device__ __forceinline__ void write_planes(const uint32_t* ring, uint8_t* dst) {
+  const int lane = xd::lane_id();
+  const xd::ResumeHead* H = (const xd::ResumeHead*)ring;
+  const int32_t* rows = (const int32_t*)(ring + sizeof(xd::ResumeHead) / 4);
+  xd::lane::StateWord* words = (xd::lane::StateWord*)(dst + sizeof(xd::lane::StateHead));
+  constexpr int kP = xd::lane::kStatePlanes;
+#pragma unroll
+  for (int q0 = 0; q0 < Q; q0 += 64) {
+    const int q = q0 + lane;
+    const int32_t u = rows[q], v = q + 1 < Q ? rows[Q + q + 1] : H->top_prev;
+    uint32_t x = 0;
+    // lane k (16 + k) takes word k of the lower (upper) 32 rows
+    auto put = [&](int k, uint64_t m) {
+      x = lane == k ? (uint32_t)m : lane == 16 + k ? (uint32_t)(m >> 32) : x;
+    };
+#pragma unroll
+    for (int p = 0; p < kP; ++p) {
+      put(p, xd::ballot64(((u - xd::kBias0) >> p) & 1));
+      put(kP + p, xd::ballot64(((v - xd::kBias0) >> p) & 1));
+    }
+    put(2 * kP, xd::ballot64(u != 0));
+    put(2 * kP + 1, xd::ballot64(v != 0));
+    if (lane < 32) ((uint32_t*)(words + q0 / 32))[lane] = x;
+  }
+  if (lane == 0) {
+    xd::lane::StateHead h = {H->d, H->base, H->thr - xd::kBias0, H->bi, H->dstar,
+                             (uint32_t)H->cells, (uint32_t)Q / 32, 0u};
+    *(xd::lane::StateHead*)dst = h;
+  }
+}
+
+// Extension e overflowed its window (its state, when the window saves one, at
+// the start of ring): it goes on R's list, the next window's work; when its
+// slot has room in R's pool the state is copied there (PLANES rows: in the
+// lane tiers' layout) and the entry marked with kResumeFlag.  Without a list
+// there is no wider window: the extension is marked unresolved.
+template <int PLANES = 0>
+__device__ __forceinline__ void overflow_to(const TaskArgs& A, const TierArgs& R, bool saved,
                                             uint32_t e, const uint32_t* ring) {
-  if (!list) {
+  if (!R.out_list) {
     if (xd::lane_id() == 0) {
       ExtOut o = {0, 0, 0, xd::kExtOverflow, 0};
-      ext[e] = o;
+      A.ext[e] = o;
     }
     return;
   }
   uint32_t slot = 0;
-  if (xd::lane_id() == 0) slot = atomicAdd(count, 1u);
+  if (xd::lane_id() == 0) slot = atomicAdd(R.out_count, 1u);
   slot = __builtin_amdgcn_readfirstlane(__shfl(slot, 0, 64));
-  const bool keep = pool && slot < cap;
+  const bool keep = saved && R.out_state && slot < R.out_cap;
   if (keep) {
-    uint32_t* dst = (uint32_t*)(pool + (uint64_t)slot * rec);
-    for (uint32_t w = xd::lane_id(); w < rec / 4; w += 64) dst[w] = ring[w];
-    if (xd::lane_id() == 0) atomicAdd(count + (kResumed - kOvfCount), 1u);
+    uint8_t* at = R.out_state + (uint64_t)slot * R.out_rec;
+    if constexpr (PLANES > 0) {
+      write_planes<PLANES>(ring, at);
+    } else {
+      uint32_t* dst = (uint32_t*)at;
+      for (uint32_t w = xd::lane_id(); w < R.out_rec / 4; w += 64) dst[w] = ring[w];
+    }
+    if (xd::lane_id() == 0) atomicAdd(R.out_count + (kResumed - kOvfCount), 1u);
   }
-  if (xd::lane_id() == 0) list[slot] = e | (keep ? kResumeFlag : 0u);
+  if (xd::lane_id() == 0) R.out_list[(int64_t)slot * R.out_step] = e | (keep ? kResumeFlag : 0u);
 }
 
 // Sets up and runs extension e on the calling wave, from its seed or from a
@@ -426,7 +483,7 @@ __global__ __launch_bounds__(64) void k_ext_first(BatchArgs A, uint32_t e0, uint
   // no state: saving one costs this hot kernel about 4 % on c2, where no
   // extension overflows; what outgrows 64 cells re-runs from its seed
   if (!run_ext<CPL, GS, UNIT, false, false>(A, e, ring, nullptr))
-    push_list(ovf_list, ovf_count, e);
+    push_list(ovf_list, 1, ovf_count, e);
   XD_STAMP(stamps::kFirst, 1u);
 }
 
@@ -442,8 +499,8 @@ __global__ __launch_bounds__(64) void k_ext_first(BatchArgs A, uint32_t e0, uint
 // VGPRs, 6 waves per SIMD; its list, which resumes and saves, and the
 // 256-cell window to 96, 5 waves; the 512-cell window, in groups of 2
 // antidiagonals, to 128, 4 waves; none of them spills a vector register)
-template <int CPL, int GS, bool UNIT, bool SAVE, bool RESUME>
-__device__ __forceinline__ void run_tier(const TierArgs* pp, uint32_t* ring) {
+template <int CPL, int GS, bool UNIT, bool SAVE, bool RESUME, bool PLANES = false>
+__device__ __forceinline__ void run_tier(const TaskArgs* ap, const TierArgs* pp, uint32_t* ring) {
   XD_STAMP_T0();
 #ifdef XD_WAVE_STAMPS
   uint32_t taken = 0;
@@ -451,7 +508,7 @@ __device__ __forceinline__ void run_tier(const TierArgs* pp, uint32_t* ring) {
   for (;;) {
     // the arguments are re-read (scalar loads) after every extension instead
     // of being held in scalar registers through the extension's loop
-    asm volatile("" : "+s"(pp));
+    asm volatile("" : "+s"(pp), "+s"(ap));
     const TierArgs& Q = *pp;
     const uint32_t seg_lo = Q.seg ? __builtin_amdgcn_readfirstlane(Q.seg[0]) : 0u;
     const uint32_t seg_len = Q.seg ? __builtin_amdgcn_readfirstlane(Q.seg[1]) - seg_lo : 0u;
@@ -462,19 +519,17 @@ __device__ __forceinline__ void run_tier(const TierArgs* pp, uint32_t* ring) {
     idx = __builtin_amdgcn_readfirstlane(__shfl(idx, 0, 64));
     if (idx >= seg_len + n_in) break;
     const uint32_t raw = __builtin_amdgcn_readfirstlane(
-        idx < seg_len ? Q.queue[seg_lo + idx] : Q.in_list[idx - seg_len]);
+        idx < seg_len ? Q.queue[seg_lo + idx]
+                      : Q.in_list[(int64_t)(idx - seg_len) * Q.in_step]);
     const uint32_t e = raw & ~kResumeFlag;
     const uint8_t* resume =
         raw & kResumeFlag ? Q.in_state + (uint64_t)(idx - seg_len) * Q.in_rec : nullptr;
 #ifdef XD_WAVE_STAMPS
     ++taken;
 #endif
-    if (!run_ext<CPL, GS, UNIT, SAVE, RESUME>(Q.A, e, ring, resume)) {
-      const TierArgs& R = *pp;
-      // (a kernel that saves nothing leaves no state to keep)
-      overflow_to(R.A.ext, R.out_list, R.out_count, SAVE ? R.out_state : nullptr, R.out_cap,
-                  R.out_rec, e, ring);
-    }
+    // (a kernel that saves nothing leaves no state to keep)
+    if (!run_ext<CPL, GS, UNIT, SAVE, RESUME>(*ap, e, ring, resume))
+      overflow_to<PLANES ? 64 * CPL : 0>(*ap, *pp, SAVE, e, ring);
   }
   XD_STAMP(stamps::kTier + CPL, taken);
 }
@@ -482,10 +537,10 @@ __device__ __forceinline__ void run_tier(const TierArgs* pp, uint32_t* ring) {
 template <int CPL, int GS, bool UNIT, int WAVES, bool SAVE, bool RESUME>
 __global__ __launch_bounds__(64 * WAVES)
 __attribute__((amdgpu_waves_per_eu(CPL == 2 ? (SAVE ? 5 : 6) : CPL == 4 ? 5 : CPL == 8 ? 4 : 1)))
-void k_ext_tier(const TierArgs* __restrict__ P) {
+void k_ext_tier(const TaskArgs* __restrict__ A, const TierArgs* __restrict__ P) {
   static_assert(WAVES * xd::Tier<CPL, GS>::LDS_WORDS * 4 <= 64 * 1024, "LDS per block");
   __shared__ uint32_t rings[WAVES][xd::Tier<CPL, GS>::LDS_WORDS];
-  run_tier<CPL, GS, UNIT, SAVE, RESUME>(P, rings[threadIdx.x >> 6]);
+  run_tier<CPL, GS, UNIT, SAVE, RESUME>(A, P, rings[threadIdx.x >> 6]);
 }
 
 // The batched form's 64-cell tier for match = 1 with two extensions per wave
@@ -494,6 +549,7 @@ void k_ext_tier(const TierArgs* __restrict__ P) {
 // limit go straight to the next tier's list.
 struct PairWork {
   static constexpr bool kTrace = false;
+  const TaskArgs* ap;
   const TierArgs* pp;
   uint32_t seg_lo, seg_len, n_in;
   uint32_t taken = 0;  // extensions started (instrumented build)
@@ -504,10 +560,10 @@ struct PairWork {
   __device__ void overflow(uint32_t e) {
     const TierArgs& R = *pp;
     if (R.out_list) {
-      push_list(R.out_list, R.out_count, e);
+      push_list(R.out_list, R.out_step, R.out_count, e);
     } else if (xd::lane_id() == 0) {
       ExtOut o = {0, 0, 0, xd::kExtOverflow, 0};
-      R.A.ext[e] = o;
+      ap->ext[e] = o;
     }
   }
   // the next extension and, for a flagged entry of the overflow list, the
@@ -521,13 +577,14 @@ struct PairWork {
       idx = __builtin_amdgcn_readfirstlane(__shfl(idx, 0, 64));
       if (idx >= seg_len + n_in) return false;
       const uint32_t raw = __builtin_amdgcn_readfirstlane(
-          idx < seg_len ? Q.queue[seg_lo + idx] : Q.in_list[idx - seg_len]);
+          idx < seg_len ? Q.queue[seg_lo + idx]
+                      : Q.in_list[(int64_t)(idx - seg_len) * Q.in_step]);
       e = raw & ~kResumeFlag;
       rs = raw & kResumeFlag ? Q.in_state + (uint64_t)(idx - seg_len) * Q.in_rec : nullptr;
-      if (!make_ext(Q.A, e, ex)) {
+      if (!make_ext(*ap, e, ex)) {
         if (xd::lane_id() == 0) {
           ExtOut o = {0, 0, 0, xd::kExtInvalid, 0};
-          Q.A.ext[e] = o;
+          ap->ext[e] = o;
         }
         continue;
       }
@@ -543,11 +600,10 @@ struct PairWork {
   }
   // one whose band outgrew the window, its state at state (LDS)
   __device__ void overflow(uint32_t e, const uint32_t* state) {
-    const TierArgs& R = *pp;
-    overflow_to(R.A.ext, R.out_list, R.out_count, R.out_state, R.out_cap, R.out_rec, e, state);
+    overflow_to(*ap, *pp, true, e, state);
   }
   __device__ void done(uint32_t e, const ExtOut& o) {
-    if (xd::lane_id() == 0) pp->A.ext[e] = o;
+    if (xd::lane_id() == 0) ap->ext[e] = o;
   }
   // the next extension for a tier that resumes nothing (its entries carry
   // no state)
@@ -561,13 +617,14 @@ struct PairWork {
 // leaves room for 5)
 template <int WAVES>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(6)))
-void k_pair_tier(const TierArgs* __restrict__ P,
-                                                          const xd::pair::Shared* Zp) {
+void k_pair_tier(const TaskArgs* __restrict__ A, const TierArgs* __restrict__ P,
+                 const xd::pair::Shared* Zp) {
   static_assert(WAVES * xd::pair::WAVE_WORDS * 4 <= 64 * 1024, "LDS per block");
   __shared__ uint32_t lds[WAVES][xd::pair::WAVE_WORDS];
   const int w = threadIdx.x >> 6;
   const TierArgs& Q = *P;
   PairWork W;
+  W.ap = A;
   W.pp = P;
   W.seg_lo = Q.seg ? __builtin_amdgcn_readfirstlane(Q.seg[0]) : 0u;
   W.seg_len = Q.seg ? __builtin_amdgcn_readfirstlane(Q.seg[1]) - W.seg_lo : 0u;
@@ -587,12 +644,14 @@ void k_pair_tier(const TierArgs* __restrict__ P,
 // unconstrained gave 4 waves and a 4 % slower c3.)
 template <int WAVES>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(5)))
-void k_pair2_tier(const TierArgs* __restrict__ P, const xd::pair::Shared* Zp) {
+void k_pair2_tier(const TaskArgs* __restrict__ A, const TierArgs* __restrict__ P,
+                  const xd::pair::Shared* Zp) {
   static_assert(WAVES * xd::pair2::WAVE_WORDS * 4 <= 64 * 1024, "LDS per block");
   __shared__ uint32_t lds[WAVES][xd::pair2::WAVE_WORDS];
   const int w = threadIdx.x >> 6;
   const TierArgs& Q = *P;
   PairWork W;
+  W.ap = A;
   W.pp = P;
   W.seg_lo = Q.seg ? __builtin_amdgcn_readfirstlane(Q.seg[0]) : 0u;
   W.seg_len = Q.seg ? __builtin_amdgcn_readfirstlane(Q.seg[1]) - W.seg_lo : 0u;
@@ -611,13 +670,14 @@ void k_pair2_tier(const TierArgs* __restrict__ P, const xd::pair::Shared* Zp) {
 // read only on the extension start and overflow paths.)
 template <int WAVES>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(4)))
-void k_pair4_tier(const TierArgs* __restrict__ P,
-                                                           const xd::pair::Shared* Zp) {
+void k_pair4_tier(const TaskArgs* __restrict__ A, const TierArgs* __restrict__ P,
+                  const xd::pair::Shared* Zp) {
   static_assert(WAVES * xd::pair4::WAVE_WORDS * 4 <= 64 * 1024, "LDS per block");
   __shared__ uint32_t lds[WAVES][xd::pair4::WAVE_WORDS];
   const int w = threadIdx.x >> 6;
   const TierArgs& Q = *P;
   PairWork W;
+  W.ap = A;
   W.pp = P;
   W.seg_lo = Q.seg ? __builtin_amdgcn_readfirstlane(Q.seg[0]) : 0u;
   W.seg_len = Q.seg ? __builtin_amdgcn_readfirstlane(Q.seg[1]) - W.seg_lo : 0u;
@@ -628,23 +688,67 @@ void k_pair4_tier(const TierArgs* __restrict__ P,
   XD_STAMP(stamps::kPair4, W.taken);
 }
 
-// Work of the lane tiers: a queue segment, claimed a few entries at a time.
-struct LaneWork {
-  const TierArgs* pp;
-  uint32_t seg_lo, seg_len;
+// Few enough extensions outgrew a window (up to this many) that the longest
+// one's chain of steps, not the instructions, decides when they end: they go
+// straight to 512 rows rather than through one launch after another.  150,000
+// seeds, 10 % spurious, 18,000 such extensions: 26.3 ms against 44.6 with a
+// launch for each window.
+constexpr uint32_t kFewOverflow = 65536;
 
+// Work of the lane tiers, claimed a few entries at a time: a queue segment
+// (S = 1, 2, 4), or with LIST = S the lists of what outgrew the tiers before.
+template <int LIST>
+struct LaneWork {
+  static constexpr bool kResumes = LIST != 0;
+  const TaskArgs* ap;
+  const TierArgs* pp;
+  uint32_t lo, len;
+  uint32_t n1, n2;  // LIST: entries of the first and of the first two lists
+
+  // (p: LIST's own tier, the tiers of the narrower lists before it)
+  __device__ bool open(const TaskArgs* a, const TierArgs* p) {
+    ap = a;
+    pp = p;
+    lo = n1 = n2 = 0;
+    if constexpr (LIST == 0) {
+      lo = __builtin_amdgcn_readfirstlane(p->seg[0]);
+      len = __builtin_amdgcn_readfirstlane(p->seg[1]) - lo;
+    } else {
+      auto entries = [](const TierArgs& t) {
+        return (uint32_t)__builtin_amdgcn_readfirstlane(*t.in_count);
+      };
+      len = n1 = n2 = entries(p[0]);
+      if (LIST < 16 && len <= kFewOverflow) return false;
+      if (LIST == 16) {  // and what the narrower windows left
+        const uint32_t a1 = entries(p[-1]), a2 = entries(p[-2]);
+        n2 = n1 + (a1 <= kFewOverflow ? a1 : 0u);
+        len = n2 + (a2 <= kFewOverflow ? a2 : 0u);
+      }
+    }
+    return len != 0;
+  }
   __device__ uint32_t grab(uint32_t n, uint32_t& idx) {
     uint32_t i = 0;
     if (xd::lane_id() == 0) i = atomicAdd(pp->head, n);
     i = __builtin_amdgcn_readfirstlane(__shfl(i, 0, 64));
-    if (i >= seg_len) return 0u;
-    idx = seg_lo + i;
-    return min(n, seg_len - i);
+    if (i >= len) return 0u;
+    idx = i;
+    return min(n, len - i);
   }
-  // (queue segments hold valid tasks only)
+  // (queue segments and lists hold valid tasks only)
   __device__ void describe(uint32_t idx, xd::lane::Item& it) {
-    const TaskArgs& A = pp->A;
-    const uint32_t e = pp->queue[idx], t = e >> 1;
+    const TaskArgs& A = *ap;
+    uint32_t raw;
+    it.state = nullptr;
+    if constexpr (LIST == 0) {
+      raw = pp->queue[lo + idx];
+    } else {
+      const TierArgs& T = idx < n1 ? pp[0] : idx < n2 ? pp[-1] : pp[-2];
+      const uint32_t at = idx < n1 ? idx : idx < n2 ? idx - n1 : idx - n2;
+      raw = T.in_list[at];
+      if (raw & kResumeFlag) it.state = T.in_state + (uint64_t)at * T.in_rec;
+    }
+    const uint32_t e = raw & ~kResumeFlag, t = e >> 1;
     const uint32_t ra = A.pairs[2 * (uint64_t)t], rb = A.pairs[2 * (uint64_t)t + 1];
     const uint32_t pa = A.seeds[2 * (uint64_t)t], pb = A.seeds[2 * (uint64_t)t + 1];
     const int32_t la = (int32_t)A.st.len[ra], lb = (int32_t)A.st.len[rb];
@@ -664,63 +768,84 @@ struct LaneWork {
     // B reverse-complemented: walked the other way from the mirrored start
     if (rc) it.t.ob = lb - 1 - it.t.ob;
   }
-  __device__ void done(uint32_t e, const ExtOut& o) { pp->A.ext[e] = o; }
-  // a place in the next tier's list, and where the state goes if it is kept
-  __device__ uint8_t* overflow(uint32_t& slot) {
-    const TierArgs& R = *pp;
-    slot = 0;
-    if (xd::lane_id() == 0) slot = atomicAdd(R.out_count, 1u);
-    slot = __builtin_amdgcn_readfirstlane(__shfl(slot, 0, 64));
-    if (slot >= R.out_cap) return nullptr;
-    if (xd::lane_id() == 0) atomicAdd(R.out_count + (kResumed - kOvfCount), 1u);
-    return R.out_state + (uint64_t)slot * R.out_rec;
-  }
-  __device__ void list(uint32_t slot, uint32_t e, bool kept) {
-    if (xd::lane_id() == 0) pp->out_list[slot] = e | (kept ? kResumeFlag : 0u);
+  __device__ void done(uint32_t e, const ExtOut& o) { ap->ext[e] = o; }
+  // (by the group's first lane)
+  __device__ uint8_t* overflow(uint32_t e) {
+    const uint32_t slot = atomicAdd(pp->out_count, 1u);
+    const bool keep = slot < pp->out_cap;
+    pp->out_list[slot] = e | (keep ? kResumeFlag : 0u);
+    if (!keep) return nullptr;
+    atomicAdd(pp->out_count + (kResumed - kOvfCount), 1u);
+    return pp->out_state + (uint64_t)slot * pp->out_rec;
   }
 };
 
-// The lane tiers (xd::lane, W * 32 rows) in the first lane_blocks workgroups.
-// Bound by vector issue: 129 instructions a step for 64 extensions of 64 rows
-// (P = 6), 65 for 32 rows (P = 5), 208 for 96 rows (P = 7), against 6.2 a step
-// and extension in the packed 64-cell kernel.  100,000 pairs of 10 kbp at X = 25:
-// 13.48 -> 5.85 ms; 400,000 seeds at X of 7, 25 and 50: 83.3 -> 28.2 ms.  One
-// workgroup per CU: a lane's step then takes about 0.24 us, and with two it
-// takes twice that for the same rate, so the longest extensions end later
-// (12.0 ms against 7.9 for the 100,000 pairs).
-// The others (W >= 2) run the class's longest extensions (k_bin_scan), one
-// per wavefront: a lane takes several times longer for a step.
+// The lane tiers (xd::lane, W * 32 rows).  The first cus workgroups, one to a
+// CU, run one extension per lane or (W >= 2, the last *split of them) one in
+// two or four lanes; the others the longest ones, one per wavefront.  Which
+// extension runs how: see split_time.
+// Bound by vector issue: 127 instructions a step for 64 extensions of 64 rows
+// (P = 6), 65 for 32 rows (P = 5), 207 for 96 rows (P = 7), 87 for 32 extensions
+// of 64 rows in two lanes each, against 6.2 a step and extension in the packed
+// 64-cell kernel.  100,000 pairs of 10 kbp at X = 25: 13.48 -> 5.6 ms; 400,000
+// seeds at X of 7, 25 and 50: 83.3 -> 27.2 ms.  One workgroup per CU: a lane's
+// step then takes about 0.25 us, and with two it takes twice that for the same
+// rate, so the longest extensions end later.
 template <int P, int W>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W == 3 ? 3 : 4)))
-void k_lane_tier(const TierArgs* __restrict__ LP, const TierArgs* __restrict__ PP,
-                 uint32_t lane_blocks) {
+void k_lane_tier(const TaskArgs* __restrict__ A, const TierArgs* __restrict__ LP,
+                 const TierArgs* __restrict__ XP, const TierArgs* __restrict__ PP,
+                 const uint32_t* __restrict__ split, uint32_t cus) {
   constexpr int kCpl = W == 3 ? 2 : 1, kGs = W == 3 ? 8 : 16;
   constexpr int kRing = W >= 2 ? xd::Tier<kCpl, kGs>::LDS_WORDS : 0;
-  constexpr int kWords = kRing > xd::lane::LDS_WORDS ? kRing : xd::lane::LDS_WORDS;
+  constexpr int kWords =
+      kRing > xd::lane::lds_words(W, 1) ? kRing : xd::lane::lds_words(W, 1);
   __shared__ uint32_t lds[4][kWords];
   const int w = threadIdx.x >> 6;
+  const uint32_t lane_blocks =
+      W >= 2 ? cus - (uint32_t)__builtin_amdgcn_readfirstlane(*split) : cus;
   if (blockIdx.x < lane_blocks) {
-    const TierArgs& Q = *LP;
-    LaneWork wk;
-    wk.pp = LP;
-    wk.seg_lo = __builtin_amdgcn_readfirstlane(Q.seg[0]);
-    wk.seg_len = __builtin_amdgcn_readfirstlane(Q.seg[1]) - wk.seg_lo;
-    if (wk.seg_len == 0) return;
+    LaneWork<0> wk;
+    if (!wk.open(A, LP)) return;
     XD_STAMP_T0();
-    xd::lane::run<P, W>(wk, lds[w], LP->A.st.planes + xd::lane::kGuard);
+    xd::lane::run<P, W, 1>(wk, lds[w], A->st.planes + xd::lane::kGuard);
     XD_STAMP(stamps::kLane + W, 1u);
     return;
   }
   if constexpr (W >= 2) {
+    if (blockIdx.x < cus) {
+      constexpr int kSplit = W == 3 ? 4 : 2;
+      LaneWork<0> wk;
+      if (!wk.open(A, XP)) return;
+      XD_STAMP_T0();
+      xd::lane::run<P, 1, kSplit>(wk, lds[w], A->st.planes + xd::lane::kGuard);
+      XD_STAMP(stamps::kLane + 4 + kSplit, 1u);
+      return;
+    }
     __builtin_amdgcn_s_setprio(3);
-    run_tier<kCpl, kGs, true, true, false>(PP, lds[w]);
+    run_tier<kCpl, kGs, true, true, false, true>(A, PP, lds[w]);
   }
+}
+
+// The lane tiers that take lists: windows of 32 * S rows, S lanes each, for
+// what outgrew the narrower ones.
+template <int S>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+void k_lane_list(const TaskArgs* __restrict__ A, const TierArgs* __restrict__ P) {
+  __shared__ uint32_t lds[4][xd::lane::lds_words(1, S)];
+  LaneWork<S> wk;
+  if (!wk.open(A, P)) return;
+  XD_STAMP_T0();
+  xd::lane::run<xd::lane::kStatePlanes, 1, S>(wk, lds[threadIdx.x >> 6],
+                                              A->st.planes + xd::lane::kGuard);
+  XD_STAMP(stamps::kLaneList + S, 1u);
 }
 
 // Band tier: persistent workgroups of kBandWaves waves, each taking the next
 // extension of in_list (what overflowed the 1024-cell window) and running it
 // with its rows in its own part of band.
-__global__ __launch_bounds__(64 * kBandWaves) void k_ext_band(const TierArgs* __restrict__ P,
+__global__ __launch_bounds__(64 * kBandWaves) void k_ext_band(const TaskArgs* __restrict__ A,
+                                                              const TierArgs* __restrict__ P,
                                                               int32_t* __restrict__ band,
                                                               int32_t cap) {
   __shared__ xd::BandPart part[2 * kBandWaves];
@@ -743,8 +868,8 @@ __global__ __launch_bounds__(64 * kBandWaves) void k_ext_band(const TierArgs* __
     ++taken;
     xd::Ext ex;
     ExtOut o = {0, 0, 0, xd::kExtInvalid, 0};
-    if (make_ext(Q.A, e, ex)) xd::extend_band<kBandWaves>(ex, Q.A.sc, buf, cap, part, csum, o);
-    if (threadIdx.x == 0) Q.A.ext[e] = o;
+    if (make_ext(*A, e, ex)) xd::extend_band<kBandWaves>(ex, A->sc, buf, cap, part, csum, o);
+    if (threadIdx.x == 0) A->ext[e] = o;
   }
   if (threadIdx.x < 64) XD_STAMP(stamps::kBand, taken);
   (void)taken;
@@ -755,7 +880,7 @@ __global__ __launch_bounds__(64 * kBandWaves) void k_ext_band(const TierArgs* __
 struct BinRule {
   int32_t x_tier1, x_tier2;  // X limits of the 64- and 128-cell first tiers
   int32_t by_cost;           // 0: keep task order inside a tier
-  uint32_t lanes;            // lanes of a lane tier's launch (0: no lane tiers)
+  uint32_t lanes;            // workgroups of a lane tier's launch, one per CU (0: no lane tiers)
 };
 
 // Length bin of an estimated antidiagonal count, 6 per octave from 64 on.
@@ -765,11 +890,16 @@ __device__ __forceinline__ uint32_t cost_bin(uint32_t cost) {
   const uint32_t sub = (((cost >> (ex - 3)) & 7u) * 6u) >> 3;
   return min(1u + (ex - 6u) * 6u + sub, (uint32_t)kCostBins - 1u);
 }
-// the middle of a length bin
-__device__ __forceinline__ uint32_t bin_cost(uint32_t cb) {
-  if (cb == 0) return 32u;
+// the middle and the end of a length bin
+__device__ __forceinline__ float bin_cost(uint32_t cb) {
+  if (cb == 0) return 32.f;
+  const uint32_t ex = (cb - 1) / 6, sub = (cb - 1) % 6;  // (sub: 2, 1, 1, 2, 1, 1 eighths)
+  return (float)(4u << ex) * (float)((0x1f1d1a171512ull >> (8 * sub)) & 255u);
+}
+__device__ __forceinline__ float bin_end(uint32_t cb) {
+  if (cb == 0) return 64.f;
   const uint32_t ex = (cb - 1) / 6, sub = (cb - 1) % 6;
-  return ((64u << ex) / 12u) * (13u + 2u * sub);
+  return (float)(4u << ex) * (float)((0x201e1c181614ull >> (8 * sub)) & 255u);
 }
 
 // Sort key of extension e: class from X (its first tier), then the length
@@ -807,73 +937,132 @@ __global__ __launch_bounds__(256) void k_bin_hist(BatchArgs A, BinRule R, uint32
     if (h[b]) atomicAdd(&hist[b], h[b]);
 }
 
-// hist[b] <- queue start of key b; seg[t] <- queue start of segment t
-// (seg[kSegEnd] = n_ext).
-//
-// A lane class's longest extensions run one per wavefront beside the lanes
-// (segments kSeg64 and kSegLong): a lane takes kLaneSlots vector instructions
-// for a step and shares them with 63 others, a wavefront of its own kSolo of
-// them, with a chain of about kSoloChain issue slots.  The split is the one
-// with the smallest estimate of when the last of these ends: the lanes'
-// longest extension, the longest of all, and the instructions of both.
-constexpr uint32_t kStall = 10;  // eighths: a lane's step against its issue slots
+// How a lane class's extensions are shared out: the longest run one per
+// wavefront, the next in several lanes each, the rest in one lane, because
+// the fewer share a wavefront the sooner a step is done and the more
+// instructions it costs.  A CU runs one workgroup of single lanes or of split
+// extensions, and the wavefronts of the longest beside it, ahead of it in
+// priority.  In issue slots of a SIMD (vector instructions):
 struct LaneCost {
-  uint32_t lane, solo, chain;  // issue slots a step
+  float lane_step, split_step, solo_step;  // from one step of an extension to the next
+  float solo;                              // one step's share of the instructions
+  uint32_t split_group;                    // split extensions a workgroup holds
 };
 __device__ __forceinline__ LaneCost lane_cost(uint32_t cls) {
-  return cls == kClsNarrow ? LaneCost{72, 9, 25} : cls == kClsLane ? LaneCost{140, 9, 25}
-                                                                   : LaneCost{230, 16, 45};
+  return cls == kClsNarrow ? LaneCost{82.f, 120.f, 25.f, 12.f, 128u}
+         : cls == kClsLane ? LaneCost{160.f, 120.f, 25.f, 12.f, 128u}
+                           : LaneCost{260.f, 130.f, 45.f, 20.f, 64u};
 }
 
-__device__ __forceinline__ uint32_t lane_split(const uint32_t* count, uint32_t cls,
-                                               uint32_t lanes) {
-  const LaneCost c = lane_cost(cls);
-  uint64_t rest = 0;
-  for (uint32_t q = 0; q < kCostBins; ++q)
-    rest += (uint64_t)count[q] * bin_cost(kCostBins - 1 - q);
-  uint64_t solo = 0, best = ~0ull, longest = 0;
-  uint32_t at = 0;
-  for (uint32_t s = 0;; ++s) {  // the first s bins run alone
-    const uint64_t next = s < kCostBins ? bin_cost(kCostBins - 1 - s) : 0u;
-    const uint64_t alone = solo * c.solo * 64 / lanes;  // slots of the wavefronts of their own
-    const uint64_t chain = max(rest / lanes, rest ? next : 0ull) * c.lane * kStall / 8 + alone / 2;
-    const uint64_t t = max(max(chain, alone + rest * c.lane / lanes), longest * c.chain);
-    if (t < best && (s == kCostBins || count[s] || !rest)) {
-      best = t;
-      at = s;
-    }
-    if (s == kCostBins) break;
-    const uint64_t w = (uint64_t)count[s] * next;
-    if (w && !longest) longest = next;
-    solo += w;
-    rest -= w;
-  }
-  return at;
+// Estimated end of a class whose first s1 length bins run alone and whose next
+// s2 - s1 run split, and the workgroups the latter get of cus: as many as
+// hold those longer than half the longest at once, and make the average load
+// no more than the longest one's.  sum, before: steps and extensions of the
+// bins before each one.
+__device__ __forceinline__ float split_time(const uint32_t* count, const float* sum,
+                                            const uint32_t* before, uint32_t s1, uint32_t s2,
+                                            const LaneCost& c, float cus, float& groups) {
+  constexpr uint32_t N = kCostBins;
+  auto longest = [&](uint32_t from, uint32_t to) -> float {
+    for (uint32_t q = from; q < to; ++q)
+      if (count[q]) return bin_end(N - 1 - q);
+    return 0.f;
+  };
+  const float solo = sum[s1] * c.solo / (4.f * cus), split = sum[s2] - sum[s1],
+              rest = sum[N] - sum[s2];
+  const float l0 = longest(0, s1), l1 = longest(s1, s2), l2 = longest(s2, N);
+  uint32_t half = s1;  // the first bin at half the longest one's length
+  while (half < s2 && bin_end(N - 1 - half) * 2.f > l1) ++half;
+  groups = split > 0.f ? fminf(ceilf(fmaxf(split / l1, (float)(before[half] - before[s1])) /
+                                     (float)c.split_group), cus - 1.f)
+                       : 0.f;
+  const float t1 = split > 0.f ? fmaxf(l1, split / (groups * (float)c.split_group)) : 0.f;
+  const float t2 = fmaxf(l2, rest / (256.f * (cus - groups)));
+  return fmaxf(l0 * c.solo_step, fmaxf(t1 * c.split_step, t2 * c.lane_step) + solo);
 }
 
+// hist[b] <- queue start of key b; seg[t] <- queue start of segment t
+// (seg[kSegEnd] = n_ext); then the workgroups of split extensions beside the
+// 64- and the 96-row class
 __global__ __launch_bounds__(512) void k_bin_scan(uint32_t* hist, uint32_t* seg, BinRule R,
                                                   uint32_t n_ext) {
+  constexpr uint32_t N = kCostBins;
   __shared__ uint32_t h[kBins];
-  __shared__ uint32_t split[4];  // bins of a lane class that run one per wavefront
+  __shared__ float sum[3][N + 1];
+  __shared__ uint32_t before[3][N + 1];
+  __shared__ unsigned long long best[3];
   const uint32_t b = threadIdx.x;
   const uint32_t mine = hist[b];
   h[b] = mine;
+  if (b < 3) best[b] = ~0ull;
   __syncthreads();
-  if (b < 4) {
-    uint32_t s = 0;
-    if (R.lanes && (b == kClsNarrow || b == kClsLane || b == kClsWide))
-      s = lane_split(h + b * kCostBins, b, R.lanes);
-    split[b] = s;
+  // the lane classes' shares: bins [0, alone), [alone, split) and the rest
+  uint32_t alone[3] = {0, 0, 0}, split[3] = {0, 0, 0};
+  float g64 = 0.f, gWide = 0.f;
+  if (R.lanes) {
+    const uint32_t cls[3] = {kClsNarrow, kClsLane, kClsWide};
+    if (b < 3) {
+      float v = 0.f;
+      uint32_t n = 0;
+      const uint32_t* c = h + (b == 0 ? kClsNarrow : b == 1 ? kClsLane : kClsWide) * N;
+      for (uint32_t q = 0; q < N; ++q) {
+        sum[b][q] = v;
+        before[b][q] = n;
+        n += c[q];
+        v += (float)c[q] * bin_cost(N - 1 - q);
+      }
+      sum[b][N] = v;
+      before[b][N] = n;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      if (sum[k][N] == 0.f) continue;
+      const LaneCost c = lane_cost(cls[k]);
+      unsigned long long m = ~0ull;
+      for (uint32_t q = b; q < (N + 1) * (N + 1); q += kBins) {
+        const uint32_t s1 = q / (N + 1), s2 = q % (N + 1);
+        if (s1 > s2) continue;
+        float g;
+        const float t = split_time(h + cls[k] * N, sum[k], before[k], s1, s2, c, (float)R.lanes, g);
+        const unsigned long long v = (unsigned long long)__float_as_uint(t) << 32 | q;
+        m = v < m ? v : m;
+      }
+      atomicMin(&best[k], m);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      if (sum[k][N] == 0.f) continue;
+      const uint32_t q = (uint32_t)best[k];
+      alone[k] = q / (N + 1);
+      split[k] = q % (N + 1);
+      if (b == 0) {
+        float g;
+        split_time(h + cls[k] * N, sum[k], before[k], alone[k], split[k], lane_cost(cls[k]),
+                   (float)R.lanes, g);
+        // (the narrow class's split extensions run beside the 64-row class)
+        if (k < 2)
+          g64 += g;
+        else
+          gWide = g;
+      }
+    }
   }
-  __syncthreads();
+  if (b == 0) {
+    seg[kSegEnd + 1] = (uint32_t)fminf(g64, (float)R.lanes - 1.f);
+    seg[kSegEnd + 2] = (uint32_t)gWide;
+  }
   // the bins in queue order
-  const uint32_t s0 = split[kClsNarrow], s1 = split[kClsLane], s3 = split[kClsWide];
-  const uint32_t cls = min(b / kCostBins, (uint32_t)kClsInvalid), q = b - cls * kCostBins;
-  constexpr uint32_t N = kCostBins;
+  const uint32_t s0 = alone[0], s1 = alone[1], s3 = alone[2];
+  const uint32_t t0 = split[0], t1 = split[1], t3 = split[2];
+  const uint32_t cls = min(b / N, (uint32_t)kClsInvalid), q = b - cls * N;
   uint32_t at = b;  // the classes from 256 cells on keep their place
   if (cls == kCls64) at = q;
-  else if (cls == kClsLane) at = q < s1 ? N + q : N + s1 + s0 + (q - s1);
-  else if (cls == kClsNarrow) at = q < s0 ? N + s1 + q : 2 * N + s0 + (q - s0);
+  else if (cls == kClsLane)
+    at = q < s1 ? N + q : q < t1 ? N + s1 + s0 + (q - s1) : N + t1 + t0 + (q - t1);
+  else if (cls == kClsNarrow)
+    at = q < s0 ? N + s1 + q : q < t0 ? N + t1 + s0 + (q - s0) : 2 * N + t0 + (q - t0);
   else if (cls == kClsWide) at = 3 * N + q;  // (its longest come first already)
   else if (cls == kCls128) at = 4 * N + q;
   __syncthreads();
@@ -892,10 +1081,12 @@ __global__ __launch_bounds__(512) void k_bin_scan(uint32_t* hist, uint32_t* seg,
   auto start = [&](uint32_t slot) { return slot ? h[slot - 1] : 0u; };
   if (b == 0) {
     seg[kSeg64] = 0;
-    seg[kSegLane] = start(N + s1 + s0);
-    seg[kSegNarrow] = start(2 * N + s0);
+    seg[kSegSplit] = start(N + s1 + s0);
+    seg[kSegLane] = start(N + t1 + t0);
+    seg[kSegNarrow] = start(2 * N + t0);
     seg[kSegLong] = start(3 * N);
-    seg[kSegWide] = start(3 * N + s3);
+    seg[kSegWideSplit] = start(3 * N + s3);
+    seg[kSegWide] = start(3 * N + t3);
     seg[kSeg128] = start(4 * N);
     seg[kSeg256] = start(5 * N);
     seg[kSegInvalid] = start(6 * N);
@@ -1377,7 +1568,8 @@ struct Route {
 // Extensions from which the lane tiers run: they hold 65,536 at once, and a
 // batch of half as many leaves most of them to wavefronts of their own.  Read
 // pairs of 10 kbp at X = 25, one per wavefront / packed / lanes: 8,000 pairs
-// 3.03 / 4.11 / 2.90 ms, 16,000 3.24 / 4.30 / 3.11, 32,000 5.83 / 4.86 / 4.40.
+// 3.02 / 4.11 / 2.90 ms, 16,000 3.16 / 4.30 / 3.11, 32,000 5.83 / 4.86 / 3.95;
+// at X = 50, one per wavefront / lanes: 8,000 4.78 / 4.90, 16,000 5.97 / 5.03.
 constexpr uint64_t kLaneMin = 32768;
 // Extensions up to which the batched form runs one per wavefront: their time
 // is the longest one's chain of steps, about 40 ns a step with a wavefront to
@@ -1402,65 +1594,78 @@ Route batch_route(const xd::Scoring& sc, uint64_t n_ext, bool queue) {
 // overflow list of the tier below
 TierPack make_pack(const BatchArgs& A, const Scratch& S, const Route& R) {
   uint32_t* c = S.ctr;
-  const bool segs = R.queue;
   TierPack p = {};
-  p.t[0] = {A, S.queue, c + kSeg + kSeg64, nullptr, nullptr, c + kHead + 0, S.ovf[0],
-            c + kOvfCount + 0};
+  p.A = A;
+  const bool lanes = R.lane_blocks != 0;
+  const uint64_t last = 2 * (uint64_t)A.n - 1;  // a list array's last entry
+  // the list (and states) of what outgrew window w, read by the next one
+  auto takes = [&](int t, int w, bool lane) {
+    TierArgs& T = p.t[t];
+    const bool back = lanes && !lane && w < 4;
+    T.in_list = S.ovf[w] + (back ? last : 0);
+    T.in_step = back ? -1 : 1;
+    T.in_count = c + (lane ? kLaneOvf : kOvfCount) + w;
+    if (w < 4) {
+      T.in_state = S.state[w] + (back ? S.lane_state[w] : 0);
+      T.in_rec = (uint32_t)(lane ? lane_rec(w) : resume_rec(w));
+    }
+  };
+  // where what outgrows window w goes
+  auto leaves = [&](int t, int w, bool lane) {
+    TierArgs& T = p.t[t];
+    const bool back = lanes && !lane && w < 4;
+    T.out_list = S.ovf[w] + (back ? last : 0);
+    T.out_step = back ? -1 : 1;
+    T.out_count = c + (lane && w < 4 ? kLaneOvf : kOvfCount) + w;
+    if (w < 4) {
+      T.out_state = S.state[w] + (back ? S.lane_state[w] : 0);
+      T.out_rec = (uint32_t)(lane ? lane_rec(w) : resume_rec(w));
+      const uint64_t room = S.state_cap[w] * resume_rec(w);
+      T.out_cap = !lanes ? S.state_cap[w]
+                         : (uint32_t)((lane ? S.lane_state[w] : room - S.lane_state[w]) / T.out_rec);
+    }
+  };
+  for (int t = 0; t < kTiers; ++t) {
+    p.t[t].queue = S.queue;
+    p.t[t].in_step = p.t[t].out_step = 1;
+    p.t[t].head = t < kTBand ? c + kHead + t
+                  : t == kTBand ? c + kBandHead
+                  : t == kTSeg128 ? c + kSegHead1 : c + kLaneHead + (t - kTLane);
+  }
+  // 64 cells: with lane tiers, the longest extensions of two of their classes
+  p.t[kT64].seg = c + kSeg + kSeg64;
+  leaves(kT64, 0, lanes);
   // the 128-cell window's queue segment (batched form: X in (x_tier1, x_tier2],
   // started here) and its list (what outgrew 64 cells, resumable onwards) run
   // as one launch of the packed kernel, or as two of the 32-bit ones, whose
   // first leaves no state and so keeps the register budget of one without
-  // saving
-  p.t[1] = {A, S.queue, segs && R.packed ? c + kSeg + kSeg128 : nullptr, S.ovf[0],
-            c + kOvfCount + 0, c + kHead + 1, S.ovf[1], c + kOvfCount + 1};
-  p.t[6] = {A, S.queue, nullptr, nullptr, nullptr, c + kSegHead1, S.ovf[1], c + kOvfCount + 1};
-  if (R.lane_blocks) {
-    p.t[6].seg = c + kSeg + kSegLong;
-    p.t[6].head = c + kLongHead;
-  } else if (segs) {
-    p.t[6].seg = c + kSeg + kSeg128;
-  }
-  p.t[2] = {A, S.queue, segs ? c + kSeg + kSeg256 : nullptr, S.ovf[1], c + kOvfCount + 1,
-            c + kHead + 2, S.ovf[2], c + kOvfCount + 2};
-  p.t[3] = {A, S.queue, nullptr, S.ovf[2], c + kOvfCount + 2, c + kHead + 3, S.ovf[3],
-            c + kOvfCount + 3};
-  p.t[4] = {A, S.queue, nullptr, S.ovf[3], c + kOvfCount + 3, c + kHead + 4, S.ovf[4],
-            c + kOvfCount + 4};
-  p.t[5] = {A, S.queue, nullptr, S.ovf[4], c + kOvfCount + 4, c + kBandHead, nullptr, nullptr};
-  // the lane tiers: what outgrows 64 or 32 rows goes to the 128-cell list,
-  // what outgrows 96 rows to the 256-cell one
-  p.t[7] = {A, S.queue, c + kSeg + kSegLane, nullptr, nullptr, c + kLaneHead + 0, S.ovf[0],
-            c + kOvfCount + 0};
-  p.t[8] = {A, S.queue, c + kSeg + kSegNarrow, nullptr, nullptr, c + kLaneHead + 1, S.ovf[0],
-            c + kOvfCount + 0};
-  p.t[9] = {A, S.queue, c + kSeg + kSegWide, nullptr, nullptr, c + kLaneHead + 2, S.ovf[1],
-            c + kOvfCount + 1};
-  // resume states: window t leaves them in pool t, window t + 1 reads them;
-  // the band tier re-runs what outgrows the 1024-cell window
-  for (int t = 0; t < 7; ++t) {
-    TierArgs& T = p.t[t];
-    T.in_state = t >= 1 && t <= 4 ? S.state[t - 1] : nullptr;
-    T.in_rec = t >= 1 && t <= 4 ? (uint32_t)resume_rec(t - 1) : 0u;
-    T.out_state = t <= 3 ? S.state[t] : nullptr;
-    T.out_cap = t <= 3 ? S.state_cap[t] : 0u;
-    T.out_rec = t <= 3 ? (uint32_t)resume_rec(t) : 0u;
-    T.pad = 0;
-  }
-  // these start their extensions; what outgrows 128 cells shares a list and
-  // its state slots with what outgrows the 128-cell list
-  p.t[6].in_state = nullptr;
-  p.t[6].in_rec = 0u;
-  p.t[6].out_state = S.state[1];
-  p.t[6].out_cap = S.state_cap[1];
-  p.t[6].out_rec = (uint32_t)resume_rec(1);
-  for (int t = 7; t < 10; ++t) {
-    const int pool = t == 9 ? 1 : 0;
-    p.t[t].in_state = nullptr;
-    p.t[t].in_rec = 0u;
-    p.t[t].out_state = S.state[pool];
-    p.t[t].out_cap = S.state_cap[pool];
-    p.t[t].out_rec = (uint32_t)resume_rec(pool);
-    p.t[t].pad = 0;
+  // saving; with lane tiers the second is their 96-row class's longest
+  takes(kT128, 0, false);
+  leaves(kT128, 1, false);
+  if (R.queue && R.packed) p.t[kT128].seg = c + kSeg + kSeg128;
+  if (R.queue) p.t[kTSeg128].seg = c + kSeg + (lanes ? kSegLong : kSeg128);
+  leaves(kTSeg128, 1, lanes);
+  if (R.queue) p.t[kT256].seg = c + kSeg + kSeg256;
+  takes(kT256, 1, false);
+  leaves(kT256, 2, false);
+  takes(kT512, 2, false);
+  leaves(kT512, 3, false);
+  takes(kT1024, 3, false);
+  leaves(kT1024, 4, false);
+  // the band tier re-runs what outgrows the 1024-cell windows
+  takes(kTBand, 4, false);
+  if (lanes) {
+    p.t[kTLane].seg = c + kSeg + kSegLane;
+    p.t[kTNarrow].seg = c + kSeg + kSegNarrow;
+    p.t[kTSplit].seg = c + kSeg + kSegSplit;
+    p.t[kTWide].seg = c + kSeg + kSegWide;
+    p.t[kTWideSplit].seg = c + kSeg + kSegWideSplit;
+    for (int t : {kTLane, kTNarrow, kTSplit}) leaves(t, 0, true);
+    for (int t : {kTWide, kTWideSplit}) leaves(t, 1, true);
+    for (int w = 0; w < 4; ++w) {
+      takes(kTL128 + w, w, true);
+      leaves(kTL128 + w, w + 1, true);
+    }
   }
   p.pz = pair_shared(A.sc);
   return p;
@@ -1473,48 +1678,53 @@ TierPack make_pack(const BatchArgs& A, const Scratch& S, const Route& R) {
 // and saves nothing.
 template <bool UNIT>
 void launch_wide(const Scratch& S, uint32_t blocks, hipStream_t stream, const Route& R) {
-  const TierArgs* ta = (const TierArgs*)S.targs;
-  const bool packed = R.packed;
-  if (R.lane_blocks)
-    hipLaunchKernelGGL((k_lane_tier<7, 3>), dim3(R.lane_blocks + blocks), dim3(256), 0, stream,
-                       ta + 9, ta + 6, R.lane_blocks);
-  else if (R.queue && !packed)
+  const TaskArgs* ga = &S.targs->A;
+  const TierArgs* ta = S.targs->t;
+  const xd::pair::Shared* pz = &S.targs->pz;
+  if (R.lane_blocks) {
+    const uint32_t n = R.lane_blocks;
+    hipLaunchKernelGGL((k_lane_tier<7, 3>), dim3(3 * n), dim3(256), 0, stream, ga, ta + kTWide,
+                       ta + kTWideSplit, ta + kTSeg128, S.ctr + kSeg + kSegEnd + 2, n);
+    hipLaunchKernelGGL((k_lane_list<4>), dim3(4 * n), dim3(256), 0, stream, ga, ta + kTL128);
+    hipLaunchKernelGGL((k_lane_list<8>), dim3(4 * n), dim3(256), 0, stream, ga, ta + kTL256);
+    hipLaunchKernelGGL((k_lane_list<16>), dim3(4 * n), dim3(256), 0, stream, ga, ta + kTL512);
+    hipLaunchKernelGGL((k_lane_list<32>), dim3(4 * n), dim3(256), 0, stream, ga, ta + kTL1024);
+  } else if (R.queue && !R.packed) {
     hipLaunchKernelGGL((k_ext_tier<2, 8, UNIT, 4, false, false>), dim3(blocks), dim3(256), 0,
-                       stream, ta + 6);
-  if (packed)
-    hipLaunchKernelGGL((k_pair2_tier<4>), dim3(blocks), dim3(256), 0, stream, ta + 1,
-                       &((const TierPack*)S.targs)->pz);
+                       stream, ga, ta + kTSeg128);
+  }
+  if (R.packed)
+    hipLaunchKernelGGL((k_pair2_tier<4>), dim3(blocks), dim3(256), 0, stream, ga, ta + kT128, pz);
   else
     hipLaunchKernelGGL((k_ext_tier<2, 8, UNIT, 4, true, true>), dim3(blocks), dim3(256), 0,
-                       stream, ta + 1);
-  if (packed)
-    hipLaunchKernelGGL((k_pair4_tier<4>), dim3(blocks), dim3(256), 0, stream, ta + 2,
-                       &((const TierPack*)S.targs)->pz);
+                       stream, ga, ta + kT128);
+  if (R.packed)
+    hipLaunchKernelGGL((k_pair4_tier<4>), dim3(blocks), dim3(256), 0, stream, ga, ta + kT256, pz);
   else
     hipLaunchKernelGGL((k_ext_tier<4, 4, UNIT, 4, true, true>), dim3(blocks), dim3(256), 0,
-                       stream, ta + 2);
+                       stream, ga, ta + kT256);
   hipLaunchKernelGGL((k_ext_tier<8, 2, UNIT, 2, true, true>), dim3(2 * blocks), dim3(128), 0,
-                     stream, ta + 3);
+                     stream, ga, ta + kT512);
   hipLaunchKernelGGL((k_ext_tier<16, 2, UNIT, 1, false, true>), dim3(4 * blocks), dim3(64), 0,
-                     stream, ta + 4);
-  hipLaunchKernelGGL(k_ext_band, dim3(S.geom.blocks), dim3(64 * kBandWaves), 0, stream, ta + 5,
-                     S.band, S.geom.cap);
+                     stream, ga, ta + kT1024);
+  hipLaunchKernelGGL(k_ext_band, dim3(S.geom.blocks), dim3(64 * kBandWaves), 0, stream, ga,
+                     ta + kTBand, S.band, S.geom.cap);
 }
 
 constexpr int kPairWaves = 4;  // waves per block of the packed tier
 
 void launch_pair(const Scratch& S, uint32_t blocks, hipStream_t stream) {
-  const TierPack* tp = (const TierPack*)S.targs;
   hipLaunchKernelGGL((k_pair_tier<kPairWaves>), dim3(blocks), dim3(64 * kPairWaves), 0, stream,
-                     &tp->t[0], &tp->pz);
+                     &S.targs->A, S.targs->t + kT64, &S.targs->pz);
 }
 
-void launch_lane(const Scratch& S, uint32_t lane_blocks, uint32_t blocks, hipStream_t stream) {
-  const TierArgs* ta = (const TierArgs*)S.targs;
-  hipLaunchKernelGGL((k_lane_tier<6, 2>), dim3(lane_blocks + blocks), dim3(256), 0, stream,
-                     ta + 7, ta + 0, lane_blocks);
-  hipLaunchKernelGGL((k_lane_tier<5, 1>), dim3(lane_blocks), dim3(256), 0, stream, ta + 8,
-                     ta + 0, lane_blocks);
+void launch_lane(const Scratch& S, uint32_t n, hipStream_t stream) {
+  const TaskArgs* ga = &S.targs->A;
+  const TierArgs* ta = S.targs->t;
+  hipLaunchKernelGGL((k_lane_tier<6, 2>), dim3(4 * n), dim3(256), 0, stream, ga, ta + kTLane,
+                     ta + kTSplit, ta + kT64, S.ctr + kSeg + kSegEnd + 1, n);
+  hipLaunchKernelGGL((k_lane_tier<5, 1>), dim3(n), dim3(256), 0, stream, ga, ta + kTNarrow,
+                     ta + kTNarrow, ta + kT64, S.ctr + kSeg + kSegEnd + 1, n);
 }
 
 template <bool UNIT>
@@ -1534,7 +1744,7 @@ void launch_plain_ext(const BatchArgs& A, const Scratch& S, uint64_t n_ext, cons
 template <bool UNIT, int GS, bool SAVE>
 void launch_tier0(const Scratch& S, uint32_t blocks, hipStream_t stream) {
   hipLaunchKernelGGL((k_ext_tier<1, GS, UNIT, 4, SAVE, false>), dim3(blocks), dim3(256), 0,
-                     stream, (const TierArgs*)S.targs);
+                     stream, &S.targs->A, S.targs->t + kT64);
 }
 
 template <bool UNIT>
@@ -1542,7 +1752,7 @@ void launch_persistent_ext(const BatchArgs& A, const Scratch& S, uint64_t n_ext,
                            const Tuned& tu, const Route& Rt, hipEvent_t* ev,
                            hipStream_t stream) {
   const uint32_t grid = (uint32_t)((n_ext + 255) / 256);
-  BinRule R = {tu.x_tier1, tu.x_tier2, tu.order == 1 ? 1 : 0, Rt.lane_blocks * 256u};
+  BinRule R = {tu.x_tier1, tu.x_tier2, tu.order == 1 ? 1 : 0, Rt.lane_blocks};
   hipLaunchKernelGGL(k_bin_hist, dim3(grid), dim3(256), 0, stream, A, R, (uint32_t)n_ext,
                      S.hist);
   hipLaunchKernelGGL(k_bin_scan, dim3(1), dim3(kBins), 0, stream, S.hist, S.ctr + kSeg, R,
@@ -1552,7 +1762,7 @@ void launch_persistent_ext(const BatchArgs& A, const Scratch& S, uint64_t n_ext,
   uint32_t blocks = (uint32_t)device_cus() * (uint32_t)tu.waves_per_cu / 4u;
   if (blocks < 1) blocks = 1;
   if (Rt.lane_blocks)
-    launch_lane(S, Rt.lane_blocks, blocks, stream);
+    launch_lane(S, Rt.lane_blocks, stream);
   else if (Rt.packed)
     launch_pair(S, blocks, stream);
   else if (UNIT && Rt.solo)
@@ -2432,12 +2642,13 @@ int xd_profile_read(xd_profile* out, int reset) {
     HIP_TRY(hipEventElapsedTime(&tt, r.ev[0], r.ev[3]));
     g_prof_sum.batches += 1;
     g_prof_sum.extensions += r.n_ext;
-    g_prof_sum.to_tier2 += r.counters[kOvfCount + 0];
-    g_prof_sum.to_tier3 += r.counters[kOvfCount + 1];
-    g_prof_sum.to_tier4 += r.counters[kOvfCount + 2];
-    g_prof_sum.to_tier5 += r.counters[kOvfCount + 3];
+    g_prof_sum.to_tier2 += r.counters[kOvfCount + 0] + r.counters[kLaneOvf + 0];
+    g_prof_sum.to_tier3 += r.counters[kOvfCount + 1] + r.counters[kLaneOvf + 1];
+    g_prof_sum.to_tier4 += r.counters[kOvfCount + 2] + r.counters[kLaneOvf + 2];
+    g_prof_sum.to_tier5 += r.counters[kOvfCount + 3] + r.counters[kLaneOvf + 3];
     g_prof_sum.to_band += r.counters[kOvfCount + 4];
-    for (int t = 0; t < 4; ++t) g_prof_sum.resumed += r.counters[kResumed + t];
+    for (int t = 0; t < 4; ++t) 
+      g_prof_sum.resumed += r.counters[kResumed + t] + r.counters[kLaneResumed + t];
     g_prof_sum.ms_tier1 += t1;
     g_prof_sum.ms_wide += t2;
     g_prof_sum.ms_combine += t3;

@@ -33,8 +33,10 @@ import numpy as np
 
 TAGS = {0x01: "k_ext_first<1,16>", 0x20: "k_pair_tier<4>", 0x21: "k_pair2_tier<4>",
         0x22: "k_pair4_tier<4>", 0x31: "k_lane_tier<5, 1>", 0x32: "k_lane_tier<6, 2>",
-        0x33: "k_lane_tier<7, 3>", 0x80: "k_ext_band"}
+        0x33: "k_lane_tier<7, 3>", 0x36: "k_lane_tier<6, 2> split", 0x38: "k_lane_tier<7, 3> split",
+        0x80: "k_ext_band"}
 for _c in (1, 2, 4, 8, 16):
+    TAGS[0x60 + 2 * _c] = "k_lane_list<%d>" % (2 * _c)
     TAGS[0x40 + _c] = "k_ext_tier<%d,...>" % _c
 PERSISTENT_TAGS = {t for t in TAGS if t != 0x01}
 CLOCK_HZ = 100e6  # steady counter

@@ -26,9 +26,11 @@ def lib(tmp_path_factory):
     return ctypes.CDLL(so)
 
 
-def run(lib, planes, a, b, X, back_a=False, back_b=False, comp=False, pad=(0, 0)):
+def run(lib, planes, a, b, X, back_a=False, back_b=False, comp=False, pad=(0, 0), chain=False):
     """Lane result of extending a against b, stored in reads as the flags say
-    (backwards, complemented), `pad` foreign bases before and after."""
+    (backwards, complemented), `pad` foreign bases before and after.  chain:
+    what outgrows the window goes on in the 96-row one; whether it did comes
+    last."""
     rng = np.random.default_rng(1)
 
     def store(s, back, comp):
@@ -38,11 +40,13 @@ def run(lib, planes, a, b, X, back_a=False, back_b=False, comp=False, pad=(0, 0)
         return np.ascontiguousarray(r, np.uint8), pad[0] + (len(s) - 1 if back else 0)
     A, oa = store(a, back_a, False)
     B, ob = store(b, back_b, comp)
-    out = (ctypes.c_int64 * 5)()
+    out = (ctypes.c_int64 * 6)()
     flags = (1 if back_a else 0) | (2 if back_b else 0) | (4 if comp else 0)
     p = lambda v: v.ctypes.data_as(ctypes.c_void_p)  # noqa: E731
-    ok = lib.lane_extend(planes, p(A), len(A), p(B), len(B), oa, ob, len(a), len(b), X, flags, out)
-    return None if ok == 0 else tuple(out[:4])
+    ok = lib.lane_extend(planes, int(chain), p(A), len(A), p(B), len(B), oa, ob, len(a), len(b), X, flags, out)
+    if ok == 0:
+        return None
+    return tuple(out[:4]) + ((out[5],) if chain else ())
 
 
 def want(a, b, X):
@@ -111,3 +115,22 @@ def test_every_small_shape(lib, planes):
             got = run(lib, planes, a, b, X, pad=(int(rng.integers(0, 70)), 0))
             if got is not None:
                 assert got == want(a, b, X), (planes, m, n, X)
+
+
+@pytest.mark.parametrize("planes", [5, 6])
+def test_wider_window_resumes(lib, planes):
+    """A band that outgrows 32 or 64 rows goes on in 96 from the state it left."""
+    rng = np.random.default_rng(planes)
+    moved = 0
+    for _ in range(1200):
+        n = int(rng.integers(100, 900))
+        a = np.resize(rand_codes(rng, int(rng.integers(1, 5))), n)
+        a = mutate_codes(rng, a, 0.1)
+        b = mutate_codes(rng, a, 0.2) if rng.integers(2) else mutate_codes(rng, np.roll(a, 7), 0.1)
+        X = int(rng.integers(LIMIT[planes] // 2, LIMIT[planes] + 1))
+        got = run(lib, planes, a, b, X, back_a=bool(rng.integers(2)), chain=True)
+        if got is None or not got[4]:
+            continue
+        moved += 1
+        assert got[:4] == want(a, b, X), (planes, n, len(b), X)
+    assert moved >= 20, moved
