@@ -954,26 +954,31 @@ __device__ __forceinline__ LaneCost lane_cost(uint32_t cls) {
                            : LaneCost{260.f, 130.f, 45.f, 20.f, 64u};
 }
 
+// What split_time reads of a class: for each length bin, longest first, the
+// first bin from it on that is not empty, and the steps and extensions of the
+// bins before it.
+struct ClassBins {
+  uint32_t next[kCostBins + 1], before[kCostBins + 1];
+  float sum[kCostBins + 1];
+};
+
 // Estimated end of a class whose first s1 length bins run alone and whose next
 // s2 - s1 run split, and the workgroups the latter get of cus: as many as
 // hold those longer than half the longest at once, and make the average load
-// no more than the longest one's.  sum, before: steps and extensions of the
-// bins before each one.
-__device__ __forceinline__ float split_time(const uint32_t* count, const float* sum,
-                                            const uint32_t* before, uint32_t s1, uint32_t s2,
+// no more than the longest one's.
+__device__ __forceinline__ float split_time(const ClassBins& x, uint32_t s1, uint32_t s2,
                                             const LaneCost& c, float cus, float& groups) {
   constexpr uint32_t N = kCostBins;
   auto longest = [&](uint32_t from, uint32_t to) -> float {
-    for (uint32_t q = from; q < to; ++q)
-      if (count[q]) return bin_end(N - 1 - q);
-    return 0.f;
+    const uint32_t q = x.next[from];
+    return q < to ? bin_end(N - 1 - q) : 0.f;
   };
-  const float solo = sum[s1] * c.solo / (4.f * cus), split = sum[s2] - sum[s1],
-              rest = sum[N] - sum[s2];
+  const float solo = x.sum[s1] * c.solo / (4.f * cus), split = x.sum[s2] - x.sum[s1],
+              rest = x.sum[N] - x.sum[s2];
   const float l0 = longest(0, s1), l1 = longest(s1, s2), l2 = longest(s2, N);
-  uint32_t half = s1;  // the first bin at half the longest one's length
-  while (half < s2 && bin_end(N - 1 - half) * 2.f > l1) ++half;
-  groups = split > 0.f ? fminf(ceilf(fmaxf(split / l1, (float)(before[half] - before[s1])) /
+  // (six bins an octave)
+  const uint32_t half = min(s2, x.next[s1] + 6u);
+  groups = split > 0.f ? fminf(ceilf(fmaxf(split / l1, (float)(x.before[half] - x.before[s1])) /
                                      (float)c.split_group), cus - 1.f)
                        : 0.f;
   const float t1 = split > 0.f ? fmaxf(l1, split / (groups * (float)c.split_group)) : 0.f;
@@ -983,82 +988,89 @@ __device__ __forceinline__ float split_time(const uint32_t* count, const float* 
 
 // hist[b] <- queue start of key b; seg[t] <- queue start of segment t
 // (seg[kSegEnd] = n_ext); then the workgroups of split extensions beside the
-// 64- and the 96-row class
+// 64- and the 96-row class.
+//
+// The narrow class's lanes run after the 64-row class's, in a launch of their
+// own; when that would take longer than running them all in 64 rows (two
+// chains of steps instead of one), the two are one class.  32,000 pairs at X
+// of 7 and 25: 4.0 ms against 5.8.
 __global__ __launch_bounds__(512) void k_bin_scan(uint32_t* hist, uint32_t* seg, BinRule R,
                                                   uint32_t n_ext) {
   constexpr uint32_t N = kCostBins;
+  constexpr int kKinds = 4;  // narrow, 64 rows, 96 rows, the first two as one
   __shared__ uint32_t h[kBins];
-  __shared__ float sum[3][N + 1];
-  __shared__ uint32_t before[3][N + 1];
-  __shared__ unsigned long long best[3];
+  __shared__ ClassBins x[kKinds];
+  __shared__ unsigned long long best[kKinds];
   const uint32_t b = threadIdx.x;
   const uint32_t mine = hist[b];
   h[b] = mine;
-  if (b < 3) best[b] = ~0ull;
+  if (b < kKinds) best[b] = ~0ull;
   __syncthreads();
   // the lane classes' shares: bins [0, alone), [alone, split) and the rest
-  uint32_t alone[3] = {0, 0, 0}, split[3] = {0, 0, 0};
-  float g64 = 0.f, gWide = 0.f;
+  uint32_t alone[kKinds] = {0, 0, 0, 0}, split[kKinds] = {0, 0, 0, 0};
+  float groups[kKinds] = {0.f, 0.f, 0.f, 0.f}, t[kKinds] = {0.f, 0.f, 0.f, 0.f};
+  const uint32_t cls_of[kKinds] = {kClsNarrow, kClsLane, kClsWide, kClsLane};
   if (R.lanes) {
-    const uint32_t cls[3] = {kClsNarrow, kClsLane, kClsWide};
-    if (b < 3) {
+    if (b < kKinds) {
       float v = 0.f;
-      uint32_t n = 0;
-      const uint32_t* c = h + (b == 0 ? kClsNarrow : b == 1 ? kClsLane : kClsWide) * N;
+      uint32_t n = 0, nx = N;
+      const uint32_t* c = h + cls_of[b] * N;
+      const uint32_t* c2 = h + kClsNarrow * N;
+      auto count = [&](uint32_t q) { return c[q] + (b == 3 ? c2[q] : 0u); };
       for (uint32_t q = 0; q < N; ++q) {
-        sum[b][q] = v;
-        before[b][q] = n;
-        n += c[q];
-        v += (float)c[q] * bin_cost(N - 1 - q);
+        x[b].sum[q] = v;
+        x[b].before[q] = n;
+        n += count(q);
+        v += (float)count(q) * bin_cost(N - 1 - q);
       }
-      sum[b][N] = v;
-      before[b][N] = n;
+      x[b].sum[N] = v;
+      x[b].before[N] = n;
+      x[b].next[N] = N;
+      for (uint32_t q = N; q-- > 0;) {
+        if (count(q)) nx = q;
+        x[b].next[q] = nx;
+      }
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      if (sum[k][N] == 0.f) continue;
-      const LaneCost c = lane_cost(cls[k]);
+    for (int k = 0; k < kKinds; ++k) {
+      if (x[k].sum[N] == 0.f) continue;
+      const LaneCost c = lane_cost(cls_of[k]);
       unsigned long long m = ~0ull;
       for (uint32_t q = b; q < (N + 1) * (N + 1); q += kBins) {
         const uint32_t s1 = q / (N + 1), s2 = q % (N + 1);
         if (s1 > s2) continue;
         float g;
-        const float t = split_time(h + cls[k] * N, sum[k], before[k], s1, s2, c, (float)R.lanes, g);
-        const unsigned long long v = (unsigned long long)__float_as_uint(t) << 32 | q;
+        const float e = split_time(x[k], s1, s2, c, (float)R.lanes, g);
+        const unsigned long long v = (unsigned long long)__float_as_uint(e) << 32 | q;
         m = v < m ? v : m;
       }
       atomicMin(&best[k], m);
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      if (sum[k][N] == 0.f) continue;
+    for (int k = 0; k < kKinds; ++k) {
+      if (x[k].sum[N] == 0.f) continue;
       const uint32_t q = (uint32_t)best[k];
       alone[k] = q / (N + 1);
       split[k] = q % (N + 1);
-      if (b == 0) {
-        float g;
-        split_time(h + cls[k] * N, sum[k], before[k], alone[k], split[k], lane_cost(cls[k]),
-                   (float)R.lanes, g);
-        // (the narrow class's split extensions run beside the 64-row class)
-        if (k < 2)
-          g64 += g;
-        else
-          gWide = g;
-      }
+      t[k] = split_time(x[k], alone[k], split[k], lane_cost(cls_of[k]), (float)R.lanes, groups[k]);
     }
   }
+  const bool merged = t[0] > 0.f && t[1] > 0.f && t[3] < t[0] + t[1];
   if (b == 0) {
-    seg[kSegEnd + 1] = (uint32_t)fminf(g64, (float)R.lanes - 1.f);
-    seg[kSegEnd + 2] = (uint32_t)gWide;
+    seg[kSegEnd + 1] =
+        (uint32_t)(merged ? groups[3] : fminf(groups[0] + groups[1], (float)R.lanes - 1.f));
+    seg[kSegEnd + 2] = (uint32_t)groups[2];
   }
   // the bins in queue order
-  const uint32_t s0 = alone[0], s1 = alone[1], s3 = alone[2];
-  const uint32_t t0 = split[0], t1 = split[1], t3 = split[2];
+  const uint32_t s0 = alone[0], s1 = alone[1], s2 = alone[2];
+  const uint32_t t0 = split[0], t1 = split[1], t2 = split[2];
   const uint32_t cls = min(b / N, (uint32_t)kClsInvalid), q = b - cls * N;
   uint32_t at = b;  // the classes from 256 cells on keep their place
   if (cls == kCls64) at = q;
+  else if (merged && (cls == kClsLane || cls == kClsNarrow))
+    at = N + 2 * q + (cls == kClsNarrow ? 1u : 0u);
   else if (cls == kClsLane)
     at = q < s1 ? N + q : q < t1 ? N + s1 + s0 + (q - s1) : N + t1 + t0 + (q - t1);
   else if (cls == kClsNarrow)
@@ -1081,12 +1093,12 @@ __global__ __launch_bounds__(512) void k_bin_scan(uint32_t* hist, uint32_t* seg,
   auto start = [&](uint32_t slot) { return slot ? h[slot - 1] : 0u; };
   if (b == 0) {
     seg[kSeg64] = 0;
-    seg[kSegSplit] = start(N + s1 + s0);
-    seg[kSegLane] = start(N + t1 + t0);
-    seg[kSegNarrow] = start(2 * N + t0);
+    seg[kSegSplit] = start(merged ? N + 2 * alone[3] : N + s1 + s0);
+    seg[kSegLane] = start(merged ? N + 2 * split[3] : N + t1 + t0);
+    seg[kSegNarrow] = start(merged ? 3 * N : 2 * N + t0);
     seg[kSegLong] = start(3 * N);
-    seg[kSegWideSplit] = start(3 * N + s3);
-    seg[kSegWide] = start(3 * N + t3);
+    seg[kSegWideSplit] = start(3 * N + s2);
+    seg[kSegWide] = start(3 * N + t2);
     seg[kSeg128] = start(4 * N);
     seg[kSeg256] = start(5 * N);
     seg[kSegInvalid] = start(6 * N);
@@ -1570,12 +1582,12 @@ struct Route {
 // pairs of 10 kbp at X = 25, one per wavefront / packed / lanes: 8,000 pairs
 // 3.02 / 4.11 / 2.90 ms, 16,000 3.16 / 4.30 / 3.11, 32,000 5.83 / 4.86 / 3.95;
 // at X = 50, one per wavefront / lanes: 8,000 4.78 / 4.90, 16,000 5.97 / 5.03.
-constexpr uint64_t kLaneMin = 32768;
+constexpr uint64_t kLaneMin = 24576;
 // Extensions up to which the batched form runs one per wavefront: their time
 // is the longest one's chain of steps, about 40 ns a step with a wavefront to
 // itself and 90 ns in a packed one.  64 pairs at X of 7 and 25: 1.59 -> 1.15 ms
 // as a plan; the figures above cross at about 24,000 pairs.
-constexpr uint64_t kSoloMax = 32767;
+constexpr uint64_t kSoloMax = kLaneMin - 1;
 
 Route batch_route(const xd::Scoring& sc, uint64_t n_ext, bool queue) {
   Route r = {queue, false, false, 0u};
