@@ -3,10 +3,13 @@
 //
 // Windows ("tiers") of 64, 128, 256, 512 and 1024 cells; an extension whose
 // band outgrows its window is appended to the next tier's overflow list and
-// re-run there from the start.  Past 1024 cells the band tier keeps the band
-// in global memory (one workgroup per extension), so no result is truncated.
+// goes on there from the state it left.  Past 1024 cells the band tier keeps
+// the band in global memory (one workgroup per extension), so no result is
+// truncated.
 //
-// Plain form (xd_align_batch), stream-ordered on the caller's stream:
+// Plain form (xd_align_batch), stream-ordered on the caller's stream, for
+// small batches and general scores (plain_queue; others go through the queue
+// below):
 //   k_reset      zero the counters and the histogram
 //   k_ext_first  one wavefront per extension (2 per task: left, right) with
 //                the 64-cell window
@@ -20,7 +23,11 @@
 // by first tier (chosen from X) and, within a tier, longest first (counting
 // sort on an estimated antidiagonal count).  Each tier's persistent waves
 // take its queue segment and then the previous tier's overflow list; the
-// combine follows.  A plan records the whole sequence in a hipGraph.
+// combine follows.  Which kernels the tiers run in (batch_route): with scores
+// 1/-1/-1 and enough extensions the lane tiers (k_lane_tier, k_lane_list), with
+// match = 1 the packed ones (k_pair*_tier) or, for few extensions, one per
+// wavefront (k_ext_tier), which general scores always take.  A plan records
+// the whole sequence in a hipGraph.
 #include <hip/hip_runtime.h>
 #include <stdarg.h>
 #include <stdint.h>
@@ -1589,6 +1596,18 @@ constexpr uint64_t kLaneMin = 24576;
 // as a plan; the figures above cross at about 24,000 pairs.
 constexpr uint64_t kSoloMax = kLaneMin - 1;
 
+// Whether a plain batch goes through the device queue all the same: with
+// match = 1, from 6,000 extensions on (longest first; read pairs of 10 kbp at
+// X = 25, without / with the queue: 2,000 pairs 1.58 / 1.64 ms, 4,000 2.30 /
+// 2.08, 100,000 17.9 / 5.6), or when X is known to need a wider first window
+// than 64 cells, which would otherwise be run and given up (2,000 pairs at X =
+// 50: 5.2 / 2.7 ms).
+constexpr uint64_t kQueueMin = 6000;
+
+bool plain_queue(const BatchArgs& A, uint64_t n_ext, const Tuned& tu) {
+  return pair_ok(A.sc) && (n_ext >= kQueueMin || (!A.x && A.x_scalar > tu.x_tier1));
+}
+
 Route batch_route(const xd::Scoring& sc, uint64_t n_ext, bool queue) {
   Route r = {queue, false, false, 0u};
   if (!queue) return r;
@@ -1979,6 +1998,7 @@ int enqueue(BatchArgs A, const Scratch& S, bool persistent, const Tuned& tu,
             hipStream_t stream, bool allow_profile) {
   A.ext = S.ext;
   const uint64_t n_ext = 2 * (uint64_t)A.n;
+  persistent = persistent || plain_queue(A, n_ext, tu);
   const bool prof = allow_profile && g_prof_on.load(std::memory_order_relaxed) != 0;
   ProfRecord rec = {};
   if (prof) {
