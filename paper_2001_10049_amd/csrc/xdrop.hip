@@ -8,7 +8,7 @@
 // truncated.
 //
 // Plain form (xd_align_batch), stream-ordered on the caller's stream, for
-// small batches and general scores (plain_queue; others go through the queue
+// small batches (plain_queue; others go through the queue
 // below):
 //   k_reset      zero the counters and the histogram
 //   k_ext_first  one wavefront per extension (2 per task: left, right) with
@@ -1542,6 +1542,7 @@ __global__ __launch_bounds__(kTraceThreads) void k_band_traceback(BandedArgs A, 
 
 struct Tuned {
   int waves_per_cu, group_steps, order, x_tier1, x_tier2, band_blocks;
+  bool x_given;  // the caller set an X limit
 };
 
 int device_cus() {
@@ -1596,16 +1597,26 @@ constexpr uint64_t kLaneMin = 24576;
 // as a plan; the figures above cross at about 24,000 pairs.
 constexpr uint64_t kSoloMax = kLaneMin - 1;
 
-// Whether a plain batch goes through the device queue all the same: with
-// match = 1, from 6,000 extensions on (longest first; read pairs of 10 kbp at
-// X = 25, without / with the queue: 2,000 pairs 1.58 / 1.64 ms, 4,000 2.30 /
-// 2.08, 100,000 17.9 / 5.6), or when X is known to need a wider first window
-// than 64 cells, which would otherwise be run and given up (2,000 pairs at X =
-// 50: 5.2 / 2.7 ms).
+// X up to which extensions start in a window whose limit is tier.  A cell k
+// rows off the best one on its antidiagonal has lost about k (gap + match /
+// 2); the default limits are for scores 1/-1/-1, where that is 1.5 k, and grow
+// with it.  20,011 pairs at X = 50 and 2/-3/-2, which so start in 64 cells
+// instead of 128 (and with wave_max_i32 by lane moves): 9.35 -> 5.13 ms; at X =
+// 100 and 5/-4/-8: 20.1 -> 5.25.
+int32_t x_limit(const Tuned& tu, const xd::Scoring& sc, int32_t tier) {
+  return tu.x_given ? tier : tier * (sc.M - 2 * sc.G) / 3;
+}
+
+// Whether a plain batch goes through the device queue all the same: from 6,000
+// extensions on (longest first; read pairs of 10 kbp at X = 25, without / with
+// the queue: 2,000 pairs 1.58 / 1.64 ms, 4,000 2.30 / 2.08, 100,000 17.9 / 5.6;
+// 20,011 pairs at X = 50 and 2/-3/-2: 6.9 / 5.1), or when X is known to need a
+// wider first window than 64 cells, which would otherwise be run and given up
+// (2,000 pairs at X = 50: 5.2 / 2.7 ms).
 constexpr uint64_t kQueueMin = 6000;
 
 bool plain_queue(const BatchArgs& A, uint64_t n_ext, const Tuned& tu) {
-  return pair_ok(A.sc) && (n_ext >= kQueueMin || (!A.x && A.x_scalar > tu.x_tier1));
+  return n_ext >= kQueueMin || (!A.x && A.x_scalar > x_limit(tu, A.sc, tu.x_tier1));
 }
 
 Route batch_route(const xd::Scoring& sc, uint64_t n_ext, bool queue) {
@@ -1783,7 +1794,8 @@ void launch_persistent_ext(const BatchArgs& A, const Scratch& S, uint64_t n_ext,
                            const Tuned& tu, const Route& Rt, hipEvent_t* ev,
                            hipStream_t stream) {
   const uint32_t grid = (uint32_t)((n_ext + 255) / 256);
-  BinRule R = {tu.x_tier1, tu.x_tier2, tu.order == 1 ? 1 : 0, Rt.lane_blocks};
+  BinRule R = {x_limit(tu, A.sc, tu.x_tier1), x_limit(tu, A.sc, tu.x_tier2),
+               tu.order == 1 ? 1 : 0, Rt.lane_blocks};
   hipLaunchKernelGGL(k_bin_hist, dim3(grid), dim3(256), 0, stream, A, R, (uint32_t)n_ext,
                      S.hist);
   hipLaunchKernelGGL(k_bin_scan, dim3(1), dim3(kBins), 0, stream, S.hist, S.ctr + kSeg, R,
@@ -1866,6 +1878,7 @@ int check_tuning(const xd_tuning* t, Tuned& out) {
   out.x_tier1 = 32;
   out.x_tier2 = 80;
   out.band_blocks = 0;
+  out.x_given = false;
   if (!t) return XD_OK;
   if (t->waves_per_cu) {
     if (t->waves_per_cu < 4 || t->waves_per_cu > 32 || t->waves_per_cu % 4)
@@ -1881,6 +1894,7 @@ int check_tuning(const xd_tuning* t, Tuned& out) {
     if (t->order != 1 && t->order != 2) return fail(XD_EINVAL, "order must be 1 or 2");
     out.order = t->order;
   }
+  out.x_given = t->x_tier1 || t->x_tier2;
   if (t->x_tier1) out.x_tier1 = t->x_tier1;
   if (t->x_tier2) out.x_tier2 = t->x_tier2;
   if (out.x_tier1 < 0 || out.x_tier2 < out.x_tier1)

