@@ -1330,12 +1330,10 @@ struct BandedArgs {
   uint32_t* end;
   int32_t* status;
   uint64_t* cells;
-  // traced bands: task t = t0 + block; its codes start at entry
-  // 16 * (tr_off[t] - tr_off0) of tr_codes and its group bases at
-  // tr_off[t] - tr_off0 of tr_bases
+  // traced bands: task t = t0 + block; its codes (64 words a group) start at
+  // group tr_off[t] - tr_off0 of tr_codes
   uint32_t t0;
-  uint4* tr_codes;
-  uint32_t* tr_bases;
+  uint32_t* tr_codes;
   const uint64_t* tr_off;
   uint64_t tr_off0;
 };
@@ -1384,8 +1382,7 @@ __global__ __launch_bounds__(64) void k_banded(BandedArgs A) {
   ExtOut o;
   if constexpr (TRACE) {
     const uint64_t g0 = A.tr_off[t] - A.tr_off0;
-    xd::banded_sw<UNIT, true>(bt, A.sc, ring, o,
-                              xd::BandTrace{A.tr_codes + g0 * kTraceGroup, A.tr_bases + g0});
+    xd::banded_sw<UNIT, true>(bt, A.sc, ring, o, xd::BandTrace{A.tr_codes + g0 * 64});
   } else {
     xd::banded_sw<UNIT>(bt, A.sc, ring, o);
   }
@@ -1422,121 +1419,144 @@ struct TraceOut {
   uint32_t* beg;    // [2 n]
 };
 
-// one thread per task: walk the stored codes back from the end cell to the
+// One wavefront per task: walk the stored codes back from the end cell to the
 // first cell whose H is 0, run-length encoding the steps, then reverse them.
-// The walk visits entries e = i + j - d_first downwards, one or two at a
-// time.  The thread's current group of 16 entries sits in its own LDS column;
-// the group before it is loaded into registers a whole group ahead and
-// written to LDS when the walk reaches it.
-constexpr int kTraceThreads = 64;
+// Lane t reads the code of the t-th cell down the current diagonal, so a run
+// of diagonal steps (up to 64) and the step that ends it take one pass; the
+// walk is then bound by that pass's LDS read and lane vote.  The codes of 16
+// groups sit in LDS in two blocks of 8, the block after them on its way in
+// registers: at most 128 antidiagonals, 8 groups, lie ahead in a pass.  10,000
+// pairs of 10 kbp reads, w = 32: 18.6 ms with one thread per task (each
+// waiting for its own group of codes) -> 3.1 ms.
+constexpr int kTraceBlock = 8;  // groups a block
 
-// the group's sixteen entries as plain locals (an array of them would be
-// kept in scratch memory)
-#define XD_TRACE_EACH(F) F(0) F(1) F(2) F(3) F(4) F(5) F(6) F(7) F(8) F(9) F(10) F(11) \
-  F(12) F(13) F(14) F(15)
-
-__global__ __launch_bounds__(kTraceThreads) void k_band_traceback(BandedArgs A, TraceOut T) {
-  __shared__ uint4 stage[kTraceGroup][kTraceThreads];
-  const uint64_t t = T.t0 + (uint64_t)blockIdx.x * kTraceThreads + threadIdx.x;
-  if (t >= T.t1) return;
+__global__ __launch_bounds__(64) void k_band_traceback(BandedArgs A, TraceOut T) {
+  constexpr int kWords = kTraceBlock * 64;
+  __shared__ uint4 ring4[2 * kWords / 4];
+  const uint32_t* ring = (const uint32_t*)ring4;
+  const int lane = xd::lane_id();
+  const uint64_t t = T.t0 + (uint64_t)blockIdx.x;
+  auto uni = [](uint32_t v) { return (int32_t)__builtin_amdgcn_readfirstlane(v); };
+  auto write = [&](int32_t i, int32_t j, uint32_t n) {
+    if (lane == 0) {
+      T.beg[2 * t] = (uint32_t)i;
+      T.beg[2 * t + 1] = (uint32_t)j;
+      T.n_ops[t] = n;
+    }
+  };
+  if (uni((uint32_t)A.status[t]) != XD_TASK_OK || uni((uint32_t)A.score[t]) <= 0) {
+    write(0, 0, 0);
+    return;
+  }
   uint32_t* ops = T.ops + t * T.max_ops;
-  int32_t i = (int32_t)A.end[2 * t], j = (int32_t)A.end[2 * t + 1];
-  if (A.status[t] != XD_TASK_OK || A.score[t] <= 0) {
-    T.beg[2 * t] = 0;
-    T.beg[2 * t + 1] = 0;
-    T.n_ops[t] = 0;
-    return;
-  }
+  int32_t i = uni(A.end[2 * t]), j = uni(A.end[2 * t + 1]);
   const uint32_t ra = A.pairs[2 * t], rb = A.pairs[2 * t + 1];
-  const int32_t c = (int32_t)A.seeds[2 * t] - (int32_t)A.seeds[2 * t + 1];
-  const int32_t w = A.w ? A.w[t] : A.w_scalar;
-  const xd::BandSpan sp = xd::band_span((int32_t)A.st.len[ra], (int32_t)A.st.len[rb], c, w);
-  const uint64_t g0 = A.tr_off[t] - A.tr_off0;
-  const int64_t n_ent = (int64_t)(A.tr_off[t + 1] - A.tr_off[t]) * kTraceGroup;
-  const uint4* codes = A.tr_codes + g0 * kTraceGroup;
-  const uint32_t* bases = A.tr_bases + g0;
-  int64_t e = (int64_t)(i + j) - sp.d_first;
-  if (e < 0 || e >= n_ent) {  // the end cell is not in the stored band
-    T.beg[2 * t] = 0;
-    T.beg[2 * t + 1] = 0;
-    T.n_ops[t] = 0;
-    A.status[t] = XD_TASK_TRACE_FAULT;
+  const int32_t lb = uni(A.st.len[rb]);
+  const int32_t c = uni(A.seeds[2 * t]) - uni(A.seeds[2 * t + 1]);
+  const int32_t w = uni((uint32_t)(A.w ? A.w[t] : A.w_scalar));
+  const xd::BandSpan sp = xd::band_span(uni(A.st.len[ra]), lb, c, w);
+  const int32_t n_groups = uni((uint32_t)(A.tr_off[t + 1] - A.tr_off[t]));
+  const uint32_t* codes = A.tr_codes + (A.tr_off[t] - A.tr_off0) * 64;
+  const int32_t d_first = sp.d_first;
+  int32_t e = i + j - d_first;
+  if (e < 0 || e >= n_groups * kTraceGroup) {  // the end cell is not in the stored band
+    write(0, 0, 0);
+    if (lane == 0) A.status[t] = XD_TASK_TRACE_FAULT;
     return;
   }
-  int64_t grp = e >> 4;
-#define XD_TRACE_DECL(k) uint4 n##k;
-#define XD_TRACE_LOAD(k) n##k = codes[pg * kTraceGroup + k];
-#define XD_TRACE_STAGE(k) stage[k][threadIdx.x] = n##k;
-  XD_TRACE_EACH(XD_TRACE_DECL)
-  int64_t pg = grp;
-  XD_TRACE_EACH(XD_TRACE_LOAD)
-  XD_TRACE_EACH(XD_TRACE_STAGE)
-  // the group before (group 0 reloads itself: a valid address, never used)
-  pg = grp > 0 ? grp - 1 : 0;
-  XD_TRACE_EACH(XD_TRACE_LOAD)
-  uint32_t gb = bases[grp], nb = bases[pg];
-  uint32_t n = 0, run = 0, cur = 0;
+  // block b's groups, four words a lane at a time (0 outside the stored ones)
+  uint4 p0, p1;
+  auto load = [&](int32_t b) {
+    const int32_t g = b * kTraceBlock + lane / 16;
+    const uint4* src = (const uint4*)codes + (int64_t)b * (kWords / 4) + lane;
+    p0 = b >= 0 && g < n_groups ? src[0] : make_uint4(0, 0, 0, 0);
+    p1 = b >= 0 && g + 4 < n_groups ? src[64] : make_uint4(0, 0, 0, 0);
+  };
+  auto stage = [&](int32_t b) {
+    uint4* dst = ring4 + (b & 1) * (kWords / 4) + lane;
+    dst[0] = p0;
+    dst[64] = p1;
+  };
+  int32_t blk = e / (kTraceGroup * kTraceBlock);  // the block of the current cell
+  load(blk);
+  stage(blk);
+  load(blk - 1);
+  stage(blk - 1);
+  load(blk - 2);
+  uint32_t n = 0, run = 0, cur = 0, out = 0;  // out: lane k holds entry n - n % 64 + k
+  auto flush = [&](uint32_t from) {
+    const uint32_t at = from + (uint32_t)lane;
+    if (at < n && at < T.max_ops) ops[at] = out;
+  };
+  auto push = [&]() {
+    out = (uint32_t)lane == (n & 63u) ? (run << 2 | cur) : out;
+    ++n;
+    if ((n & 63u) == 0) flush(n - 64);
+  };
+  auto take = [&](uint32_t op, uint32_t by) {
+    if (run && op != cur) {
+      push();
+      run = 0;
+    }
+    cur = op;
+    run += by;
+  };
   bool fault = false;
   while (i > 0 && j > 0) {
-    e = (int64_t)(i + j) - sp.d_first;
+    e = i + j - d_first;
     if (e < 0) {
       fault = true;
       break;
     }
-    if ((e >> 4) != grp) {  // stepped into the group before: its entries are in nxt
-      --grp;
-      if ((e >> 4) != grp) {
-        fault = true;
-        break;
-      }
-      XD_TRACE_EACH(XD_TRACE_STAGE)
-      gb = nb;
-      pg = grp > 0 ? grp - 1 : 0;
-      XD_TRACE_EACH(XD_TRACE_LOAD)
-      nb = bases[pg];
+    while (e / (kTraceGroup * kTraceBlock) < blk) {
+      --blk;
+      stage(blk - 1);  // (in place of the block above)
+      load(blk - 2);
     }
-    const int32_t bit = i - (int32_t)gb;
-    if (bit < 0 || bit > 63) {
+    xd::wave_lds_fence();
+    const int32_t row = i - lane, ent = e - 2 * lane;
+    const bool there = row > 0 && j - lane > 0 && ent >= 0;
+    const int32_t g = ent >> 4;
+    const int32_t bit = row - xd::band_base(d_first + 16 * g, lb, c, w);
+    const bool in = there && bit >= 0 && bit < 64;
+    const uint32_t word = ring[(g & (2 * kTraceBlock - 1)) * 64 + (bit & 63)];
+    const uint32_t code = (word >> (2 * (ent & 15))) & 3u;
+    const uint64_t stop = ~xd::ballot64(in && code == 1u);
+    const int32_t r = stop ? (int32_t)__builtin_ctzll(stop) : 64;
+    if (r) {
+      take(XD_OP_M, (uint32_t)r);
+      i -= r;
+      j -= r;
+    }
+    if (r == 64) continue;
+    if (!((xd::ballot64(there) >> r) & 1)) continue;  // at the grid's edge, or before the band
+    if (!((xd::ballot64(in) >> r) & 1)) {
       fault = true;
       break;
     }
-    const uint4 v = stage[e & (kTraceGroup - 1)][threadIdx.x];
-    const uint64_t plane0 = (uint64_t)v.y << 32 | v.x, plane1 = (uint64_t)v.w << 32 | v.z;
-    const uint32_t code =
-        (uint32_t)((plane0 >> bit) & 1u) | (uint32_t)(((plane1 >> bit) & 1u) << 1);
-    if (code == 0) break;
-    // ops: 0 = M (from the diagonal), 2 = D (from (i-1, j)), 1 = I (from (i, j-1))
-    const uint32_t op = code == 1 ? XD_OP_M : code == 2 ? XD_OP_D : XD_OP_I;
-    if (run && op != cur) {
-      if (n < T.max_ops) ops[n] = run << 2 | cur;
-      ++n;
-      run = 0;
-    }
-    cur = op;
-    ++run;
-    if (code != 3) --i;
-    if (code != 2) --j;
+    const uint32_t step = (uint32_t)__builtin_amdgcn_readlane((int)code, r);
+    if (step == 0) break;
+    // 2: from (i-1, j); 3: from (i, j-1)
+    take(step == 2 ? XD_OP_D : XD_OP_I, 1u);
+    if (step == 2) --i;
+    else --j;
   }
-  if (run) {
-    if (n < T.max_ops) ops[n] = run << 2 | cur;
-    ++n;
-  }
-  if (n <= T.max_ops)
-    for (uint32_t a = 0, b = n; a + 1 < b; ++a, --b) {
-      const uint32_t x = ops[a];
-      ops[a] = ops[b - 1];
-      ops[b - 1] = x;
+  if (run) push();
+  if (n & 63u) flush(n & ~63u);
+  if (n <= T.max_ops) {
+    __threadfence_block();
+    for (uint32_t a = (uint32_t)lane; a < n / 2; a += 64) {
+      const uint32_t x = ops[a], y = ops[n - 1 - a];
+      ops[a] = y;
+      ops[n - 1 - a] = x;
     }
-  T.beg[2 * t] = (uint32_t)i;
-  T.beg[2 * t + 1] = (uint32_t)j;
-  T.n_ops[t] = n;
-  if (fault) A.status[t] = XD_TASK_TRACE_FAULT;
-  else if (n > T.max_ops) A.status[t] = XD_TASK_OPS_OVERFLOW;
+  }
+  write(i, j, n);
+  if (lane == 0) {
+    if (fault) A.status[t] = XD_TASK_TRACE_FAULT;
+    else if (n > T.max_ops) A.status[t] = XD_TASK_OPS_OVERFLOW;
+  }
 }
-#undef XD_TRACE_STAGE
-#undef XD_TRACE_LOAD
-#undef XD_TRACE_DECL
-#undef XD_TRACE_EACH
 
 // ---- launch sequences -------------------------------------------------------
 
@@ -2481,7 +2501,6 @@ int xd_banded_batch(const xd_store* store, const uint32_t* pairs, const uint32_t
   A.cells = cells;
   A.t0 = 0;
   A.tr_codes = nullptr;
-  A.tr_bases = nullptr;
   A.tr_off = nullptr;
   A.tr_off0 = 0;
   hipStream_t stream = (hipStream_t)hip_stream;
@@ -2538,16 +2557,13 @@ int xd_banded_traceback(const xd_store* store, const uint32_t* pairs, const uint
   std::vector<uint64_t> h(n + 1);
   HIP_TRY(hipMemcpyAsync(h.data(), off, (n + 1) * 8, hipMemcpyDeviceToHost, stream));
   HIP_TRY(hipStreamSynchronize(stream));
-  const uint64_t group_bytes = kTraceGroup * sizeof(uint4) + sizeof(uint32_t);
+  const uint64_t group_bytes = 64 * sizeof(uint32_t);
   uint64_t cap = (trace_budget ? trace_budget : (32ull << 30)) / group_bytes;
   for (uint64_t t = 0; t < n; ++t) cap = std::max(cap, h[t + 1] - h[t]);
   cap = std::max<uint64_t>(std::min(cap, h[n]), 1);
-  uint4* codes = nullptr;
-  uint32_t* bases = nullptr;
-  HIP_TRY(ar.get(&codes, cap * kTraceGroup));
-  HIP_TRY(ar.get(&bases, cap));
+  uint32_t* codes = nullptr;
+  HIP_TRY(ar.get(&codes, cap * 64));
   A.tr_codes = codes;
-  A.tr_bases = bases;
   A.tr_off = off;
   for (uint64_t t0 = 0; t0 < n;) {
     uint64_t t1 = t0 + 1;
@@ -2561,8 +2577,7 @@ int xd_banded_traceback(const xd_store* store, const uint32_t* pairs, const uint
       hipLaunchKernelGGL((k_banded<false, true>), dim3((uint32_t)(t1 - t0)), dim3(64), 0, stream,
                          A);
     TraceOut T{(uint32_t)t0, (uint32_t)t1, max_ops, ops, n_ops, beg};
-    hipLaunchKernelGGL(k_band_traceback, dim3(xscan::grid_for(t1 - t0, kTraceThreads)),
-                       dim3(kTraceThreads), 0, stream, A, T);
+    hipLaunchKernelGGL(k_band_traceback, dim3((uint32_t)(t1 - t0)), dim3(64), 0, stream, A, T);
     t0 = t1;
   }
   hipError_t le = hipGetLastError();
