@@ -1147,11 +1147,11 @@ __device__ __forceinline__ void banded_sw(const BandTask& e, const Scoring& sc,
     const int32_t thr0 = thr;
     int32_t fl2 = g * (d - 2) + bias;  // floor two antidiagonals back
     int32_t fl1 = fl2 + g;
-    auto body = [&](auto t_tag) {
+    auto body = [&](auto t_tag, auto inside) {
       constexpr int t = decltype(t_tag)::value;
       const int32_t fl = fl1 + g;  // floor of this antidiagonal
       uint64_t m;
-      if (interior) {
+      if constexpr (decltype(inside)::value) {
         m = mk[t & 1];
         mk[t & 1] = m << 1;
       } else {
@@ -1192,7 +1192,14 @@ __device__ __forceinline__ void banded_sw(const BandTask& e, const Scoring& sc,
       fl2 = fl1;
       fl1 = fl;
     };
-    static_for<GS>(body);
+    // one test per group: each of the two sixteen-step bodies is straight-line code
+    auto inner = [&](auto t) { body(t, std::true_type{}); };
+    auto edge = [&](auto t) { body(t, std::false_type{}); };
+    if (interior) {
+      static_for<GS>(inner);
+    } else {
+      static_for<GS>(edge);
+    }
     if constexpr (UNIT) {
       if (thr != thr0 + GS * g) {
         uint64_t lm[1];
