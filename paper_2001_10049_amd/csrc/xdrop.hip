@@ -43,6 +43,7 @@
 #include "xdrop.h"
 #include "scan.h"
 #include "store_view.h"
+#include "band_pair.h"
 #include "xdrop_device.h"
 #include "lane_device.h"
 #include "pair2_device.h"
@@ -1395,6 +1396,80 @@ __global__ __launch_bounds__(64) void k_banded(BandedArgs A) {
   }
 }
 
+// Two tasks at a time to a wavefront, `per` (at most 64) to a workgroup: the
+// longest that is left goes to the half that is free first, so that both halves
+// end close together (see pair_tasks).
+template <bool UNIT>
+__global__ __launch_bounds__(64) void k_banded_pair(BandedArgs A, uint32_t n, uint32_t per) {
+  __shared__ uint32_t lds[xd::pair_band::kLdsWords];
+  __shared__ uint32_t ring[kBandedLdsWords];
+  const int lane = xd::lane_id();
+  const uint32_t first = blockIdx.x * per, i = first + lane;
+  auto put = [&](int32_t task, const ExtOut& o) {
+    const uint64_t t = A.t0 + (uint32_t)task;
+    if (lane == 0) {
+      A.score[t] = o.best;
+      A.end[2 * t] = (uint32_t)o.bi;
+      A.end[2 * t + 1] = (uint32_t)o.bj;
+      A.status[t] = XD_TASK_OK;
+      if (A.cells) A.cells[t] = o.cells;
+    }
+  };
+  // a task to a lane: its reads and band, and the antidiagonals it sweeps
+  uint32_t ra = 0, rb = 0;
+  int32_t la = 0, lb = 0, c = 0, w = 0, len = -1;
+  bool wide = false;
+  if ((uint32_t)lane < per && i < n) {
+    const uint64_t t = A.t0 + i;
+    ra = A.pairs[2 * t], rb = A.pairs[2 * t + 1];
+    const uint32_t pa = A.seeds[2 * t], pb = A.seeds[2 * t + 1];
+    w = A.w ? A.w[t] : A.w_scalar;
+    const int32_t st = banded_status(A, (uint32_t)t, ra, rb, pa, pb, w);
+    if (st != XD_TASK_OK) {
+      A.score[t] = INT32_MIN;
+      A.end[2 * t] = 0;
+      A.end[2 * t + 1] = 0;
+      A.status[t] = st;
+      if (A.cells) A.cells[t] = 0;
+    } else {
+      la = (int32_t)A.st.len[ra];
+      lb = (int32_t)A.st.len[rb];
+      c = (int32_t)pa - (int32_t)pb;
+      const xd::BandSpan sp = xd::band_span(la, lb, c, w);
+      // too long for 16 bits, or no band inside the grid
+      wide = sp.dlo > sp.dhi || (int64_t)min(la, lb) * A.sc.M > xd::pair_band::kMaxH;
+      if (!wide) len = sp.d_last - sp.d_first;
+    }
+  }
+  auto load = [&](int l, auto& e) {
+    const uint32_t ua = __builtin_amdgcn_readlane(ra, l), ub = __builtin_amdgcn_readlane(rb, l);
+    e.wa = A.st.words + A.st.word_off[ua];
+    e.wb = A.st.words + A.st.word_off[ub];
+    e.la = __builtin_amdgcn_readlane(la, l);
+    e.lb = __builtin_amdgcn_readlane(lb, l);
+    e.c = __builtin_amdgcn_readlane(c, l);
+    e.w = __builtin_amdgcn_readlane(w, l);
+  };
+  for (uint64_t m = __builtin_amdgcn_ballot_w64(wide); m; m &= m - 1) {
+    const int l = __builtin_ctzll(m);
+    xd::BandTask bt;
+    load(l, bt);
+    ExtOut o;
+    xd::banded_sw<UNIT>(bt, A.sc, ring, o);
+    put((int32_t)first + l, o);
+  }
+  auto next = [&](xd::pair_band::Half& e) {
+    const int32_t top = xd::wave_max_i32(len + 1) - 1;
+    e.task = -1;
+    if (top < 0) return;
+    const int l = __builtin_ctzll(__builtin_amdgcn_ballot_w64(len == top));
+    load(l, e);
+    e.task = (int32_t)first + l;
+    if (lane == l) len = -1;
+  };
+  xd::banded_pairs<UNIT>(A.sc, lds, ring, next, put);
+}
+
 // trace groups of task t (0 when the task is invalid or its band misses the grid)
 __global__ __launch_bounds__(256) void k_band_groups(BandedArgs A, uint64_t* groups) {
   const uint64_t t = (uint64_t)blockIdx.x * 256 + threadIdx.x;
@@ -2472,6 +2547,13 @@ int xd_align_pairs(const xd_store* store, uint64_t n_pairs, const uint32_t* pair
   return XD_OK;
 }
 
+// Tasks to a workgroup of the two-task kernel.  Four even out the lengths of
+// the two halves, two leave more workgroups to spread: of 10 kbp pairs, w = 32,
+// 50,000 take 6.25 ms by fours and 7.03 by twos (6.90 by eights), 20,000 3.21
+// and 3.53, 10,000 2.58 and 2.52, 2,000 1.59 and 1.47 (eight wavefronts a SIMD
+// hold 16,384 tasks).
+uint32_t pair_tasks(uint64_t n) { return n > 16384 ? 4 : 2; }
+
 int xd_banded_batch(const xd_store* store, const uint32_t* pairs, const uint32_t* seeds,
                     const int32_t* w, int32_t w_scalar, uint64_t n, int32_t k, int32_t match,
                     int32_t mismatch, int32_t gap, int32_t* score, uint32_t* end,
@@ -2504,10 +2586,22 @@ int xd_banded_batch(const xd_store* store, const uint32_t* pairs, const uint32_t
   A.tr_off = nullptr;
   A.tr_off0 = 0;
   hipStream_t stream = (hipStream_t)hip_stream;
-  // one wave per task, in chunks of 2^24 (a grid holds at most 2^32 - 1 work-items)
+  // in chunks of 2^24 tasks (a grid holds at most 2^32 - 1 work-items)
   for (uint64_t t0 = 0; t0 < n; t0 += kChunkBlocks) {
     A.t0 = (uint32_t)t0;
     const uint32_t nb = (uint32_t)std::min<uint64_t>(kChunkBlocks, n - t0);
+    // Two tasks to a wavefront wherever a mismatch costs (the floor in 16 bits
+    // rests on that): 50,000 pairs of 10 kbp reads, w = 32, 11.6 -> 6.25 ms
+    // against one to a wavefront, 500 of them 2.10 -> 1.42 (its antidiagonals
+    // are the shorter chain too).
+    if (mismatch < 0) {
+      const uint32_t per = pair_tasks(n), np = (nb + per - 1) / per;
+      if (match == 1)
+        hipLaunchKernelGGL((k_banded_pair<true>), dim3(np), dim3(64), 0, stream, A, nb, per);
+      else
+        hipLaunchKernelGGL((k_banded_pair<false>), dim3(np), dim3(64), 0, stream, A, nb, per);
+      continue;
+    }
     if (match == 1)
       hipLaunchKernelGGL((k_banded<true, false>), dim3(nb), dim3(64), 0, stream, A);
     else

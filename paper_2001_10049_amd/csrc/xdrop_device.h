@@ -1034,10 +1034,19 @@ __device__ __forceinline__ int32_t band_base(int32_t d, int32_t lb, int32_t c, i
   return max(max(1, d - lb), (d + c - w + 1) >> 1) - 1;
 }
 
-template <bool UNIT, bool TRACE = false>
+// A state to go on from (antidiagonal d next, lane l = row base + l, the last
+// two antidiagonals as banded_sw holds them, best so far T), up to d_stop.
+struct BandStart {
+  int32_t d, d_stop, base;
+  int32_t U1, Up;
+  int32_t T;
+};
+
+template <bool UNIT, bool TRACE = false, bool RESUME = false>
 __device__ __forceinline__ void banded_sw(const BandTask& e, const Scoring& sc,
                                           uint32_t* __restrict__ ring, ExtOut& res,
-                                          BandTrace tr = BandTrace{nullptr}) {
+                                          BandTrace tr = BandTrace{nullptr},
+                                          BandStart from = BandStart{}) {
   constexpr int GS = 16;
   constexpr int RING = 256, MASK = RING - 1, MIR = GS + 1, RA = 128;
   const int lane = lane_id();
@@ -1061,13 +1070,14 @@ __device__ __forceinline__ void banded_sw(const BandTask& e, const Scoring& sc,
   res.bj = 0;
   res.flags = kExtDone;
   if (dlo > dhi) return;
-  const int32_t d_first = sp.d_first, d_last = sp.d_last;
+  const int32_t d_first = RESUME ? from.d : sp.d_first;
+  const int32_t d_last = RESUME ? min(from.d_stop, sp.d_last) : sp.d_last;
   // band rows on antidiagonal dd, inside the grid
   auto row_lo = [&](int32_t dd) { return max(max(1, dd - lb), (dd + c - w + 1) >> 1); };
   auto row_hi = [&](int32_t dd) { return min(min(la, dd - 1), (dd + c + w) >> 1); };
 
-  int32_t base = row_lo(d_first) - 1;  // row of lane 0
-  int32_t U1 = 0, Up = 0;  // U on the last antidiagonal, and on the one before shifted up a row
+  int32_t base = RESUME ? from.base : row_lo(d_first) - 1;  // row of lane 0
+  int32_t U1 = RESUME ? from.U1 : 0, Up = RESUME ? from.Up : 0;  // U on the last antidiagonal, and on the one before shifted up a row
   uint32_t aa = 0;
   uint8_t* aring = (uint8_t*)(ring + RING + MIR);
   auto word_of = [&](const uint32_t* wd, int32_t q, int32_t lim) -> uint32_t {
@@ -1111,6 +1121,7 @@ __device__ __forceinline__ void banded_sw(const BandTask& e, const Scoring& sc,
 
   int32_t d = d_first;                 // next antidiagonal
   int32_t thr = g * d + bias;          // T + g*d + bias: an improving cell exceeds it
+  if constexpr (RESUME) thr += from.T;
   int32_t bi = 0, dstar = 0;
   while (d <= d_last) {
     // slide the window to the group's lowest band row minus one
