@@ -167,7 +167,7 @@ __device__ __forceinline__ void banded_pairs(const Scoring& sc, uint32_t* __rest
     s.T = max(e.best - 1, 0);
     BandTask bt{e.wa, e.wb, e.la, e.lb, e.c, e.w};
     ExtOut o;
-    banded_sw<UNIT, false, true>(bt, sc, ring, o, BandTrace{nullptr}, s);
+    banded_sw<UNIT, kNoTrace, true>(bt, sc, ring, o, BandTrace{nullptr}, s);
     done(e.task, o);
   };
   using zero = std::integral_constant<int, 0>;

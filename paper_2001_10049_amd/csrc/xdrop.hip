@@ -1354,163 +1354,35 @@ __device__ __forceinline__ int32_t banded_status(const BandedArgs& A, uint32_t t
   return XD_TASK_OK;
 }
 
-// One wavefront per task: band around the seed's diagonal over the whole reads.
-template <bool UNIT, bool TRACE>
-__global__ __launch_bounds__(64) void k_banded(BandedArgs A) {
-  __shared__ uint32_t ring[kBandedLdsWords];
-  const uint32_t t = A.t0 + blockIdx.x;
-  const uint32_t ra = A.pairs[2 * (uint64_t)t], rb = A.pairs[2 * (uint64_t)t + 1];
-  const uint32_t pa = A.seeds[2 * (uint64_t)t], pb = A.seeds[2 * (uint64_t)t + 1];
-  const int32_t w = A.w ? A.w[t] : A.w_scalar;
-  const int32_t st = banded_status(A, t, ra, rb, pa, pb, w);
-  if (__builtin_amdgcn_readfirstlane(st) != XD_TASK_OK) {
-    if (xd::lane_id() == 0) {
-      A.score[t] = INT32_MIN;
-      A.end[2 * (uint64_t)t] = 0;
-      A.end[2 * (uint64_t)t + 1] = 0;
-      A.status[t] = st;
-      if (A.cells) A.cells[t] = 0;
-    }
-    return;
-  }
-  xd::BandTask bt;
-  bt.wa = A.st.words + A.st.word_off[__builtin_amdgcn_readfirstlane(ra)];
-  bt.wb = A.st.words + A.st.word_off[__builtin_amdgcn_readfirstlane(rb)];
-  bt.la = (int32_t)A.st.len[ra];
-  bt.lb = (int32_t)A.st.len[rb];
-  bt.c = (int32_t)pa - (int32_t)pb;
-  bt.w = w;
-  ExtOut o;
-  if constexpr (TRACE) {
-    const uint64_t g0 = A.tr_off[t] - A.tr_off0;
-    xd::banded_sw<UNIT, true>(bt, A.sc, ring, o, xd::BandTrace{A.tr_codes + g0 * 64});
-  } else {
-    xd::banded_sw<UNIT>(bt, A.sc, ring, o);
-  }
-  if (xd::lane_id() == 0) {
-    A.score[t] = o.best;
-    A.end[2 * (uint64_t)t] = (uint32_t)o.bi;
-    A.end[2 * (uint64_t)t + 1] = (uint32_t)o.bj;
-    A.status[t] = XD_TASK_OK;
-    if (A.cells) A.cells[t] = o.cells;
-  }
-}
-
-// Two tasks at a time to a wavefront, `per` (at most 64) to a workgroup: the
-// longest that is left goes to the half that is free first, so that both halves
-// end close together (see pair_tasks).
-template <bool UNIT>
-__global__ __launch_bounds__(64) void k_banded_pair(BandedArgs A, uint32_t n, uint32_t per) {
-  __shared__ uint32_t lds[xd::pair_band::kLdsWords];
-  __shared__ uint32_t ring[kBandedLdsWords];
-  const int lane = xd::lane_id();
-  const uint32_t first = blockIdx.x * per, i = first + lane;
-  auto put = [&](int32_t task, const ExtOut& o) {
-    const uint64_t t = A.t0 + (uint32_t)task;
-    if (lane == 0) {
-      A.score[t] = o.best;
-      A.end[2 * t] = (uint32_t)o.bi;
-      A.end[2 * t + 1] = (uint32_t)o.bj;
-      A.status[t] = XD_TASK_OK;
-      if (A.cells) A.cells[t] = o.cells;
-    }
-  };
-  // a task to a lane: its reads and band, and the antidiagonals it sweeps
-  uint32_t ra = 0, rb = 0;
-  int32_t la = 0, lb = 0, c = 0, w = 0, len = -1;
-  bool wide = false;
-  if ((uint32_t)lane < per && i < n) {
-    const uint64_t t = A.t0 + i;
-    ra = A.pairs[2 * t], rb = A.pairs[2 * t + 1];
-    const uint32_t pa = A.seeds[2 * t], pb = A.seeds[2 * t + 1];
-    w = A.w ? A.w[t] : A.w_scalar;
-    const int32_t st = banded_status(A, (uint32_t)t, ra, rb, pa, pb, w);
-    if (st != XD_TASK_OK) {
-      A.score[t] = INT32_MIN;
-      A.end[2 * t] = 0;
-      A.end[2 * t + 1] = 0;
-      A.status[t] = st;
-      if (A.cells) A.cells[t] = 0;
-    } else {
-      la = (int32_t)A.st.len[ra];
-      lb = (int32_t)A.st.len[rb];
-      c = (int32_t)pa - (int32_t)pb;
-      const xd::BandSpan sp = xd::band_span(la, lb, c, w);
-      // too long for 16 bits, or no band inside the grid
-      wide = sp.dlo > sp.dhi || (int64_t)min(la, lb) * A.sc.M > xd::pair_band::kMaxH;
-      if (!wide) len = sp.d_last - sp.d_first;
-    }
-  }
-  auto load = [&](int l, auto& e) {
-    const uint32_t ua = __builtin_amdgcn_readlane(ra, l), ub = __builtin_amdgcn_readlane(rb, l);
-    e.wa = A.st.words + A.st.word_off[ua];
-    e.wb = A.st.words + A.st.word_off[ub];
-    e.la = __builtin_amdgcn_readlane(la, l);
-    e.lb = __builtin_amdgcn_readlane(lb, l);
-    e.c = __builtin_amdgcn_readlane(c, l);
-    e.w = __builtin_amdgcn_readlane(w, l);
-  };
-  for (uint64_t m = __builtin_amdgcn_ballot_w64(wide); m; m &= m - 1) {
-    const int l = __builtin_ctzll(m);
-    xd::BandTask bt;
-    load(l, bt);
-    ExtOut o;
-    xd::banded_sw<UNIT>(bt, A.sc, ring, o);
-    put((int32_t)first + l, o);
-  }
-  auto next = [&](xd::pair_band::Half& e) {
-    const int32_t top = xd::wave_max_i32(len + 1) - 1;
-    e.task = -1;
-    if (top < 0) return;
-    const int l = __builtin_ctzll(__builtin_amdgcn_ballot_w64(len == top));
-    load(l, e);
-    e.task = (int32_t)first + l;
-    if (lane == l) len = -1;
-  };
-  xd::banded_pairs<UNIT>(A.sc, lds, ring, next, put);
-}
-
-// trace groups of task t (0 when the task is invalid or its band misses the grid)
-__global__ __launch_bounds__(256) void k_band_groups(BandedArgs A, uint64_t* groups) {
-  const uint64_t t = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t >= A.n) return;
-  const uint32_t ra = A.pairs[2 * t], rb = A.pairs[2 * t + 1];
-  const uint32_t pa = A.seeds[2 * t], pb = A.seeds[2 * t + 1];
-  const int32_t w = A.w ? A.w[t] : A.w_scalar;
-  uint64_t g = 0;
-  if (banded_status(A, (uint32_t)t, ra, rb, pa, pb, w) == XD_TASK_OK) {
-    const xd::BandSpan sp = xd::band_span((int32_t)A.st.len[ra], (int32_t)A.st.len[rb],
-                                          (int32_t)pa - (int32_t)pb, w);
-    if (sp.dlo <= sp.dhi) g = (uint64_t)(sp.d_last - sp.d_first + kTraceGroup) / kTraceGroup;
-  }
-  groups[t] = g;
-}
-
 struct TraceOut {
-  uint32_t t0, t1;  // tasks of this sub-batch
   uint32_t max_ops;
   uint32_t* ops;    // [n * max_ops]
   uint32_t* n_ops;  // [n]
   uint32_t* beg;    // [2 n]
 };
 
-// One wavefront per task: walk the stored codes back from the end cell to the
-// first cell whose H is 0, run-length encoding the steps, then reverse them.
+// Walks task t's stored codes back from the end cell to the first cell whose H
+// is 0, run-length encoding the steps, then reverses them.  The wavefront that
+// swept the band walks it, while others sweep (pairs of 10 kbp reads, w = 32, in
+// launches of their own and in one: 10,000 pairs 8.85 and 8.6 ms, 3,000 pairs
+// 5.11 and 4.80).
 // Lane t reads the code of the t-th cell down the current diagonal, so a run
 // of diagonal steps (up to 64) and the step that ends it take one pass; the
 // walk is then bound by that pass's LDS read and lane vote.  The codes of 16
 // groups sit in LDS in two blocks of 8, the block after them on its way in
 // registers: at most 128 antidiagonals, 8 groups, lie ahead in a pass.  10,000
 // pairs of 10 kbp reads, w = 32: 18.6 ms with one thread per task (each
-// waiting for its own group of codes) -> 3.1 ms.
+// waiting for its own group of codes) -> 3.1 ms alone.
 constexpr int kTraceBlock = 8;  // groups a block
+constexpr int kTraceWords = kTraceBlock * 64;
 
-__global__ __launch_bounds__(64) void k_band_traceback(BandedArgs A, TraceOut T) {
-  constexpr int kWords = kTraceBlock * 64;
-  __shared__ uint4 ring4[2 * kWords / 4];
+// bt, o: the task and its end cell; ring4: 2 * kTraceWords words of LDS
+__device__ __forceinline__ void band_walk(const BandedArgs& A, const TraceOut& T, uint64_t t,
+                                          const xd::BandTask& bt, const ExtOut& o,
+                                          uint4* ring4) {
+  constexpr int kWords = kTraceWords;
   const uint32_t* ring = (const uint32_t*)ring4;
   const int lane = xd::lane_id();
-  const uint64_t t = T.t0 + (uint64_t)blockIdx.x;
   auto uni = [](uint32_t v) { return (int32_t)__builtin_amdgcn_readfirstlane(v); };
   auto write = [&](int32_t i, int32_t j, uint32_t n) {
     if (lane == 0) {
@@ -1519,17 +1391,15 @@ __global__ __launch_bounds__(64) void k_band_traceback(BandedArgs A, TraceOut T)
       T.n_ops[t] = n;
     }
   };
-  if (uni((uint32_t)A.status[t]) != XD_TASK_OK || uni((uint32_t)A.score[t]) <= 0) {
+  if (o.best <= 0) {
     write(0, 0, 0);
     return;
   }
+  __threadfence_block();  // the sweep's codes are in memory, its LDS reads done
   uint32_t* ops = T.ops + t * T.max_ops;
-  int32_t i = uni(A.end[2 * t]), j = uni(A.end[2 * t + 1]);
-  const uint32_t ra = A.pairs[2 * t], rb = A.pairs[2 * t + 1];
-  const int32_t lb = uni(A.st.len[rb]);
-  const int32_t c = uni(A.seeds[2 * t]) - uni(A.seeds[2 * t + 1]);
-  const int32_t w = uni((uint32_t)(A.w ? A.w[t] : A.w_scalar));
-  const xd::BandSpan sp = xd::band_span(uni(A.st.len[ra]), lb, c, w);
+  int32_t i = uni((uint32_t)o.bi), j = uni((uint32_t)o.bj);
+  const int32_t lb = uni((uint32_t)bt.lb), c = uni((uint32_t)bt.c), w = uni((uint32_t)bt.w);
+  const xd::BandSpan sp = xd::band_span(uni((uint32_t)bt.la), lb, c, w);
   const int32_t n_groups = uni((uint32_t)(A.tr_off[t + 1] - A.tr_off[t]));
   const uint32_t* codes = A.tr_codes + (A.tr_off[t] - A.tr_off0) * 64;
   const int32_t d_first = sp.d_first;
@@ -1631,6 +1501,147 @@ __global__ __launch_bounds__(64) void k_band_traceback(BandedArgs A, TraceOut T)
     if (fault) A.status[t] = XD_TASK_TRACE_FAULT;
     else if (n > T.max_ops) A.status[t] = XD_TASK_OPS_OVERFLOW;
   }
+}
+
+// One wavefront per task: band around the seed's diagonal over the whole reads.
+template <bool UNIT, int TRACE>
+__global__ __launch_bounds__(64) void k_banded(BandedArgs A, TraceOut T) {
+  // the walk's codes go where the sweep's bases were
+  constexpr int kLds = TRACE ? std::max(kBandedLdsWords, 2 * kTraceWords) : kBandedLdsWords;
+  __shared__ uint4 lds[(kLds + 3) / 4];
+  uint32_t* ring = (uint32_t*)lds;
+  const uint32_t t = A.t0 + blockIdx.x;
+  const uint32_t ra = A.pairs[2 * (uint64_t)t], rb = A.pairs[2 * (uint64_t)t + 1];
+  const uint32_t pa = A.seeds[2 * (uint64_t)t], pb = A.seeds[2 * (uint64_t)t + 1];
+  const int32_t w = A.w ? A.w[t] : A.w_scalar;
+  const int32_t st = banded_status(A, t, ra, rb, pa, pb, w);
+  if (__builtin_amdgcn_readfirstlane(st) != XD_TASK_OK) {
+    if (xd::lane_id() == 0) {
+      A.score[t] = INT32_MIN;
+      A.end[2 * (uint64_t)t] = 0;
+      A.end[2 * (uint64_t)t + 1] = 0;
+      A.status[t] = st;
+      if (A.cells) A.cells[t] = 0;
+      if constexpr (TRACE) {
+        T.beg[2 * (uint64_t)t] = 0;
+        T.beg[2 * (uint64_t)t + 1] = 0;
+        T.n_ops[t] = 0;
+      }
+    }
+    return;
+  }
+  xd::BandTask bt;
+  bt.wa = A.st.words + A.st.word_off[__builtin_amdgcn_readfirstlane(ra)];
+  bt.wb = A.st.words + A.st.word_off[__builtin_amdgcn_readfirstlane(rb)];
+  bt.la = (int32_t)A.st.len[ra];
+  bt.lb = (int32_t)A.st.len[rb];
+  bt.c = (int32_t)pa - (int32_t)pb;
+  bt.w = w;
+  ExtOut o;
+  if constexpr (TRACE) {
+    const uint64_t g0 = A.tr_off[t] - A.tr_off0;
+    xd::banded_sw<UNIT, TRACE>(bt, A.sc, ring, o, xd::BandTrace{A.tr_codes + g0 * 64});
+  } else {
+    xd::banded_sw<UNIT>(bt, A.sc, ring, o);
+  }
+  if (xd::lane_id() == 0) {
+    A.score[t] = o.best;
+    A.end[2 * (uint64_t)t] = (uint32_t)o.bi;
+    A.end[2 * (uint64_t)t + 1] = (uint32_t)o.bj;
+    A.status[t] = XD_TASK_OK;
+    if (A.cells) A.cells[t] = o.cells;
+  }
+  if constexpr (TRACE) band_walk(A, T, t, bt, o, lds);
+}
+
+// Two tasks at a time to a wavefront, `per` (at most 64) to a workgroup: the
+// longest that is left goes to the half that is free first, so that both halves
+// end close together (see pair_tasks).
+template <bool UNIT>
+__global__ __launch_bounds__(64) void k_banded_pair(BandedArgs A, uint32_t n, uint32_t per) {
+  __shared__ uint32_t lds[xd::pair_band::kLdsWords];
+  __shared__ uint32_t ring[kBandedLdsWords];
+  const int lane = xd::lane_id();
+  const uint32_t first = blockIdx.x * per, i = first + lane;
+  auto put = [&](int32_t task, const ExtOut& o) {
+    const uint64_t t = A.t0 + (uint32_t)task;
+    if (lane == 0) {
+      A.score[t] = o.best;
+      A.end[2 * t] = (uint32_t)o.bi;
+      A.end[2 * t + 1] = (uint32_t)o.bj;
+      A.status[t] = XD_TASK_OK;
+      if (A.cells) A.cells[t] = o.cells;
+    }
+  };
+  // a task to a lane: its reads and band, and the antidiagonals it sweeps
+  uint32_t ra = 0, rb = 0;
+  int32_t la = 0, lb = 0, c = 0, w = 0, len = -1;
+  bool wide = false;
+  if ((uint32_t)lane < per && i < n) {
+    const uint64_t t = A.t0 + i;
+    ra = A.pairs[2 * t], rb = A.pairs[2 * t + 1];
+    const uint32_t pa = A.seeds[2 * t], pb = A.seeds[2 * t + 1];
+    w = A.w ? A.w[t] : A.w_scalar;
+    const int32_t st = banded_status(A, (uint32_t)t, ra, rb, pa, pb, w);
+    if (st != XD_TASK_OK) {
+      A.score[t] = INT32_MIN;
+      A.end[2 * t] = 0;
+      A.end[2 * t + 1] = 0;
+      A.status[t] = st;
+      if (A.cells) A.cells[t] = 0;
+    } else {
+      la = (int32_t)A.st.len[ra];
+      lb = (int32_t)A.st.len[rb];
+      c = (int32_t)pa - (int32_t)pb;
+      const xd::BandSpan sp = xd::band_span(la, lb, c, w);
+      // too long for 16 bits, or no band inside the grid
+      wide = sp.dlo > sp.dhi || (int64_t)min(la, lb) * A.sc.M > xd::pair_band::kMaxH;
+      if (!wide) len = sp.d_last - sp.d_first;
+    }
+  }
+  auto load = [&](int l, auto& e) {
+    const uint32_t ua = __builtin_amdgcn_readlane(ra, l), ub = __builtin_amdgcn_readlane(rb, l);
+    e.wa = A.st.words + A.st.word_off[ua];
+    e.wb = A.st.words + A.st.word_off[ub];
+    e.la = __builtin_amdgcn_readlane(la, l);
+    e.lb = __builtin_amdgcn_readlane(lb, l);
+    e.c = __builtin_amdgcn_readlane(c, l);
+    e.w = __builtin_amdgcn_readlane(w, l);
+  };
+  for (uint64_t m = __builtin_amdgcn_ballot_w64(wide); m; m &= m - 1) {
+    const int l = __builtin_ctzll(m);
+    xd::BandTask bt;
+    load(l, bt);
+    ExtOut o;
+    xd::banded_sw<UNIT>(bt, A.sc, ring, o);
+    put((int32_t)first + l, o);
+  }
+  auto next = [&](xd::pair_band::Half& e) {
+    const int32_t top = xd::wave_max_i32(len + 1) - 1;
+    e.task = -1;
+    if (top < 0) return;
+    const int l = __builtin_ctzll(__builtin_amdgcn_ballot_w64(len == top));
+    load(l, e);
+    e.task = (int32_t)first + l;
+    if (lane == l) len = -1;
+  };
+  xd::banded_pairs<UNIT>(A.sc, lds, ring, next, put);
+}
+
+// trace groups of task t (0 when the task is invalid or its band misses the grid)
+__global__ __launch_bounds__(256) void k_band_groups(BandedArgs A, uint64_t* groups) {
+  const uint64_t t = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+  if (t >= A.n) return;
+  const uint32_t ra = A.pairs[2 * t], rb = A.pairs[2 * t + 1];
+  const uint32_t pa = A.seeds[2 * t], pb = A.seeds[2 * t + 1];
+  const int32_t w = A.w ? A.w[t] : A.w_scalar;
+  uint64_t g = 0;
+  if (banded_status(A, (uint32_t)t, ra, rb, pa, pb, w) == XD_TASK_OK) {
+    const xd::BandSpan sp = xd::band_span((int32_t)A.st.len[ra], (int32_t)A.st.len[rb],
+                                          (int32_t)pa - (int32_t)pb, w);
+    if (sp.dlo <= sp.dhi) g = (uint64_t)(sp.d_last - sp.d_first + kTraceGroup) / kTraceGroup;
+  }
+  groups[t] = g;
 }
 
 // ---- launch sequences -------------------------------------------------------
@@ -2603,9 +2614,9 @@ int xd_banded_batch(const xd_store* store, const uint32_t* pairs, const uint32_t
       continue;
     }
     if (match == 1)
-      hipLaunchKernelGGL((k_banded<true, false>), dim3(nb), dim3(64), 0, stream, A);
+      hipLaunchKernelGGL((k_banded<true, xd::kNoTrace>), dim3(nb), dim3(64), 0, stream, A, TraceOut{});
     else
-      hipLaunchKernelGGL((k_banded<false, false>), dim3(nb), dim3(64), 0, stream, A);
+      hipLaunchKernelGGL((k_banded<false, xd::kNoTrace>), dim3(nb), dim3(64), 0, stream, A, TraceOut{});
   }
   hipError_t le = hipGetLastError();
   if (le != hipSuccess) return hip_fail(le, "kernel launch");
@@ -2659,19 +2670,23 @@ int xd_banded_traceback(const xd_store* store, const uint32_t* pairs, const uint
   HIP_TRY(ar.get(&codes, cap * 64));
   A.tr_codes = codes;
   A.tr_off = off;
+  // codes that come with the values take two bits of them
+  const bool tags = match - mismatch <= xd::kTagBonus &&
+                    4 * ((int64_t)(match - 2 * gap) * store->max_len + 64 * 128 + xd::kBias0) <
+                        INT32_MAX;
   for (uint64_t t0 = 0; t0 < n;) {
     uint64_t t1 = t0 + 1;
     while (t1 < n && t1 - t0 < kChunkBlocks && h[t1 + 1] - h[t0] <= cap) ++t1;
     A.t0 = (uint32_t)t0;
     A.tr_off0 = h[t0];
+    const TraceOut T{max_ops, ops, n_ops, beg};
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3((uint32_t)(t1 - t0)), dim3(64), 0, stream, A, T);
+    };
     if (match == 1)
-      hipLaunchKernelGGL((k_banded<true, true>), dim3((uint32_t)(t1 - t0)), dim3(64), 0, stream,
-                         A);
+      tags ? launch(k_banded<true, xd::kTraceTags>) : launch(k_banded<true, xd::kTraceChecks>);
     else
-      hipLaunchKernelGGL((k_banded<false, true>), dim3((uint32_t)(t1 - t0)), dim3(64), 0, stream,
-                         A);
-    TraceOut T{(uint32_t)t0, (uint32_t)t1, max_ops, ops, n_ops, beg};
-    hipLaunchKernelGGL(k_band_traceback, dim3((uint32_t)(t1 - t0)), dim3(64), 0, stream, A, T);
+      tags ? launch(k_banded<false, xd::kTraceTags>) : launch(k_banded<false, xd::kTraceChecks>);
     t0 = t1;
   }
   hipError_t le = hipGetLastError();

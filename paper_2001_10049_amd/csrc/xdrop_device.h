@@ -1022,11 +1022,22 @@ __device__ __forceinline__ BandSpan band_span(int32_t la, int32_t lb, int32_t c,
 // its first one + l at codes[64k + l].  Each lane so collects its row's codes
 // in a register and the group leaves with one store of the wave; gathering
 // each antidiagonal's two lane masks instead took four lane writes and eight
-// scalar instructions a step (10,000 pairs of 10 kbp reads, w = 32: 11.3 -> 8.3 ms for the band, most of it the longest
-// task).
+// scalar instructions a step (10,000 pairs of 10 kbp reads, w = 32: 11.3 -> 8.3
+// ms for the band).
+//
+// The code of a step comes with the maximum itself where values have room for
+// two more bits: a unit of the score counts 4, and the candidates carry 3 (H =
+// 0), 2 (diagonal), 1 (row above) and 0 (same row) there, so that the larger
+// of equals is the one the walk wants; the complement is the code.  Found by
+// comparisons instead, they take 14 vector instructions an antidiagonal, not 10
+// (sweep and walk of
+// those pairs: 9.4 -> 8.1 ms).
 struct BandTrace {
   uint32_t* codes;
 };
+enum { kNoTrace = 0, kTraceChecks = 1, kTraceTags = 2 };
+// the widest M - MM whose bonus is still a byte in quarters
+constexpr int32_t kTagBonus = 63;
 
 // first row of the window on antidiagonal d, the first of a group: the row
 // below the band's lowest one inside the grid
@@ -1042,7 +1053,7 @@ struct BandStart {
   int32_t T;
 };
 
-template <bool UNIT, bool TRACE = false, bool RESUME = false>
+template <bool UNIT, int TRACE = 0, bool RESUME = false>
 __device__ __forceinline__ void banded_sw(const BandTask& e, const Scoring& sc,
                                           uint32_t* __restrict__ ring, ExtOut& res,
                                           BandTrace tr = BandTrace{nullptr},
@@ -1050,14 +1061,15 @@ __device__ __forceinline__ void banded_sw(const BandTask& e, const Scoring& sc,
   constexpr int GS = 16;
   constexpr int RING = 256, MASK = RING - 1, MIR = GS + 1, RA = 128;
   const int lane = lane_id();
-  const int32_t g = __builtin_amdgcn_readfirstlane(-sc.G);
-  const int32_t C = __builtin_amdgcn_readfirstlane(sc.MM + 2 * g);
-  const uint32_t dM = __builtin_amdgcn_readfirstlane((uint32_t)(sc.M - sc.MM));
+  constexpr int32_t Q = TRACE == kTraceTags ? 4 : 1;  // what a unit of the score counts here
+  const int32_t g = __builtin_amdgcn_readfirstlane(-sc.G * Q);
+  const int32_t C = __builtin_amdgcn_readfirstlane(sc.MM * Q + 2 * g);
+  const uint32_t dM = __builtin_amdgcn_readfirstlane((uint32_t)(sc.M - sc.MM) * Q);
   const int32_t la = __builtin_amdgcn_readfirstlane(e.la);
   const int32_t lb = __builtin_amdgcn_readfirstlane(e.lb);
   const int32_t c = __builtin_amdgcn_readfirstlane(e.c);
   const int32_t w = __builtin_amdgcn_readfirstlane(e.w);
-  const int32_t bias = kBias0;
+  const int32_t bias = kBias0 * Q;
   // band diagonals that meet the grid, and the cells on them
   const BandSpan sp = band_span(la, lb, c, w);
   const int32_t dlo = sp.dlo, dhi = sp.dhi;
@@ -1170,26 +1182,34 @@ __device__ __forceinline__ void banded_sw(const BandTask& e, const Scoring& sc,
       }
       const int32_t upv = shr1_zero(U1);
       const int32_t dg = max(Up, fl2);
-      const int32_t dgs = dg + (int32_t)bmv[t] + C;
-      int32_t s = max(max(dgs, upv), U1);
-      s = max(s, fl);
       const bool in = __builtin_amdgcn_inverse_ballot_w64(m);
-      const int32_t u = in ? s : 0;
-      if constexpr (TRACE) {
-        // the step that produced H: diagonal first, then (i-1, j), then (i, j-1);
-        // 0 where H is 0.  Out-of-band neighbours hold 0 < fl and never match,
-        // so the walk never reaches a cell outside the band.
-        uint32_t code = s == upv ? 2u : 3u;
-        code = s == dgs ? 1u : code;
-        code = s == fl ? 0u : code;
-        trc = __builtin_amdgcn_alignbit(code, trc, 2);
+      int32_t u;
+      if constexpr (TRACE == kTraceTags) {
+        const int32_t s = max(max(max(dg + (int32_t)bmv[t] + (C + 2), upv + 1), U1), fl + 3);
+        trc = __builtin_amdgcn_alignbit((uint32_t)s, trc, 2);
+        u = in ? s & ~3 : 0;
+      } else {
+        const int32_t dgs = dg + (int32_t)bmv[t] + C;
+        int32_t s = max(max(dgs, upv), U1);
+        s = max(s, fl);
+        u = in ? s : 0;
+        if constexpr (TRACE == kTraceChecks) {
+          // the step that produced H: diagonal first, then (i-1, j), then (i, j-1);
+          // 0 where H is 0.  Out-of-band neighbours hold 0 < fl and never match,
+          // so the walk never reaches a cell outside the band.
+          uint32_t code = s == upv ? 2u : 3u;
+          code = s == dgs ? 1u : code;
+          code = s == fl ? 0u : code;
+          trc = __builtin_amdgcn_alignbit(code, trc, 2);
+        }
       }
       const uint64_t im = ballot64(u > thr);
       Up = upv;
       U1 = u;
       if constexpr (UNIT) {
         imp[t][0] = im;
-        thr = add_nonzero(thr, g, im);
+        if constexpr (Q == 1) thr = add_nonzero(thr, g, im);
+        else thr += im ? g + Q : g;
       } else {
         int32_t dT = 0;
         if (im) {
@@ -1223,13 +1243,13 @@ __device__ __forceinline__ void banded_sw(const BandTask& e, const Scoring& sc,
       bi = base + (int32_t)__builtin_ctzll(last);
       dstar = d + lastt - 1;
     }
-    if constexpr (TRACE) {
-      tr.codes[(d - d_first) / GS * 64 + lane] = trc;
+    if constexpr (TRACE != 0) {
+      tr.codes[(d - d_first) / GS * 64 + lane] = TRACE == kTraceTags ? ~trc : trc;
     }
     d += GS;
   }
   // thr = T + g*d + bias with d the next antidiagonal
-  res.best = thr - g * d - bias;
+  res.best = (thr - g * d - bias) / Q;
   res.bi = res.best > 0 ? bi : 0;
   res.bj = res.best > 0 ? dstar - bi : 0;
 }
