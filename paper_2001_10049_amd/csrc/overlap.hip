@@ -20,6 +20,7 @@
 #include <stdint.h>
 #include <stdio.h>
 
+#include <algorithm>
 #include <mutex>
 #include <vector>
 
@@ -65,6 +66,26 @@ __device__ __forceinline__ uint64_t bloom_word(uint64_t h, uint64_t W) {
   return ((h >> 32) * W) >> 32;
 }
 
+// Filter B is lines of kLine words (128 bytes, what a memory access moves).  A
+// k-mer's line comes from the smallest hash of its m-mers, which neighbouring
+// k-mers share three or four at a time, and the word in the line from four bits
+// of h that bloom_bits leaves: pass 2 looks kAhead k-mers up at once and so
+// waits for fewer lines (138 Mbp, k = 17: 2.73 -> 2.08 ms; 2.63 with a line for
+// every k-mer, and 2.15 and 2.47 with 8 and 16 k-mers at once).  Pass 1 gains
+// nothing from it (5.6 ms): its atomics are carried out at the memory, 26 G a
+// second, wherever they lie.  A filter that a die's L2 holds (4 MB) has nothing
+// to gain and takes the word from h alone (LINES = false): 30 Mbp, both strands,
+// 1.95 ms for the stage with lines and 1.91 without.
+constexpr uint64_t kLine = 16;
+constexpr uint64_t kLineWords = (4 << 20) / 8;  // smallest filter B with lines
+
+template <bool LINES>
+__device__ __forceinline__ uint64_t b_word(uint32_t mh, uint64_t h, uint64_t W) {
+  if constexpr (!LINES) return bloom_word(h, W);
+  const uint32_t lines = (uint32_t)(W / kLine);
+  return (uint64_t)__umulhi(mh * 0x9e3779b1u, lines) * kLine + ((h >> 18) & (kLine - 1));
+}
+
 // ---- k-mer enumeration --------------------------------------------------------
 
 struct KmerScan {
@@ -77,15 +98,27 @@ struct KmerScan {
   int32_t k;
   uint64_t kmask;             // 2k low bits
   int32_t both;               // 1: canonical k-mers (both strands)
+  int32_t m;                  // length of the m-mers that choose a k-mer's line in B
+  uint64_t mmask;             // 2m low bits
 };
 
-// calls f(read, pos, code, strand) for each k-mer start in chunk c, in
-// increasing pos; code packs the k bases 2 bits each, the first base highest.
-// Forward strand only: the k-mer's code, strand 0.  Both strands: the
-// smaller of the code and its reverse complement's code (the complement
-// 3 - b of each base, in reverse order), strand 1 when the reverse
-// complement is the smaller.
-template <class F>
+constexpr int kWindow = 6;  // the m-mers of a k-mer, at most
+constexpr int kAhead = 4;   // k-mers handed over at a time
+
+// a k-mer: its code and strand, and the smallest hash of its m-mers
+struct Kmer {
+  uint64_t code;
+  uint32_t strand;
+  uint32_t mh;
+};
+
+// Calls f(read, pos, kmers, n) for the k-mer starts of chunk c in increasing
+// pos, kAhead of them at a time (n <= kAhead in the last call); code packs the k
+// bases 2 bits each, the first base highest.  Forward strand only: the k-mer's
+// code, strand 0.  Both strands: the smaller of the code and its reverse
+// complement's code (the complement 3 - b of each base, in reverse order),
+// strand 1 when the reverse complement is the smaller; the m-mers likewise.
+template <bool LINES, class F>
 __device__ __forceinline__ void for_kmers(const KmerScan& s, uint64_t c, F&& f) {
   uint32_t lo = 0, hi = s.n_reads - 1;  // the last read whose first chunk is <= c
   while (lo < hi) {
@@ -107,18 +140,41 @@ __device__ __forceinline__ void for_kmers(const KmerScan& s, uint64_t c, F&& f) 
     return (wv >> ((q & 15) * 2)) & 3u;
   };
   const uint32_t top = 2u * (uint32_t)(s.k - 1);  // bit of a reverse-complement k-mer's last base
+  const uint32_t mtop = 2u * (uint32_t)(s.k - s.m);
+  const int window = s.k - s.m + 1;
   uint64_t code = 0, rcode = 0;
-  for (uint32_t q = p0; q + 1 < p0 + (uint32_t)s.k; ++q) {
-    const uint64_t b = base(q);
-    code = (code << 2) | b;
-    rcode = (rcode >> 2) | ((3ull - b) << top);
-  }
-  for (uint32_t p = p0; p < p1; ++p) {
-    const uint64_t b = base(p + (uint32_t)s.k - 1);
+  uint32_t h[kWindow];  // hashes of the last m-mers, the newest first
+  for (int i = 0; i < kWindow; ++i) h[i] = 0xffffffffu;
+  auto add = [&](uint64_t b) {
     code = ((code << 2) | b) & s.kmask;
     rcode = (rcode >> 2) | ((3ull - b) << top);
-    const bool flip = s.both && rcode < code;
-    f(r, p, flip ? rcode : code, flip ? 1u : 0u);
+  };
+  auto add_hash = [&]() {
+    if constexpr (!LINES) return;
+    uint64_t v = code & s.mmask;
+    if (s.both) v = min(v, rcode >> mtop);
+    for (int i = kWindow - 1; i > 0; --i) h[i] = h[i - 1];
+    h[0] = (uint32_t)((v * 0x9e3779b97f4a7c15ull) >> 32);
+  };
+  for (uint32_t q = 0; q + 1 < (uint32_t)s.k; ++q) {
+    add(base(p0 + q));
+    if (q + 1 >= (uint32_t)s.m) add_hash();
+  }
+  for (uint32_t p = p0; p < p1; p += kAhead) {
+    Kmer km[kAhead];
+    const int n = (int)min((uint32_t)kAhead, p1 - p);
+    for (int i = 0; i < kAhead; ++i) {
+      if (i < n) {
+        add(base(p + i + (uint32_t)s.k - 1));
+        add_hash();
+      }
+      const bool flip = s.both && rcode < code;
+      uint32_t mh = h[0];
+      if constexpr (LINES)
+        for (int q = 1; q < kWindow; ++q) mh = q < window ? min(mh, h[q]) : mh;
+      km[i] = Kmer{flip ? rcode : code, flip ? 1u : 0u, mh};
+    }
+    f(r, p, km, n);
   }
 }
 
@@ -133,22 +189,26 @@ __device__ __forceinline__ void block_add(unsigned long long* dst, uint64_t v) {
 
 // pass 1: filter A, repeats into filter B; ctr[0] += repeats, ctr[3] += the
 // repeats that set new bits in B (about one per distinct repeated k-mer)
+template <bool LINES>
 __global__ __launch_bounds__(kThreads) void k_bloom(KmerScan s, unsigned long long* A,
                                                     uint64_t WA, unsigned long long* B,
                                                     uint64_t WB, unsigned long long* ctr) {
   const uint64_t c = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
   uint32_t rep = 0, fresh = 0;
   if (c < s.n_chunks) {
-    for_kmers(s, c, [&](uint32_t, uint32_t, uint64_t code, uint32_t) {
-      const uint64_t h = fmix64(code);
-      const unsigned long long bits = bloom_bits(h);
-      const unsigned long long old = atomicOr(&A[bloom_word(h, WA)], bits);
-      if ((old & bits) == bits) {
-        const uint64_t h2 = fmix64(code ^ kSaltB);
-        const unsigned long long b2 = bloom_bits(h2);
-        const unsigned long long old2 = atomicOr(&B[bloom_word(h2, WB)], b2);
-        ++rep;
-        fresh += (old2 & b2) != b2;
+    for_kmers<LINES>(s, c, [&](uint32_t, uint32_t, const Kmer* km, int n) {
+      for (int q = 0; q < kAhead; ++q) {
+        if (q >= n) break;
+        const uint64_t h = fmix64(km[q].code);
+        const unsigned long long bits = bloom_bits(h);
+        const unsigned long long old = atomicOr(&A[bloom_word(h, WA)], bits);
+        if ((old & bits) == bits) {
+          const uint64_t h2 = fmix64(km[q].code ^ kSaltB);
+          const unsigned long long b2 = bloom_bits(h2);
+          const unsigned long long old2 = atomicOr(&B[b_word<LINES>(km[q].mh, h2, WB)], b2);
+          ++rep;
+          fresh += (old2 & b2) != b2;
+        }
       }
     });
   }
@@ -176,32 +236,39 @@ struct Table {
 
 // pass 2: the k-mers in B into the table; ctr[2] = 1 when a key found no slot
 // within kMaxProbe probes (the host then doubles the table and reruns the pass)
+template <bool LINES>
 __global__ __launch_bounds__(kThreads) void k_table(KmerScan s, const unsigned long long* B,
                                                     uint64_t WB, Table t,
                                                     unsigned long long* ctr) {
   const uint64_t c = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
   if (c >= s.n_chunks) return;
-  for_kmers(s, c, [&](uint32_t r, uint32_t p, uint64_t code, uint32_t strand) {
-    const uint64_t h2 = fmix64(code ^ kSaltB);
-    const unsigned long long bits = bloom_bits(h2);
-    if ((B[bloom_word(h2, WB)] & bits) != bits) return;
-    const unsigned long long key = code + 1;
-    uint64_t slot = fmix64(code ^ kSaltT) & (t.cap - 1);
-    for (uint64_t probe = 0;; ++probe) {
-      if (probe == t.cap || probe == kMaxProbe) {  // full or crowded: the host regrows it
-        atomicOr(&ctr[2], 1ull);
-        return;
-      }
-      unsigned long long cur = t.keys[slot];
-      if (cur == 0) {
-        cur = atomicCAS(&t.keys[slot], 0ull, key);
-        if (cur == 0) cur = key;
-      }
-      if (cur == key) break;
-      slot = (slot + 1) & (t.cap - 1);
+  for_kmers<LINES>(s, c, [&](uint32_t r, uint32_t p, const Kmer* km, int n) {
+    unsigned long long bits[kAhead], have[kAhead];
+    for (int q = 0; q < kAhead; ++q) {
+      const uint64_t h2 = fmix64(km[q].code ^ kSaltB);
+      bits[q] = bloom_bits(h2);
+      have[q] = B[b_word<LINES>(km[q].mh, h2, WB)];
     }
-    const uint32_t i = atomicAdd(&t.cnt[slot], 1u);
-    if (i < t.m) t.loc[slot * t.m + i] = make_uint2(r, p | strand << 31);
+    for (int q = 0; q < kAhead; ++q) {
+      if (q >= n || (have[q] & bits[q]) != bits[q]) continue;
+      const unsigned long long key = km[q].code + 1;
+      uint64_t slot = fmix64(km[q].code ^ kSaltT) & (t.cap - 1);
+      for (uint64_t probe = 0;; ++probe) {
+        if (probe == t.cap || probe == kMaxProbe) {  // full or crowded: the host regrows it
+          atomicOr(&ctr[2], 1ull);
+          return;
+        }
+        unsigned long long cur = t.keys[slot];
+        if (cur == 0) {
+          cur = atomicCAS(&t.keys[slot], 0ull, key);
+          if (cur == 0) cur = key;
+        }
+        if (cur == key) break;
+        slot = (slot + 1) & (t.cap - 1);
+      }
+      const uint32_t i = atomicAdd(&t.cnt[slot], 1u);
+      if (i < t.m) t.loc[slot * t.m + i] = make_uint2(r, (p + q) | km[q].strand << 31);
+    }
   });
 }
 
@@ -488,7 +555,7 @@ int find_overlaps(const xd_store* store, int32_t k, uint32_t m, uint32_t bloom_b
   Arena ar(st, &g_cache[dev]);
   if (cn.kmers > 0) {
     const uint64_t WA = (cn.kmers * bloom_bits + 63) / 64;
-    const uint64_t WB = WA / 16 + 64;
+    const uint64_t WB = (WA / 16 + 64 + kLine - 1) & ~(kLine - 1);
     uint64_t* d_chunk = nullptr;
     unsigned long long *A = nullptr, *B = nullptr, *ctr = nullptr;
     OV_TRY(ar.get(&d_chunk, chunk_off.size()));
@@ -500,10 +567,15 @@ int find_overlaps(const xd_store* store, int32_t k, uint32_t m, uint32_t bloom_b
     OV_TRY(hipMemsetAsync(A, 0, WA * 8, st));
     OV_TRY(hipMemsetAsync(B, 0, WB * 8, st));
     OV_TRY(hipMemsetAsync(ctr, 0, 4 * 8, st));
+    // up to kWindow m-mers to a k-mer, none shorter than 11 bases
+    const int32_t mm = std::min(k, std::max(k - kWindow + 1, 11));
     KmerScan ks{sv.words, sv.word_off, sv.len, d_chunk, n_chunks, sv.n_reads, k,
-                k == 32 ? ~0ull : (1ull << (2 * k)) - 1, strands == 2 ? 1 : 0};
-    hipLaunchKernelGGL(k_bloom, dim3(grid_for(n_chunks, kThreads)), dim3(kThreads), 0, st, ks, A,
-                       WA, B, WB, ctr);
+                k == 32 ? ~0ull : (1ull << (2 * k)) - 1, strands == 2 ? 1 : 0, mm,
+                mm == 32 ? ~0ull : (1ull << (2 * mm)) - 1};
+    const bool in_lines = WB >= kLineWords;
+    hipLaunchKernelGGL(in_lines ? k_bloom<true> : k_bloom<false>,
+                       dim3(grid_for(n_chunks, kThreads)), dim3(kThreads), 0, st, ks, A, WA, B, WB,
+                       ctr);
     hipLaunchKernelGGL(k_popcount, dim3(grid_for(WB, kThreads * 16)), dim3(kThreads), 0, st, B,
                        WB, ctr);
     unsigned long long h_ctr[4];
@@ -535,8 +607,9 @@ int find_overlaps(const xd_store* store, int32_t k, uint32_t m, uint32_t bloom_b
       OV_TRY(hipMemsetAsync(t.keys, 0, cap * 8, st));
       OV_TRY(hipMemsetAsync(t.cnt, 0, cap * 4, st));
       OV_TRY(hipMemsetAsync(ctr + 2, 0, 8, st));
-      hipLaunchKernelGGL(k_table, dim3(grid_for(n_chunks, kThreads)), dim3(kThreads), 0, st, ks,
-                         B, WB, t, ctr);
+      hipLaunchKernelGGL(in_lines ? k_table<true> : k_table<false>,
+                         dim3(grid_for(n_chunks, kThreads)), dim3(kThreads), 0, st, ks, B, WB, t,
+                         ctr);
       unsigned long long full = 0;
       if ((rc = fetch(st, ctr + 2, &full))) return rc;
       if (!full) break;
