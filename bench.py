@@ -13,8 +13,7 @@ Prints one JSON line: GCUPS (evaluated cells of both extensions per second,
 the oracle's cell definition) as `value`, pairs/s beside it, the dominant
 kernel's roofline position and the CPU oracle timed on a bounded sample
 (all host threads, then one; the host CPU model).  Beside them: the batched
-form's packed tier against the int32 and packed 16-bit peaks, the
-2,000,000-task c3 workload (X in {7, 25, 50}) plain against batched, and a
+form's first tier, the 2,000,000-task c3 workload (X in {7, 25, 50}) plain against batched, and a
 short c5 serving window (Poisson requests, p50/p99 latency and pairs/s;
 bench_serve.py runs the full 20 s window).
 """
@@ -33,9 +32,12 @@ sys.path.insert(0, ROOT)
 METRIC = "GCUPS and aligned pairs/sec for X-drop extension at X=25 (1 MI355X)"
 # MI355X: 256 CUs x 64 int32 lanes per clock x 2.4 GHz
 PEAK_INT32_TOPS = 256 * 64 * 2.4e9 / 1e12
-OPS_PER_CELL = 8  # compare, select, add diagonal, max(up,left), add gap, max, compare, select
-KERNEL_NAMES = {"plain": "k_ext_first<1, 16, true>",
-                "persistent": "k_pair_tier<4> (64-cell tier, two extensions per wave, queue)"}
+# compare, select, add diagonal, max(up,left), add gap, max, compare, select: what a cell
+# costs one int32 lane.  The lane tiers hold 32 rows of a window in the bits of a register,
+# so a lane's operation works on up to 32 cells and `frac` can pass 1.
+OPS_PER_CELL = 8
+FIRST_TIER = "k_lane_tier<6, 2> (one extension per lane, 64 rows in bit planes)"
+KERNEL_NAMES = {"plain": FIRST_TIER, "persistent": FIRST_TIER, "plan": FIRST_TIER}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_c2.json")
 
 WORKLOAD_DESC = {
@@ -234,7 +236,7 @@ def main():
     gcups = results[head]["gcups"]
     prof = profs.get(head) or next(iter(profs.values()))
 
-    # dominant kernel: the 64-cell first tier; its algorithmic work is every
+    # dominant kernel: the 64-row first tier; its algorithmic work is every
     # cell it completes (all cells when no extension moved to a wider tier)
     launches = max(prof["batches"], 1)
     if prof["to_tier2"] == 0 and (head == "plain" or w.x.max() <= 32):
@@ -253,21 +255,17 @@ def main():
                 "ext_overflowed": [int(prof["to_tier2"]), int(prof["to_tier3"]),
                                    int(prof["to_tier4"]), int(prof["to_tier5"]),
                                    int(prof["to_band"])]}
-    # the batched form's packed tier (two extensions per wave, 16-bit halves)
-    # against both peaks: int32 lanes, and packed 16-bit lanes (twice that)
-    # (only when that tier runs every extension: no X above its limit, no
-    # overflow into the 128-cell tier)
+    # the batched form's first tier, when it runs every extension (no X above
+    # its limit, no overflow into a wider window)
     pp = profs.get("persistent")
-    packed = None
+    first = None
     if pp is not None and pp["to_tier2"] == 0 and int(w.x.max()) <= tuning.get("x_tier1", 32):
-        pk_ms = pp["ms_tier1"] / max(pp["batches"], 1)
-        pk_ach = OPS_PER_CELL * cells_per_step / (pk_ms / 1e3) / 1e12
-        packed = {"kernel": KERNEL_NAMES["persistent"], "ms_per_launch": round(pk_ms, 4),
-                  "kernel_gcups": round(cells_per_step / (pk_ms / 1e3) / 1e9, 2),
-                  "achieved": round(pk_ach, 3), "unit": "TOP/s",
-                  "frac_int32_peak": round(pk_ach / PEAK_INT32_TOPS, 4),
-                  "peak_packed16": round(2 * PEAK_INT32_TOPS, 3),
-                  "frac_packed16_peak": round(pk_ach / (2 * PEAK_INT32_TOPS), 4)}
+        f_ms = pp["ms_tier1"] / max(pp["batches"], 1)
+        f_ach = OPS_PER_CELL * cells_per_step / (f_ms / 1e3) / 1e12
+        first = {"kernel": KERNEL_NAMES["persistent"], "ms_per_launch": round(f_ms, 4),
+                 "kernel_gcups": round(cells_per_step / (f_ms / 1e3) / 1e9, 2),
+                 "achieved": round(f_ach, 3), "unit": "TOP/s",
+                 "frac_int32_peak": round(f_ach / PEAK_INT32_TOPS, 4)}
 
     if args.copy_calibration:
         a = torch.empty(1 << 28, dtype=torch.int32, device=dev)  # 1 GiB
@@ -318,7 +316,7 @@ def main():
         "forms": results,
         "cells_per_step": cells_per_step,
         "roofline": roofline,
-        "packed_tier": packed,
+        "first_tier": first,
         "c3": c3,
         "serving": serving,
         "cpu_baseline": cpu,
