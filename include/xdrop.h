@@ -91,7 +91,9 @@ int xd_pack_reads(const uint8_t* codes, const uint64_t* off, const uint32_t* len
                   uint32_t n_reads, uint32_t* words, uint64_t* word_off, uint64_t* n_words);
 
 /* Copies a packed read set (host pointers, store layout) to the current HIP
- * device.  The store owns its device memory until xd_store_destroy().  It is
+ * device, and lays it out there a second time in bit planes (2 bits a base too),
+ * which the lane kernels read (where the memory does not hold both, the planes
+ * and those kernels are left out).  The store owns its device memory until xd_store_destroy().  It is
  * read-only afterwards and may be used from several streams at once. */
 int xd_store_create(const uint32_t* words, uint64_t n_words, const uint64_t* word_off,
                     const uint32_t* len, uint32_t n_reads, xd_store** out);
@@ -108,7 +110,10 @@ int xd_store_info(const xd_store* store, uint64_t* device_bytes, uint32_t* n_rea
 
 /* ---- batch alignment ----------------------------------------------------- */
 
-/* Aligns n tasks, one launch sequence per call (the plain form).
+/* Aligns n tasks, one launch sequence per call (the plain form): in task order
+ * one wavefront per extension for batches of less than 3,000 tasks, else (and
+ * where x_scalar asks for a wider first window) through the device queue of
+ * the batched form with its default tuning.
  *
  * Device pointers, caller-owned, valid until the stream reaches the work:
  *   pairs  uint32[2n]  (ra, rb) per task
@@ -154,12 +159,17 @@ int xd_align_batch_noalloc(const xd_store* store, const uint32_t* pairs, const u
 /* ---- batched form: longest-first device queue, persistent waves ---------- */
 
 /* Tunables of the batched form (all 0 = default).  An autotuner picks them per
- * workload; results never depend on them. */
+ * workload; results never depend on them.  With scores 1/-1/-1 and 12,288 tasks
+ * or more, extensions with X <= 62 run one to a lane (or to a few lanes, or, the
+ * longest, one to a wavefront), whatever waves_per_cu, group_steps and the X
+ * limits say. */
 typedef struct {
   int32_t waves_per_cu; /* resident waves per CU of the persistent kernels: 4..32, default 32 */
   int32_t group_steps;  /* antidiagonals per group in the 64-cell tier: 4, 8 or 16, default 16 */
   int32_t order;        /* 1 = longest-first queue (default), 2 = task order */
-  int32_t x_tier1;      /* tasks with X <= x_tier1 start in the 64-cell window (default 32) */
+  int32_t x_tier1;      /* tasks with X <= x_tier1 start in the 64-cell window (default 32;
+                           both defaults, when neither limit is given, times
+                           (match - 2 gap) / 3, what a row off the best one costs) */
   int32_t x_tier2;      /* X <= x_tier2 start in the 128-cell window (default 80); larger X
                            start in the 256-cell window.  An extension whose band outgrows its
                            window moves to the next wider one (64, 128, 256, 512, 1024): out

@@ -451,12 +451,11 @@ __device__ __forceinline__ bool run_ext(const TaskArgs& A, uint32_t e, uint32_t*
   return true;
 }
 
-// One block per read: its bases in bit planes (lane_core.h).
+// The reads' bases in bit planes (lane_core.h), a read at a time to a workgroup
+// (at most kPlaneBlocks of them: a grid holds at most 2^32 - 1 work-items).
+constexpr uint32_t kPlaneBlocks = 65536;
+
 __global__ __launch_bounds__(256) void k_planes(StoreDev st, xd::lane::Chunk* planes) {
-  const uint32_t r = blockIdx.x;
-  const uint32_t len = st.len[r], n_words = (len + 15) / 16;
-  const uint32_t* w = st.words + st.word_off[r];
-  xd::lane::Chunk* dst = planes + st.plane_off[r];
   // every other bit of v, packed into the low half
   auto even = [](uint32_t v) -> uint32_t {
     v &= 0x55555555u;
@@ -465,9 +464,14 @@ __global__ __launch_bounds__(256) void k_planes(StoreDev st, xd::lane::Chunk* pl
     v = (v | v >> 4) & 0x00ff00ffu;
     return (v | v >> 8) & 0xffffu;
   };
-  for (uint32_t c = threadIdx.x; 32 * c < len; c += 256) {
-    const uint32_t x = w[2 * c], y = 2 * c + 1 < n_words ? w[2 * c + 1] : 0u;
-    dst[c] = xd::lane::Chunk{even(x) | even(y) << 16, even(x >> 1) | even(y >> 1) << 16};
+  for (uint64_t r = blockIdx.x; r < st.n_reads; r += gridDim.x) {
+    const uint32_t len = st.len[r], n_words = (len + 15) / 16;
+    const uint32_t* w = st.words + st.word_off[r];
+    xd::lane::Chunk* dst = planes + st.plane_off[r];
+    for (uint64_t c = threadIdx.x; 32 * c < len; c += 256) {
+      const uint32_t x = w[2 * c], y = 2 * c + 1 < n_words ? w[2 * c + 1] : 0u;
+      dst[c] = xd::lane::Chunk{even(x) | even(y) << 16, even(x >> 1) | even(y >> 1) << 16};
+    }
   }
 }
 
@@ -1725,10 +1729,10 @@ bool plain_queue(const BatchArgs& A, uint64_t n_ext, const Tuned& tu) {
   return n_ext >= kQueueMin || (!A.x && A.x_scalar > x_limit(tu, A.sc, tu.x_tier1));
 }
 
-Route batch_route(const xd::Scoring& sc, uint64_t n_ext, bool queue) {
+Route batch_route(const xd::Scoring& sc, uint64_t n_ext, bool queue, bool planes) {
   Route r = {queue, false, false, 0u};
   if (!queue) return r;
-  if (lane_ok(sc) && n_ext >= kLaneMin) r.lane_blocks = (uint32_t)device_cus();
+  if (planes && lane_ok(sc) && n_ext >= kLaneMin) r.lane_blocks = (uint32_t)device_cus();
   if (pair_ok(sc)) {
     r.solo = n_ext <= kSoloMax;
     r.packed = !r.solo;
@@ -2127,7 +2131,7 @@ int enqueue(BatchArgs A, const Scratch& S, bool persistent, const Tuned& tu,
                           hipHostMallocDefault));
     rec.n_ext = n_ext;
   }
-  const Route R = batch_route(A.sc, n_ext, persistent);
+  const Route R = batch_route(A.sc, n_ext, persistent, A.st.planes != nullptr);
   hipLaunchKernelGGL(k_reset, dim3(1), dim3(256), 0, stream, S.ctr, S.hist,
                      make_pack(A, S, R), (uint32_t*)S.targs);
   if (persistent) {
@@ -2351,12 +2355,22 @@ int xd_store_create(const uint32_t* words, uint64_t n_words, const uint64_t* wor
     e = hipMemcpy(s->word_off, word_off, n_reads * 8ull, hipMemcpyHostToDevice);
   if (e == hipSuccess && n_reads)
     e = hipMemcpy(s->len, len, n_reads * 4ull, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMalloc((void**)&s->planes, n_chunks * sizeof(xd::lane::Chunk));
-  if (e == hipSuccess) e = hipMalloc((void**)&s->plane_off, (n_reads ? n_reads : 1) * 8ull);
-  if (e == hipSuccess && n_reads)
+  if (e == hipSuccess) {
+    hipError_t pe = hipMalloc((void**)&s->planes, n_chunks * sizeof(xd::lane::Chunk));
+    if (pe == hipSuccess) pe = hipMalloc((void**)&s->plane_off, (n_reads ? n_reads : 1) * 8ull);
+    if (pe != hipSuccess) {  // no room for the planes: a store without them, and no lane tiers
+      (void)hipGetLastError();
+      (void)hipFree(s->planes);
+      s->planes = nullptr;
+      s->plane_off = nullptr;
+      s->n_chunks = 0;
+    }
+  }
+  if (e == hipSuccess && s->planes && n_reads)
     e = hipMemcpy(s->plane_off, plane_off.data(), n_reads * 8ull, hipMemcpyHostToDevice);
-  if (e == hipSuccess && n_reads) {
-    hipLaunchKernelGGL(k_planes, dim3(n_reads), dim3(256), 0, (hipStream_t) nullptr,
+  if (e == hipSuccess && s->planes && n_reads) {
+    hipLaunchKernelGGL(k_planes, dim3(std::min(n_reads, kPlaneBlocks)), dim3(256), 0,
+                       (hipStream_t) nullptr,
                        StoreDev{s->words, s->word_off, s->len, s->planes, s->plane_off, n_reads},
                        s->planes);
     e = hipGetLastError();

@@ -175,3 +175,15 @@ def test_reverse_strand_in_lanes():
     got = gpu_pairs(many, store, many["rc"], many["pairs"][:, 1], 0, 0)
     store.close()
     same(got, {k: np.asarray(v)[kept] for k, v in ref.items()}, "reverse strand")
+
+
+def test_many_reads():
+    # more reads than the planes' kernel has workgroups
+    rng = np.random.default_rng(11)
+    reads = [rand_codes(rng, int(n)) for n in rng.integers(17, 60, 70001)]
+    tasks = []
+    for q in range(600):
+        r = int(rng.integers(0, 300)) if q % 2 else 70000 - int(rng.integers(0, 5000))
+        n = len(reads[r]) - 17
+        tasks.append((r, r, int(rng.integers(0, n + 1)), int(rng.integers(0, n + 1)), 20))
+    check(workload_from(reads, tasks), LANES, label="many reads")
