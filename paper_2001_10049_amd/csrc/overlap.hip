@@ -22,6 +22,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <utility>
 #include <vector>
 
 #include "scan.h"
@@ -335,14 +336,58 @@ __global__ __launch_bounds__(kThreads) void k_retain_write(Table t, const uint64
   }
 }
 
-// one thread per retained k-mer: its seeds (ra, rb, rc << sbit | pa, pb) with
-// ra < rb.  rc = the two occurrences' strand bits differ: read rb matches the
-// reverse complement of read ra there, and pb counts in that reverse
-// complement (len[rb] - k - its position in rb).  sbit is above every
-// position, so the sort orders a pair's forward seeds before its reverse ones.
+// How the sort holds a seed (ra, rb, rc, pa, pb), most significant part first.
+// In 64 bits when the read set's ids and positions leave room (138 Mbp: 60
+// bits): half the bytes a pass (17.4 M seeds, eight passes: 1.93 -> 1.07 ms).
+struct Narrow {
+  using Item = uint64_t;
+  uint32_t bits_r, bits_s, bits_p;  // of a read id, the strand flag (0 or 1), a position
+  __device__ Item pack(uint32_t ra, uint32_t rb, uint32_t rc, uint32_t pa, uint32_t pb) const {
+    const uint64_t pair = ((uint64_t)ra << bits_r | rb) << bits_s | rc;
+    return (pair << bits_p | pa) << bits_p | pb;
+  }
+  __device__ uint64_t pair_of(Item v) const { return v >> (2 * bits_p); }
+  __device__ bool same_pair(Item a, Item b) const { return pair_of(a) == pair_of(b); }
+  __device__ uint32_t rc(Item v) const { return (uint32_t)pair_of(v) & ((1u << bits_s) - 1u); }
+  __device__ uint2 reads(Item v) const {
+    const uint64_t q = pair_of(v) >> bits_s;
+    return make_uint2((uint32_t)(q >> bits_r), (uint32_t)(q & ((1ull << bits_r) - 1ull)));
+  }
+  __device__ uint2 seed(Item v) const {
+    const uint32_t m = (1u << bits_p) - 1u;
+    return make_uint2((uint32_t)(v >> bits_p) & m, (uint32_t)v & m);
+  }
+  __device__ static uint32_t digit(Item v, int, int shift) { return (uint32_t)(v >> shift) & 255u; }
+};
+
+// In four words otherwise: ra, rb, rc << sbit | pa, pb (sbit is above every position).
+struct Wide {
+  using Item = uint4;
+  uint32_t sbit;
+  __device__ Item pack(uint32_t ra, uint32_t rb, uint32_t rc, uint32_t pa, uint32_t pb) const {
+    return make_uint4(ra, rb, rc << sbit | pa, pb);
+  }
+  __device__ bool same_pair(Item a, Item b) const {
+    return a.x == b.x && a.y == b.y && a.z >> sbit == b.z >> sbit;
+  }
+  __device__ uint32_t rc(Item v) const { return v.z >> sbit; }
+  __device__ uint2 reads(Item v) const { return make_uint2(v.x, v.y); }
+  __device__ uint2 seed(Item v) const { return make_uint2(v.z & ((1u << sbit) - 1u), v.w); }
+  __device__ static uint32_t digit(const Item& v, int field, int shift) {
+    const uint32_t f = field == 0 ? v.x : field == 1 ? v.y : field == 2 ? v.z : v.w;
+    return (f >> shift) & 255u;
+  }
+};
+
+// one thread per retained k-mer: its seeds with ra < rb.  rc = the two
+// occurrences' strand bits differ: read rb matches the reverse complement of
+// read ra there, and pb counts in that reverse complement (len[rb] - k - its
+// position in rb).  The flag is above every position, so the sort orders a
+// pair's forward seeds before its reverse ones.
+template <class F>
 __global__ __launch_bounds__(kThreads) void k_emit(Table t, const uint32_t* ret, uint64_t n_ret,
                                                    const uint64_t* pair_off, const uint32_t* len,
-                                                   int32_t k, uint32_t sbit, uint4* items) {
+                                                   int32_t k, F form, typename F::Item* items) {
   const uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
   if (i >= n_ret) return;
   const uint64_t s = ret[i];
@@ -358,28 +403,24 @@ __global__ __launch_bounds__(kThreads) void k_emit(Table t, const uint32_t* ret,
       const uint32_t rc = (lo.y ^ hi.y) >> 31;
       const uint32_t pa = lo.y & 0x7fffffffu, p_hi = hi.y & 0x7fffffffu;
       const uint32_t pb = rc ? len[hi.x] - (uint32_t)k - p_hi : p_hi;
-      items[o++] = make_uint4(lo.x, hi.x, rc << sbit | pa, pb);
+      items[o++] = form.pack(lo.x, hi.x, rc, pa, pb);
     }
   }
 }
 
-// ---- LSD radix sort of (ra, rb, pa, pb) ---------------------------------------
-
-__device__ __forceinline__ uint32_t digit_of(const uint4& v, int field, int shift) {
-  const uint32_t f = field == 0 ? v.x : field == 1 ? v.y : field == 2 ? v.z : v.w;
-  return (f >> shift) & 255u;
-}
+// ---- LSD radix sort of (ra, rb, rc, pa, pb) ---------------------------------------
 
 // hist[d * n_tiles + tile] = items of the tile with digit d
-__global__ __launch_bounds__(kThreads) void k_sort_hist(const uint4* in, uint64_t n, int field,
-                                                        int shift, uint32_t* hist) {
+template <class F>
+__global__ __launch_bounds__(kThreads) void k_sort_hist(const typename F::Item* in, uint64_t n,
+                                                        int field, int shift, uint32_t* hist) {
   __shared__ uint32_t h[256];
   h[threadIdx.x] = 0;
   __syncthreads();
   const uint64_t b0 = (uint64_t)blockIdx.x * kSortTile;
   for (int u = 0; u < kSortPer; ++u) {
     const uint64_t i = b0 + (uint64_t)u * kThreads + threadIdx.x;
-    if (i < n) atomicAdd(&h[digit_of(in[i], field, shift)], 1u);
+    if (i < n) atomicAdd(&h[F::digit(in[i], field, shift)], 1u);
   }
   __syncthreads();
   hist[(uint64_t)threadIdx.x * gridDim.x + blockIdx.x] = h[threadIdx.x];
@@ -389,8 +430,10 @@ __global__ __launch_bounds__(kThreads) void k_sort_hist(const uint4* in, uint64_
 // tile] ...] in their input order.  Each round ranks 256 items: within a wave
 // by matching digits over eight ballots, across the block's four waves by
 // per-wave digit counts in LDS.
-__global__ __launch_bounds__(kThreads) void k_sort_scatter(const uint4* in, uint4* out,
-                                                           uint64_t n, int field, int shift,
+template <class F>
+__global__ __launch_bounds__(kThreads) void k_sort_scatter(const typename F::Item* in,
+                                                           typename F::Item* out, uint64_t n,
+                                                           int field, int shift,
                                                            const uint32_t* off) {
   constexpr int kWaves = kThreads / 64;
   __shared__ uint32_t run[256];
@@ -403,8 +446,8 @@ __global__ __launch_bounds__(kThreads) void k_sort_scatter(const uint4* in, uint
   for (int u = 0; u < kSortPer; ++u) {
     const uint64_t i = b0 + (uint64_t)u * kThreads + t;
     const bool valid = i < n;
-    const uint4 v = valid ? in[i] : make_uint4(0, 0, 0, 0);
-    const uint32_t d = valid ? digit_of(v, field, shift) : 0;
+    const typename F::Item v = valid ? in[i] : typename F::Item{};
+    const uint32_t d = valid ? F::digit(v, field, shift) : 0;
     uint64_t peers = __builtin_amdgcn_ballot_w64(valid);
     for (int b = 0; b < 8; ++b) {
       const bool bit = (d >> b) & 1u;
@@ -435,32 +478,35 @@ __global__ __launch_bounds__(kThreads) void k_sort_scatter(const uint4* in, uint
 // ---- output -------------------------------------------------------------------
 
 // a new pair starts where (ra, rb, rc) changes
-__global__ __launch_bounds__(kThreads) void k_heads(const uint4* items, uint64_t n,
-                                                    uint32_t sbit, uint32_t* flag) {
+template <class F>
+__global__ __launch_bounds__(kThreads) void k_heads(const typename F::Item* items, uint64_t n,
+                                                    F form, uint32_t* flag) {
   const uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
   if (i >= n) return;
-  flag[i] = i == 0 || items[i].x != items[i - 1].x || items[i].y != items[i - 1].y ||
-            (items[i].z >> sbit) != (items[i - 1].z >> sbit);
+  flag[i] = i == 0 || !form.same_pair(items[i], items[i - 1]);
 }
 
 // head[] is the exclusive scan of the head flags (n + 1 entries); rc may be
 // null (forward strand only)
-__global__ __launch_bounds__(kThreads) void k_csr(const uint4* items, uint64_t n,
-                                                  const uint32_t* head, uint32_t sbit,
+template <class F>
+__global__ __launch_bounds__(kThreads) void k_csr(const typename F::Item* items, uint64_t n,
+                                                  const uint32_t* head, F form,
                                                   uint32_t* pairs, uint8_t* rc,
                                                   uint64_t* seed_off, uint32_t* seeds) {
   const uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
   if (i >= n) return;
-  const uint4 v = items[i];
+  const typename F::Item v = items[i];
   const uint32_t p = head[i];
   if (head[i + 1] != p) {
-    pairs[2 * (uint64_t)p] = v.x;
-    pairs[2 * (uint64_t)p + 1] = v.y;
-    if (rc) rc[p] = (uint8_t)(v.z >> sbit);
+    const uint2 r = form.reads(v);
+    pairs[2 * (uint64_t)p] = r.x;
+    pairs[2 * (uint64_t)p + 1] = r.y;
+    if (rc) rc[p] = (uint8_t)form.rc(v);
     seed_off[p] = i;
   }
-  seeds[2 * i] = v.z & ((1u << sbit) - 1u);
-  seeds[2 * i + 1] = v.w;
+  const uint2 q = form.seed(v);
+  seeds[2 * i] = q.x;
+  seeds[2 * i + 1] = q.y;
   if (i == 0) seed_off[head[n]] = n;
 }
 
@@ -503,6 +549,69 @@ uint32_t bit_length(uint64_t v) { return v ? 64u - (uint32_t)__builtin_clzll(v) 
 }  // namespace
 
 namespace {
+
+// the retained k-mers and their seeds' places
+struct Seeds {
+  Table t;
+  const uint32_t* ret;
+  const uint64_t* npair;
+  uint64_t retained, seeds;
+  const uint32_t* len;
+  int32_t k;
+};
+
+// the sort's fields, least significant first, and their bits
+struct Digits {
+  int n;
+  int field[4];
+  uint32_t bits[4];
+};
+
+// where the pairs go, when they fit (pairs null: nowhere)
+struct Csr {
+  uint64_t max_pairs, max_seeds;
+  uint32_t* pairs;
+  uint8_t* rc;
+  uint64_t* seed_off;
+  uint32_t* seeds;
+};
+
+// lists the seeds, sorts them, counts the pairs and writes them out
+template <class F>
+int sort_seeds(Arena& ar, hipStream_t st, const Seeds& in, F form, const Digits& dg,
+               const Csr& out, uint64_t* n_pairs) {
+  using Item = typename F::Item;
+  const uint64_t S = in.seeds;
+  Item *cur = nullptr, *alt = nullptr;
+  OV_TRY(ar.get(&cur, S));
+  OV_TRY(ar.get(&alt, S));
+  hipLaunchKernelGGL(k_emit<F>, dim3(grid_for(in.retained, kThreads)), dim3(kThreads), 0, st, in.t,
+                     in.ret, in.retained, in.npair, in.len, in.k, form, cur);
+  const uint32_t nt = grid_for(S, kSortTile);
+  uint32_t* hist = nullptr;
+  OV_TRY(ar.get(&hist, (uint64_t)nt * 256 + 1));
+  for (int fi = 0; fi < dg.n; ++fi)
+    for (uint32_t sh = 0; sh < dg.bits[fi]; sh += 8) {
+      hipLaunchKernelGGL(k_sort_hist<F>, dim3(nt), dim3(kThreads), 0, st, cur, S, dg.field[fi],
+                         (int)sh, hist);
+      OV_TRY(xscan::exclusive_scan<uint32_t>(ar, hist, hist, (uint64_t)nt * 256));
+      hipLaunchKernelGGL(k_sort_scatter<F>, dim3(nt), dim3(kThreads), 0, st, cur, alt, S,
+                         dg.field[fi], (int)sh, hist);
+      std::swap(cur, alt);
+    }
+  uint32_t* head = nullptr;
+  OV_TRY(ar.get(&head, S + 1));
+  hipLaunchKernelGGL(k_heads<F>, dim3(grid_for(S, kThreads)), dim3(kThreads), 0, st, cur, S, form,
+                     head);
+  OV_TRY(xscan::exclusive_scan<uint32_t>(ar, head, head, S));
+  uint32_t P = 0;
+  if (int rc = fetch(st, head + S, &P)) return rc;
+  *n_pairs = P;
+  if (out.pairs && P <= out.max_pairs && S <= out.max_seeds)
+    hipLaunchKernelGGL(k_csr<F>, dim3(grid_for(S, kThreads)), dim3(kThreads), 0, st, cur, S, head,
+                       form, out.pairs, out.rc, out.seed_off, out.seeds);
+  return XD_OK;
+}
 
 int find_overlaps(const xd_store* store, int32_t k, uint32_t m, uint32_t bloom_bits,
                   uint64_t table_slots, int32_t strands, uint64_t max_pairs, uint32_t* pairs,
@@ -652,43 +761,21 @@ int find_overlaps(const xd_store* store, int32_t k, uint32_t m, uint32_t bloom_b
     }
 
     if (cn.seeds > 0) {
-      const uint64_t S = cn.seeds;
-      uint4 *cur = nullptr, *alt = nullptr;
-      OV_TRY(ar.get(&cur, S));
-      OV_TRY(ar.get(&alt, S));
-      // positions take bits_p bits; the strand flag sits just above them
+      // read ids take bits_r bits, positions bits_p, the strand flag one
       const uint32_t bits_r = bit_length(sv.n_reads ? sv.n_reads - 1 : 0);
       const uint32_t bits_p = bit_length(sv.max_len);
-      hipLaunchKernelGGL(k_emit, dim3(grid_for(cn.retained, kThreads)), dim3(kThreads), 0, st, t,
-                         ret, cn.retained, npair, sv.len, k, bits_p, cur);
-      // keys (ra, rb, rc, pa, pb): least significant field first
-      const int fields[4] = {3, 2, 1, 0};
-      const uint32_t fbits[4] = {bits_p, bits_p + (strands == 2 ? 1u : 0u), bits_r, bits_r};
-      const uint32_t nt = grid_for(S, kSortTile);
-      uint32_t* hist = nullptr;
-      OV_TRY(ar.get(&hist, (uint64_t)nt * 256 + 1));
-      for (int fi = 0; fi < 4; ++fi)
-        for (uint32_t sh = 0; sh < fbits[fi]; sh += 8) {
-          hipLaunchKernelGGL(k_sort_hist, dim3(nt), dim3(kThreads), 0, st, cur, S, fields[fi],
-                             (int)sh, hist);
-          OV_TRY(xscan::exclusive_scan<uint32_t>(ar, hist, hist, (uint64_t)nt * 256));
-          hipLaunchKernelGGL(k_sort_scatter, dim3(nt), dim3(kThreads), 0, st, cur, alt, S,
-                             fields[fi], (int)sh, hist);
-          uint4* tmp = cur;
-          cur = alt;
-          alt = tmp;
-        }
-      uint32_t* head = nullptr;
-      OV_TRY(ar.get(&head, S + 1));
-      hipLaunchKernelGGL(k_heads, dim3(grid_for(S, kThreads)), dim3(kThreads), 0, st, cur, S,
-                         bits_p, head);
-      OV_TRY(xscan::exclusive_scan<uint32_t>(ar, head, head, S));
-      uint32_t P = 0;
-      if ((rc = fetch(st, head + S, &P))) return rc;
-      cn.pairs = P;
-      if (write && cn.pairs <= max_pairs && cn.seeds <= max_seeds)
-        hipLaunchKernelGGL(k_csr, dim3(grid_for(S, kThreads)), dim3(kThreads), 0, st, cur, S,
-                           head, bits_p, pairs, rc_out, seed_off, seeds);
+      const uint32_t bits_s = strands == 2 ? 1u : 0u;
+      const uint32_t bits = 2 * bits_r + bits_s + 2 * bits_p;
+      const Seeds in{t, ret, npair, cn.retained, cn.seeds, sv.len, k};
+      const Csr out{write ? max_pairs : 0, write ? max_seeds : 0, pairs, rc_out, seed_off, seeds};
+      if (bits <= 64) {
+        const Digits d{1, {0}, {bits}};
+        rc = sort_seeds(ar, st, in, Narrow{bits_r, bits_s, bits_p}, d, out, &cn.pairs);
+      } else {  // least significant field first
+        const Digits d{4, {3, 2, 1, 0}, {bits_p, bits_p + bits_s, bits_r, bits_r}};
+        rc = sort_seeds(ar, st, in, Wide{bits_p}, d, out, &cn.pairs);
+      }
+      if (rc) return rc;
     }
   }
   if (counts) *counts = cn;
