@@ -10,7 +10,9 @@ is full rather than on a short launch whose tail favours few waves (a
 than 24).  Per X bin the tuner picks the first window (64, 128 or
 256 cells: the X limits x_tier1 and x_tier2), per length bin the queue
 order (longest first, or task order), and beside them waves per CU, the
-antidiagonal group length and, when the slice sends any extension to the
+antidiagonal group length (of the packed and 32-bit tiers; the lane tiers,
+which take scores 1/-1/-1 with X <= 62 at this scale, use none of these but
+the order) and, when the slice sends any extension to the
 band tier, the band tier's workgroup count.  Results never depend on the
 tuning, only speed does.  The winners are cached in tuned.json next to this
 file, keyed by the device's architecture and compute-unit count (for
