@@ -67,22 +67,29 @@ __device__ __forceinline__ uint64_t bloom_word(uint64_t h, uint64_t W) {
   return ((h >> 32) * W) >> 32;
 }
 
-// Filter B is lines of kLine words (128 bytes, what a memory access moves).  A
-// k-mer's line comes from the smallest hash of its m-mers, which neighbouring
-// k-mers share three or four at a time, and the word in the line from four bits
-// of h that bloom_bits leaves: pass 2 looks kAhead k-mers up at once and so
-// waits for fewer lines (138 Mbp, k = 17: 2.73 -> 2.08 ms; 2.63 with a line for
-// every k-mer, and 2.15 and 2.47 with 8 and 16 k-mers at once).  Pass 1 gains
-// nothing from it (5.6 ms): its atomics are carried out at the memory, 26 G a
-// second, wherever they lie.  A filter that a die's L2 holds (4 MB) has nothing
-// to gain and takes the word from h alone (LINES = false): 30 Mbp, both strands,
-// 1.95 ms for the stage with lines and 1.91 without.
-constexpr uint64_t kLine = 16;
-constexpr uint64_t kLineWords = (4 << 20) / 8;  // smallest filter B with lines
+// Neighbouring k-mers share the smallest hash `mh` of their m-mers, three of them
+// or so, and the filters are laid out by it.
+//
+// Filter A: all k-mers of one mh lie in one word, so that a run of them in a
+// thread takes one atomic.  Atomics are what bounds pass 1: the counters show
+// every one carried out at the memory, 26 G a second, whatever line it lies in
+// (138 Mbp, k = 17: 149 M -> 78 M of them, 5.7 -> 3.7 ms).  Words fill less
+// evenly than by the k-mer's own hash: the m-mers have to outnumber the
+// words by eight, which keeps false repeats to 1 % of the k-mers (0.25 % by the
+// k-mer's own hash; 2.8 % with four to a word, 18 % with half a one to a word),
+// and filters of more than 2^27 words (1 GB) are too many for a 32-bit mh.
+__device__ __forceinline__ uint64_t run_word(uint32_t mh, uint64_t W) {
+  return ((uint64_t)(mh * 0x9e3779b1u) * W) >> 32;
+}
+constexpr uint64_t kRunWords = 1ull << 27;
 
-template <bool LINES>
-__device__ __forceinline__ uint64_t b_word(uint32_t mh, uint64_t h, uint64_t W) {
-  if constexpr (!LINES) return bloom_word(h, W);
+// Filter B is lines of kLine words (128 bytes, what a memory access moves): the
+// line comes from mh, the word in the line from four bits of h that bloom_bits
+// leaves.  Pass 2 looks four k-mers up at once and so waits for fewer lines
+// (2.73 -> 2.1 ms; 2.63 with a line for every k-mer).
+constexpr uint64_t kLine = 16;
+
+__device__ __forceinline__ uint64_t line_word(uint32_t mh, uint64_t h, uint64_t W) {
   const uint32_t lines = (uint32_t)(W / kLine);
   return (uint64_t)__umulhi(mh * 0x9e3779b1u, lines) * kLine + ((h >> 18) & (kLine - 1));
 }
@@ -99,12 +106,11 @@ struct KmerScan {
   int32_t k;
   uint64_t kmask;             // 2k low bits
   int32_t both;               // 1: canonical k-mers (both strands)
-  int32_t m;                  // length of the m-mers that choose a k-mer's line in B
+  int32_t m;                  // length of the m-mers that choose a k-mer's words
   uint64_t mmask;             // 2m low bits
 };
 
 constexpr int kWindow = 6;  // the m-mers of a k-mer, at most
-constexpr int kAhead = 4;   // k-mers handed over at a time
 
 // a k-mer: its code and strand, and the smallest hash of its m-mers
 struct Kmer {
@@ -114,12 +120,12 @@ struct Kmer {
 };
 
 // Calls f(read, pos, kmers, n) for the k-mer starts of chunk c in increasing
-// pos, kAhead of them at a time (n <= kAhead in the last call); code packs the k
+// pos, AHEAD of them at a time (n <= AHEAD in the last call); code packs the k
 // bases 2 bits each, the first base highest.  Forward strand only: the k-mer's
 // code, strand 0.  Both strands: the smaller of the code and its reverse
 // complement's code (the complement 3 - b of each base, in reverse order),
 // strand 1 when the reverse complement is the smaller; the m-mers likewise.
-template <bool LINES, class F>
+template <int AHEAD, class F>
 __device__ __forceinline__ void for_kmers(const KmerScan& s, uint64_t c, F&& f) {
   uint32_t lo = 0, hi = s.n_reads - 1;  // the last read whose first chunk is <= c
   while (lo < hi) {
@@ -151,7 +157,6 @@ __device__ __forceinline__ void for_kmers(const KmerScan& s, uint64_t c, F&& f) 
     rcode = (rcode >> 2) | ((3ull - b) << top);
   };
   auto add_hash = [&]() {
-    if constexpr (!LINES) return;
     uint64_t v = code & s.mmask;
     if (s.both) v = min(v, rcode >> mtop);
     for (int i = kWindow - 1; i > 0; --i) h[i] = h[i - 1];
@@ -161,18 +166,17 @@ __device__ __forceinline__ void for_kmers(const KmerScan& s, uint64_t c, F&& f) 
     add(base(p0 + q));
     if (q + 1 >= (uint32_t)s.m) add_hash();
   }
-  for (uint32_t p = p0; p < p1; p += kAhead) {
-    Kmer km[kAhead];
-    const int n = (int)min((uint32_t)kAhead, p1 - p);
-    for (int i = 0; i < kAhead; ++i) {
+  for (uint32_t p = p0; p < p1; p += AHEAD) {
+    Kmer km[AHEAD];
+    const int n = (int)min((uint32_t)AHEAD, p1 - p);
+    for (int i = 0; i < AHEAD; ++i) {
       if (i < n) {
         add(base(p + i + (uint32_t)s.k - 1));
         add_hash();
       }
       const bool flip = s.both && rcode < code;
       uint32_t mh = h[0];
-      if constexpr (LINES)
-        for (int q = 1; q < kWindow; ++q) mh = q < window ? min(mh, h[q]) : mh;
+      for (int q = 1; q < kWindow; ++q) mh = q < window ? min(mh, h[q]) : mh;
       km[i] = Kmer{flip ? rcode : code, flip ? 1u : 0u, mh};
     }
     f(r, p, km, n);
@@ -189,24 +193,38 @@ __device__ __forceinline__ void block_add(unsigned long long* dst, uint64_t v) {
 }
 
 // pass 1: filter A, repeats into filter B; ctr[0] += repeats, ctr[3] += the
-// repeats that set new bits in B (about one per distinct repeated k-mer)
-template <bool LINES>
+// repeats that set new bits in B (about one per distinct repeated k-mer).
+// RUNS: A's words by mh, the k-mers of a run with one atomic (eight at a time).
+template <bool RUNS>
 __global__ __launch_bounds__(kThreads) void k_bloom(KmerScan s, unsigned long long* A,
                                                     uint64_t WA, unsigned long long* B,
                                                     uint64_t WB, unsigned long long* ctr) {
+  constexpr int kAhead = 8;
   const uint64_t c = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
   uint32_t rep = 0, fresh = 0;
   if (c < s.n_chunks) {
-    for_kmers<LINES>(s, c, [&](uint32_t, uint32_t, const Kmer* km, int n) {
+    for_kmers<kAhead>(s, c, [&](uint32_t, uint32_t, const Kmer* km, int n) {
+      // each k-mer's bits, with those of the run's k-mers after it, and what the
+      // word held before it
+      unsigned long long bits[kAhead], all[kAhead], old[kAhead];
+      uint64_t word[kAhead];
+      for (int q = 0; q < kAhead; ++q) {
+        const uint64_t h = fmix64(km[q].code);
+        bits[q] = q < n ? bloom_bits(h) : 0ull;
+        word[q] = RUNS ? run_word(km[q].mh, WA) : bloom_word(h, WA);
+      }
+      auto first = [&](int q) { return !RUNS || q == 0 || km[q].mh != km[q - 1].mh; };
+      for (int q = kAhead - 1; q >= 0; --q)
+        all[q] = bits[q] | (q + 1 < kAhead && !first(q + 1) ? all[q + 1] : 0ull);
+      for (int q = 0; q < kAhead; ++q)
+        if (q < n && first(q)) old[q] = atomicOr(&A[word[q]], all[q]);
       for (int q = 0; q < kAhead; ++q) {
         if (q >= n) break;
-        const uint64_t h = fmix64(km[q].code);
-        const unsigned long long bits = bloom_bits(h);
-        const unsigned long long old = atomicOr(&A[bloom_word(h, WA)], bits);
-        if ((old & bits) == bits) {
+        if (!first(q)) old[q] = old[q - 1] | bits[q - 1];
+        if ((old[q] & bits[q]) == bits[q]) {
           const uint64_t h2 = fmix64(km[q].code ^ kSaltB);
           const unsigned long long b2 = bloom_bits(h2);
-          const unsigned long long old2 = atomicOr(&B[b_word<LINES>(km[q].mh, h2, WB)], b2);
+          const unsigned long long old2 = atomicOr(&B[line_word(km[q].mh, h2, WB)], b2);
           ++rep;
           fresh += (old2 & b2) != b2;
         }
@@ -237,18 +255,18 @@ struct Table {
 
 // pass 2: the k-mers in B into the table; ctr[2] = 1 when a key found no slot
 // within kMaxProbe probes (the host then doubles the table and reruns the pass)
-template <bool LINES>
 __global__ __launch_bounds__(kThreads) void k_table(KmerScan s, const unsigned long long* B,
                                                     uint64_t WB, Table t,
                                                     unsigned long long* ctr) {
   const uint64_t c = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
   if (c >= s.n_chunks) return;
-  for_kmers<LINES>(s, c, [&](uint32_t r, uint32_t p, const Kmer* km, int n) {
+  constexpr int kAhead = 4;
+  for_kmers<kAhead>(s, c, [&](uint32_t r, uint32_t p, const Kmer* km, int n) {
     unsigned long long bits[kAhead], have[kAhead];
     for (int q = 0; q < kAhead; ++q) {
       const uint64_t h2 = fmix64(km[q].code ^ kSaltB);
       bits[q] = bloom_bits(h2);
-      have[q] = B[b_word<LINES>(km[q].mh, h2, WB)];
+      have[q] = B[line_word(km[q].mh, h2, WB)];
     }
     for (int q = 0; q < kAhead; ++q) {
       if (q >= n || (have[q] & bits[q]) != bits[q]) continue;
@@ -676,13 +694,16 @@ int find_overlaps(const xd_store* store, int32_t k, uint32_t m, uint32_t bloom_b
     OV_TRY(hipMemsetAsync(A, 0, WA * 8, st));
     OV_TRY(hipMemsetAsync(B, 0, WB * 8, st));
     OV_TRY(hipMemsetAsync(ctr, 0, 4 * 8, st));
-    // up to kWindow m-mers to a k-mer, none shorter than 11 bases
-    const int32_t mm = std::min(k, std::max(k - kWindow + 1, 11));
+    // up to kWindow m-mers to a k-mer, and eight of them to a word of A where its
+    // words go by them
+    const bool runs = WA <= kRunWords;
+    int32_t mm = runs ? 1 : 11;
+    while (runs && mm < 16 && (1ull << (2 * mm)) < 8 * WA) ++mm;
+    mm = std::min(k, std::max(k - kWindow + 1, mm));
     KmerScan ks{sv.words, sv.word_off, sv.len, d_chunk, n_chunks, sv.n_reads, k,
                 k == 32 ? ~0ull : (1ull << (2 * k)) - 1, strands == 2 ? 1 : 0, mm,
                 mm == 32 ? ~0ull : (1ull << (2 * mm)) - 1};
-    const bool in_lines = WB >= kLineWords;
-    hipLaunchKernelGGL(in_lines ? k_bloom<true> : k_bloom<false>,
+    hipLaunchKernelGGL(runs ? k_bloom<true> : k_bloom<false>,
                        dim3(grid_for(n_chunks, kThreads)), dim3(kThreads), 0, st, ks, A, WA, B, WB,
                        ctr);
     hipLaunchKernelGGL(k_popcount, dim3(grid_for(WB, kThreads * 16)), dim3(kThreads), 0, st, B,
@@ -716,8 +737,7 @@ int find_overlaps(const xd_store* store, int32_t k, uint32_t m, uint32_t bloom_b
       OV_TRY(hipMemsetAsync(t.keys, 0, cap * 8, st));
       OV_TRY(hipMemsetAsync(t.cnt, 0, cap * 4, st));
       OV_TRY(hipMemsetAsync(ctr + 2, 0, 8, st));
-      hipLaunchKernelGGL(in_lines ? k_table<true> : k_table<false>,
-                         dim3(grid_for(n_chunks, kThreads)), dim3(kThreads), 0, st, ks, B, WB, t,
+      hipLaunchKernelGGL(k_table, dim3(grid_for(n_chunks, kThreads)), dim3(kThreads), 0, st, ks, B, WB, t,
                          ctr);
       unsigned long long full = 0;
       if ((rc = fetch(st, ctr + 2, &full))) return rc;

@@ -1,8 +1,7 @@
-"""The second filter's two layouts: word by word, and in lines shared by
-neighbouring k-mers (from 4 MB on, here by 64 filter bits a k-mer).  A filter
-only decides which k-mers are counted, so every k, from one m-mer to a k-mer up
-to six, and both strands have to give the same result in each; the first is the
-one that the oracle checks at these sizes."""
+"""The filters' layouts by the k-mers' smallest m-mers: a filter only decides
+which k-mers are counted, so every k, from one m-mer to a k-mer up to six, both
+strands and every filter size have to give the same result; past 2^27 words the
+first filter goes by the k-mers themselves."""
 import numpy as np
 import pytest
 
@@ -15,6 +14,7 @@ if not torch.cuda.is_available():  # pragma: no cover
     pytest.skip("no GPU", allow_module_level=True)
 
 import paper_2001_10049_amd as xd  # noqa: E402
+import synth  # noqa: E402
 
 
 @pytest.fixture(scope="module")
@@ -51,3 +51,16 @@ def test_layouts_agree(store, k, strands):
     assert out[0]["counts"]["kmers"] * 64 >= 8 * (4 << 20) * 16
     if k >= 15:
         assert out[0]["counts"]["pairs"] > 100
+
+
+def test_large_filter():
+    w = synth.config("c2", n_tasks=1)
+    with xd.ReadStore.from_workload(w) as st:
+        out = [xd.find_overlaps(st, k=17, m=8, bloom_bits=b) for b in (16, 64)]
+        torch.cuda.synchronize()
+    assert out[1]["counts"]["kmers"] > 1 << 27  # a word for each at 64 bits
+    for key in ("pairs", "seed_off", "seeds"):
+        assert torch.equal(out[0][key], out[1][key]), key
+    for key in ("non_singletons", "retained", "occurrences"):
+        assert out[0]["counts"][key] == out[1]["counts"][key], key
+    assert out[0]["counts"]["pairs"] == 803126
