@@ -4,7 +4,8 @@
 // xd_align_pairs consumes.
 //
 // Pass 1 streams every k-mer through a blocked Bloom filter A (one 64-bit word
-// and three bits per k-mer, set with one atomic OR).  An occurrence that finds
+// and three bits per k-mer; neighbours that share a word set theirs with one
+// atomic OR).  An occurrence that finds
 // all its bits already set is a repeat (or a false positive) and marks the
 // k-mer in a second, smaller filter B, so every k-mer occurring twice or more
 // is in B while most singletons never reach it (section 6).  Pass 2 streams
@@ -694,11 +695,12 @@ int find_overlaps(const xd_store* store, int32_t k, uint32_t m, uint32_t bloom_b
     OV_TRY(hipMemsetAsync(A, 0, WA * 8, st));
     OV_TRY(hipMemsetAsync(B, 0, WB * 8, st));
     OV_TRY(hipMemsetAsync(ctr, 0, 4 * 8, st));
-    // up to kWindow m-mers to a k-mer, and eight of them to a word of A where its
-    // words go by them
+    // up to kWindow m-mers to a k-mer, and eight to a word of the filters that go
+    // by them (3.0 Gbp, where that is B alone: 626 ms with a third of one to a
+    // word of B, 611 so, 608 by the k-mer's own hash)
     const bool runs = WA <= kRunWords;
-    int32_t mm = runs ? 1 : 11;
-    while (runs && mm < 16 && (1ull << (2 * mm)) < 8 * WA) ++mm;
+    int32_t mm = 1;
+    while (mm < 16 && (1ull << (2 * mm)) < 8 * (runs ? WA : WB)) ++mm;
     mm = std::min(k, std::max(k - kWindow + 1, mm));
     KmerScan ks{sv.words, sv.word_off, sv.len, d_chunk, n_chunks, sv.n_reads, k,
                 k == 32 ? ~0ull : (1ull << (2 * k)) - 1, strands == 2 ? 1 : 0, mm,
