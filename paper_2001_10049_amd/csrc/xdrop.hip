@@ -46,6 +46,7 @@
 #include "band_pair.h"
 #include "xdrop_device.h"
 #include "lane_device.h"
+#include "lane_share.h"
 #include "pair2_device.h"
 #include "pair4_device.h"
 #include "pair_device.h"
@@ -95,11 +96,7 @@ namespace {
 
 constexpr uint32_t kWideBlocks = 2048;
 constexpr uint64_t kChunkBlocks = 1ull << 24;  // one-wave blocks per launch of a per-item grid
-// queue classes (ext_key), 73 length bins each, in 512 bins (the last class
-// is the invalid tasks', whose length does not matter)
-constexpr int kCostBins = 73;
-constexpr int kBins = 512;
-enum { kClsNarrow = 0, kClsLane, kCls64, kClsWide, kCls128, kCls256, kClsInvalid };
+using namespace xd::queue;  // classes, bins and segments of the batched form's queue
 constexpr int kBandWaves = 16;          // waves per band-tier workgroup
 constexpr uint32_t kBandBlocksMax = 16;
 constexpr uint64_t kBandBudget = 64ull << 20;  // default band area per batch
@@ -191,8 +188,8 @@ struct Scratch {
 // ctr layout
 constexpr int kOvfCount = 0;   // [0..4] sizes of ovf[0..4]
 constexpr int kHead = 5;       // [5..9] work heads of tiers 0..4
-constexpr int kSeg = 10;       // [10..20] queue starts of the segments (k_bin_scan), then 2n
-                               // and [21..22] the workgroups of split extensions
+constexpr int kSeg = 10;       // [10..22] queue starts of the segments, then 2n, and the
+                               // workgroups of split extensions (k_bin_scan)
 constexpr int kBandHead = 23;  // work head of the band tier
 constexpr int kResumed = 24;   // [24..27] moves out of windows 0..3 that carried their state
 constexpr int kSegHead1 = 28;  // work head of the 128-cell window's queue segment (batched form)
@@ -200,13 +197,7 @@ constexpr int kLaneOvf = 29;   // [29..32] sizes of the lane tiers' lists 0..3
 constexpr int kLaneHead = 33;  // [33..41] work heads of tiers kTLane on
 constexpr int kLaneResumed = kLaneOvf + kResumed;  // [53..56] as kResumed, out of lane tiers
 constexpr int kCtrWords = 64;
-// queue segments, in queue order (with lane tiers kSeg64 holds the
-// extensions of the narrow and the 64-row class that run one per wavefront
-// and kSegLong those of the 96-row class; kSegSplit and kSegWideSplit those
-// that run in several lanes each)
-enum { kSeg64 = 0, kSegSplit, kSegLane, kSegNarrow, kSegLong, kSegWideSplit, kSegWide, kSeg128,
-       kSeg256, kSegInvalid, kSegEnd };
-static_assert(kSeg + kSegEnd + 2 < kBandHead && kLaneResumed + 4 <= kCtrWords, "counters");
+static_assert(kSeg + kSegWords <= kBandHead && kLaneResumed + 4 <= kCtrWords, "counters");
 constexpr int kTierArgsBytes = 8 * 256;  // >= sizeof(TierPack), checked below
 constexpr uint64_t kFixedBytes = (kBins * 4 + kCtrWords * 4 + kTierArgsBytes + 255) & ~255ull;
 
@@ -795,7 +786,7 @@ struct LaneWork {
 // The lane tiers (xd::lane, W * 32 rows).  The first cus workgroups, one to a
 // CU, run one extension per lane or (W >= 2, the last *split of them) one in
 // two or four lanes; the others the longest ones, one per wavefront.  Which
-// extension runs how: see split_time.
+// extension runs how: see xd::queue::split_time.
 // Bound by vector issue: 127 instructions a step for 64 extensions of 64 rows
 // (P = 6), 65 for 32 rows (P = 5), 207 for 96 rows (P = 7), 87 for 32 extensions
 // of 64 rows in two lanes each, against 6.2 a step and extension in the packed
@@ -889,52 +880,19 @@ __global__ __launch_bounds__(64 * kBandWaves) void k_ext_band(const TaskArgs* __
 
 // ---- queue: tier-major, longest first ------------------------------------
 
-struct BinRule {
-  int32_t x_tier1, x_tier2;  // X limits of the 64- and 128-cell first tiers
-  int32_t by_cost;           // 0: keep task order inside a tier
-  uint32_t lanes;            // workgroups of a lane tier's launch, one per CU (0: no lane tiers)
-};
-
-// Length bin of an estimated antidiagonal count, 6 per octave from 64 on.
-__device__ __forceinline__ uint32_t cost_bin(uint32_t cost) {
-  if (cost < 64u) return 0u;
-  const uint32_t ex = 31u - __builtin_clz(cost);
-  const uint32_t sub = (((cost >> (ex - 3)) & 7u) * 6u) >> 3;
-  return min(1u + (ex - 6u) * 6u + sub, (uint32_t)kCostBins - 1u);
-}
-// the middle and the end of a length bin
-__device__ __forceinline__ float bin_cost(uint32_t cb) {
-  if (cb == 0) return 32.f;
-  const uint32_t ex = (cb - 1) / 6, sub = (cb - 1) % 6;  // (sub: 2, 1, 1, 2, 1, 1 eighths)
-  return (float)(4u << ex) * (float)((0x1f1d1a171512ull >> (8 * sub)) & 255u);
-}
-__device__ __forceinline__ float bin_end(uint32_t cb) {
-  if (cb == 0) return 64.f;
-  const uint32_t ex = (cb - 1) / 6, sub = (cb - 1) % 6;
-  return (float)(4u << ex) * (float)((0x201e1c181614ull >> (8 * sub)) & 255u);
-}
-
-// Sort key of extension e: class from X (its first tier), then the length
-// bin of the estimated antidiagonal count (a true overlap extends along the
-// diagonal until the shorter side runs out, about 2*min(m, n)
-// antidiagonals), longest first.  k_bin_scan places the keys in the queue;
-// invalid tasks sort last, into a segment that is never run.
+// Sort key of extension e (bin_key): a true overlap extends along the diagonal
+// until the shorter side runs out, about 2*min(m, n) antidiagonals.
+// k_bin_scan places the keys in the queue; invalid tasks sort last, into a
+// segment that is never run.
 __device__ __forceinline__ uint32_t ext_key(const TaskArgs& A, const BinRule& R, uint32_t e) {
   uint32_t ra, rb, pa, pb;
   int32_t X;
   // invalid tasks go to the last segment, which no tier runs: the combine
   // writes their status without reading extension results
   if (task_status(A, e >> 1, ra, rb, pa, pb, X) != XD_TASK_OK) return kBins - 1;
-  uint32_t cls = X <= R.x_tier1 ? kCls64 : X <= R.x_tier2 ? kCls128 : kCls256;
-  if (R.lanes && X <= xd::lane::x_limit(7))  // the planes a lane needs
-    cls = X <= xd::lane::x_limit(5) ? kClsNarrow : X <= xd::lane::x_limit(6) ? kClsLane : kClsWide;
-  else if (R.lanes && cls == kCls64)
-    cls = kCls128;
-  if (!R.by_cost) return cls * kCostBins;
   int32_t m, n;
   ext_lengths(A, e, pa, pb, (int32_t)A.st.len[ra], (int32_t)A.st.len[rb], m, n);
-  const uint32_t cb = cost_bin(2u * (uint32_t)min(m, n) + 2u);
-  return cls * kCostBins + (kCostBins - 1 - cb);
+  return bin_key(R, X, 2u * (uint32_t)min(m, n) + 2u);
 }
 
 __global__ __launch_bounds__(256) void k_bin_hist(BatchArgs A, BinRule R, uint32_t n_ext,
@@ -949,67 +907,10 @@ __global__ __launch_bounds__(256) void k_bin_hist(BatchArgs A, BinRule R, uint32
     if (h[b]) atomicAdd(&hist[b], h[b]);
 }
 
-// How a lane class's extensions are shared out: the longest run one per
-// wavefront, the next in several lanes each, the rest in one lane, because
-// the fewer share a wavefront the sooner a step is done and the more
-// instructions it costs.  A CU runs one workgroup of single lanes or of split
-// extensions, and the wavefronts of the longest beside it, ahead of it in
-// priority.  In issue slots of a SIMD (vector instructions):
-struct LaneCost {
-  float lane_step, split_step, solo_step;  // from one step of an extension to the next
-  float solo;                              // one step's share of the instructions
-  uint32_t split_group;                    // split extensions a workgroup holds
-};
-__device__ __forceinline__ LaneCost lane_cost(uint32_t cls) {
-  return cls == kClsNarrow ? LaneCost{82.f, 120.f, 25.f, 12.f, 128u}
-         : cls == kClsLane ? LaneCost{160.f, 120.f, 25.f, 12.f, 128u}
-                           : LaneCost{260.f, 130.f, 45.f, 20.f, 64u};
-}
-
-// What split_time reads of a class: for each length bin, longest first, the
-// first bin from it on that is not empty, and the steps and extensions of the
-// bins before it.
-struct ClassBins {
-  uint32_t next[kCostBins + 1], before[kCostBins + 1];
-  float sum[kCostBins + 1];
-};
-
-// Estimated end of a class whose first s1 length bins run alone and whose next
-// s2 - s1 run split, and the workgroups the latter get of cus: as many as
-// hold those longer than half the longest at once, and make the average load
-// no more than the longest one's.
-__device__ __forceinline__ float split_time(const ClassBins& x, uint32_t s1, uint32_t s2,
-                                            const LaneCost& c, float cus, float& groups) {
-  constexpr uint32_t N = kCostBins;
-  auto longest = [&](uint32_t from, uint32_t to) -> float {
-    const uint32_t q = x.next[from];
-    return q < to ? bin_end(N - 1 - q) : 0.f;
-  };
-  const float solo = x.sum[s1] * c.solo / (4.f * cus), split = x.sum[s2] - x.sum[s1],
-              rest = x.sum[N] - x.sum[s2];
-  const float l0 = longest(0, s1), l1 = longest(s1, s2), l2 = longest(s2, N);
-  // (six bins an octave)
-  const uint32_t half = min(s2, x.next[s1] + 6u);
-  groups = split > 0.f ? fminf(ceilf(fmaxf(split / l1, (float)(x.before[half] - x.before[s1])) /
-                                     (float)c.split_group), cus - 1.f)
-                       : 0.f;
-  const float t1 = split > 0.f ? fmaxf(l1, split / (groups * (float)c.split_group)) : 0.f;
-  const float t2 = fmaxf(l2, rest / (256.f * (cus - groups)));
-  return fmaxf(l0 * c.solo_step, fmaxf(t1 * c.split_step, t2 * c.lane_step) + solo);
-}
-
-// hist[b] <- queue start of key b; seg[t] <- queue start of segment t
-// (seg[kSegEnd] = n_ext); then the workgroups of split extensions beside the
-// 64- and the 96-row class.
-//
-// The narrow class's lanes run after the 64-row class's, in a launch of their
-// own; when that would take longer than running them all in 64 rows (two
-// chains of steps instead of one), the two are one class.  32,000 pairs at X
-// of 7 and 25: 4.0 ms against 5.8.
+// hist[b] <- queue start of key b; seg <- the segments (xd::queue), each lane
+// class shared out by the best of its candidates.
 __global__ __launch_bounds__(512) void k_bin_scan(uint32_t* hist, uint32_t* seg, BinRule R,
                                                   uint32_t n_ext) {
-  constexpr uint32_t N = kCostBins;
-  constexpr int kKinds = 4;  // narrow, 64 rows, 96 rows, the first two as one
   __shared__ uint32_t h[kBins];
   __shared__ ClassBins x[kKinds];
   __shared__ unsigned long long best[kKinds];
@@ -1018,77 +919,27 @@ __global__ __launch_bounds__(512) void k_bin_scan(uint32_t* hist, uint32_t* seg,
   h[b] = mine;
   if (b < kKinds) best[b] = ~0ull;
   __syncthreads();
-  // the lane classes' shares: bins [0, alone), [alone, split) and the rest
-  uint32_t alone[kKinds] = {0, 0, 0, 0}, split[kKinds] = {0, 0, 0, 0};
-  float groups[kKinds] = {0.f, 0.f, 0.f, 0.f}, t[kKinds] = {0.f, 0.f, 0.f, 0.f};
-  const uint32_t cls_of[kKinds] = {kClsNarrow, kClsLane, kClsWide, kClsLane};
+  Shares S;
   if (R.lanes) {
-    if (b < kKinds) {
-      float v = 0.f;
-      uint32_t n = 0, nx = N;
-      const uint32_t* c = h + cls_of[b] * N;
-      const uint32_t* c2 = h + kClsNarrow * N;
-      auto count = [&](uint32_t q) { return c[q] + (b == 3 ? c2[q] : 0u); };
-      for (uint32_t q = 0; q < N; ++q) {
-        x[b].sum[q] = v;
-        x[b].before[q] = n;
-        n += count(q);
-        v += (float)count(q) * bin_cost(N - 1 - q);
-      }
-      x[b].sum[N] = v;
-      x[b].before[N] = n;
-      x[b].next[N] = N;
-      for (uint32_t q = N; q-- > 0;) {
-        if (count(q)) nx = q;
-        x[b].next[q] = nx;
-      }
-    }
+    if (b < kKinds) class_bins(h, (int)b, x[b]);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kKinds; ++k) {
-      if (x[k].sum[N] == 0.f) continue;
-      const LaneCost c = lane_cost(cls_of[k]);
+      if (!x[k].before[kCostBins]) continue;
       unsigned long long m = ~0ull;
-      for (uint32_t q = b; q < (N + 1) * (N + 1); q += kBins) {
-        const uint32_t s1 = q / (N + 1), s2 = q % (N + 1);
-        if (s1 > s2) continue;
-        float g;
-        const float e = split_time(x[k], s1, s2, c, (float)R.lanes, g);
-        const unsigned long long v = (unsigned long long)__float_as_uint(e) << 32 | q;
+      for (uint32_t q = b; q < kCandidates; q += kBins) {
+        const unsigned long long v = share_rank(x[k], k, q, R.lanes);
         m = v < m ? v : m;
       }
       atomicMin(&best[k], m);
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < kKinds; ++k) {
-      if (x[k].sum[N] == 0.f) continue;
-      const uint32_t q = (uint32_t)best[k];
-      alone[k] = q / (N + 1);
-      split[k] = q % (N + 1);
-      t[k] = split_time(x[k], alone[k], split[k], lane_cost(cls_of[k]), (float)R.lanes, groups[k]);
-    }
+    for (int k = 0; k < kKinds; ++k)
+      if (x[k].before[kCostBins]) S.choose(x[k], k, best[k], R.lanes);
   }
-  const bool merged = t[0] > 0.f && t[1] > 0.f && t[3] < t[0] + t[1];
-  if (b == 0) {
-    seg[kSegEnd + 1] =
-        (uint32_t)(merged ? groups[3] : fminf(groups[0] + groups[1], (float)R.lanes - 1.f));
-    seg[kSegEnd + 2] = (uint32_t)groups[2];
-  }
-  // the bins in queue order
-  const uint32_t s0 = alone[0], s1 = alone[1], s2 = alone[2];
-  const uint32_t t0 = split[0], t1 = split[1], t2 = split[2];
-  const uint32_t cls = min(b / N, (uint32_t)kClsInvalid), q = b - cls * N;
-  uint32_t at = b;  // the classes from 256 cells on keep their place
-  if (cls == kCls64) at = q;
-  else if (merged && (cls == kClsLane || cls == kClsNarrow))
-    at = N + 2 * q + (cls == kClsNarrow ? 1u : 0u);
-  else if (cls == kClsLane)
-    at = q < s1 ? N + q : q < t1 ? N + s1 + s0 + (q - s1) : N + t1 + t0 + (q - t1);
-  else if (cls == kClsNarrow)
-    at = q < s0 ? N + s1 + q : q < t0 ? N + t1 + s0 + (q - s0) : 2 * N + t0 + (q - t0);
-  else if (cls == kClsWide) at = 3 * N + q;  // (its longest come first already)
-  else if (cls == kCls128) at = 4 * N + q;
+  const bool merged = S.merged();
+  const uint32_t at = slot_of(b, S, merged);
   __syncthreads();
   h[at] = mine;
   __syncthreads();
@@ -1102,20 +953,9 @@ __global__ __launch_bounds__(512) void k_bin_scan(uint32_t* hist, uint32_t* seg,
     __syncthreads();
   }
   hist[b] = h[at] - mine;
-  auto start = [&](uint32_t slot) { return slot ? h[slot - 1] : 0u; };
-  if (b == 0) {
-    seg[kSeg64] = 0;
-    seg[kSegSplit] = start(merged ? N + 2 * alone[3] : N + s1 + s0);
-    seg[kSegLane] = start(merged ? N + 2 * split[3] : N + t1 + t0);
-    seg[kSegNarrow] = start(merged ? 3 * N : 2 * N + t0);
-    seg[kSegLong] = start(3 * N);
-    seg[kSegWideSplit] = start(3 * N + s2);
-    seg[kSegWide] = start(3 * N + t2);
-    seg[kSeg128] = start(4 * N);
-    seg[kSeg256] = start(5 * N);
-    seg[kSegInvalid] = start(6 * N);
-    seg[kSegEnd] = n_ext;
-  }
+  if (b == 0)
+    segments(S, merged, n_ext, R.lanes, [&](uint32_t slot) { return slot ? h[slot - 1] : 0u; },
+             seg);
 }
 
 // Each block places kScatterItems extensions: it counts its keys in LDS,
@@ -1836,7 +1676,7 @@ void launch_wide(const Scratch& S, uint32_t blocks, hipStream_t stream, const Ro
   if (R.lane_blocks) {
     const uint32_t n = R.lane_blocks;
     hipLaunchKernelGGL((k_lane_tier<7, 3>), dim3(3 * n), dim3(256), 0, stream, ga, ta + kTWide,
-                       ta + kTWideSplit, ta + kTSeg128, S.ctr + kSeg + kSegEnd + 2, n);
+                       ta + kTWideSplit, ta + kTSeg128, S.ctr + kSeg + kWideSplitBlocks, n);
     hipLaunchKernelGGL((k_lane_list<4>), dim3(4 * n), dim3(256), 0, stream, ga, ta + kTL128);
     hipLaunchKernelGGL((k_lane_list<8>), dim3(4 * n), dim3(256), 0, stream, ga, ta + kTL256);
     hipLaunchKernelGGL((k_lane_list<16>), dim3(4 * n), dim3(256), 0, stream, ga, ta + kTL512);
@@ -1874,9 +1714,9 @@ void launch_lane(const Scratch& S, uint32_t n, hipStream_t stream) {
   const TaskArgs* ga = &S.targs->A;
   const TierArgs* ta = S.targs->t;
   hipLaunchKernelGGL((k_lane_tier<6, 2>), dim3(4 * n), dim3(256), 0, stream, ga, ta + kTLane,
-                     ta + kTSplit, ta + kT64, S.ctr + kSeg + kSegEnd + 1, n);
+                     ta + kTSplit, ta + kT64, S.ctr + kSeg + kSplitBlocks, n);
   hipLaunchKernelGGL((k_lane_tier<5, 1>), dim3(n), dim3(256), 0, stream, ga, ta + kTNarrow,
-                     ta + kTNarrow, ta + kT64, S.ctr + kSeg + kSegEnd + 1, n);
+                     ta + kTNarrow, ta + kT64, S.ctr + kSeg + kSplitBlocks, n);
 }
 
 template <bool UNIT>

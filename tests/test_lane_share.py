@@ -1,0 +1,49 @@
+"""The sharing of the batched form's queue on the CPU: every extension lies in
+one segment, and a segment that holds any has workgroups that open it."""
+import numpy as np
+import pytest
+
+import share
+
+
+def check(x, cost, **kw):
+    s = share.segments(x, cost, **kw)
+    cus = kw.get("cus", 256)
+    assert sum(s[n] for n in share.NAMES) == len(x), s
+    for seg, rest, blocks in (("split", "lane", "split_blocks"),
+                              ("wide_split", "wide", "wide_split_blocks")):
+        if s[seg]:
+            assert 1 <= s[blocks] < cus, s
+        assert s[blocks] < max(cus, 1), s
+    return s
+
+
+@pytest.mark.parametrize("X", [7, 25, 50])
+@pytest.mark.parametrize("n,steps,short", [(4000, 200_000, 50), (6000, 100_000, 50),
+                                           (30_000, 250_000, 10), (4000, 200_000, 300)])
+def test_many_long_and_one_short(X, n, steps, short):
+    # the short one's steps are lost in a float32 sum of the long ones'
+    check(np.full(n + 1, X), np.r_[np.full(n, steps), short])
+
+
+@pytest.mark.parametrize("cus", [1, 2, 3, 32, 256])
+def test_random_batches(cus):
+    rng = np.random.default_rng(cus)
+    for _ in range(120):
+        x, cost = [], []
+        for _ in range(int(rng.integers(1, 5))):  # groups of like extensions
+            n = int(2 ** rng.uniform(0, 15))
+            x.append(np.full(n, rng.choice([0, 7, 14, 15, 25, 30, 31, 50, 62, 63, 200, -1])))
+            cost.append(np.full(n, int(2 ** rng.uniform(1, 23))))
+        check(np.concatenate(x), np.concatenate(cost), cus=cus, by_cost=int(rng.integers(2)))
+
+
+def test_one_workgroup_splits_nothing():
+    s = check(np.full(5000, 50), np.full(5000, 20_000), cus=1)
+    assert s["split"] == s["wide_split"] == 0, s
+
+
+def test_no_lane_tiers():
+    x = np.resize([7, 25, 33, 80, 81, 5000, -1], 7000)
+    s = check(x, np.full(7000, 5000), cus=0)
+    assert (s["solo"], s["first128"], s["first256"], s["invalid"]) == (2000, 2000, 2000, 1000), s
