@@ -210,7 +210,7 @@ XD_HD void gather(const Chunk* read, int32_t n_chunks, int32_t first, bool up,
 constexpr int kStatePlanes = 7;
 struct StateHead {
   int32_t d, base, thr, bi, dstar;
-  uint32_t cells, words, pad;
+  uint32_t cells, words, cells_high;
 };
 struct StateWord {
   uint32_t U[kStatePlanes], D[kStatePlanes], L, LD;
@@ -219,6 +219,19 @@ constexpr uint32_t state_bytes(int words) {
   return (uint32_t)(sizeof(StateHead) + words * sizeof(StateWord));
 }
 static_assert(sizeof(StateHead) == 32 && sizeof(StateWord) == 64, "state layout");
+
+// Evaluated cells: a lane counts its own in 32 bits (at most 96 rows of 2^23
+// antidiagonals), an extension's need 33 in 1,024 rows.  A resumed extension's
+// count is spread over its S lanes, lane s's part being count_part, and a
+// group's is the sum of its lanes' halves (count_of).
+template <int S>
+XD_HD uint32_t count_part(const StateHead& h, int s) {
+  const uint64_t cells = (uint64_t)h.cells_high << 32 | h.cells;
+  return (uint32_t)(cells / S) + (s == 0 ? (uint32_t)(cells % S) : 0u);
+}
+XD_HD uint64_t count_of(uint32_t low_sum, uint32_t high_sum) {
+  return ((uint64_t)high_sum << 16) + low_sum;
+}
 
 // ---- one extension ---------------------------------------------------------------
 

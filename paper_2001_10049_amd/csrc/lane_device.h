@@ -96,14 +96,16 @@ __device__ __forceinline__ void run(Work& wk, uint32_t* lds, const Chunk* planes
     bool fresh = false;
     const uint64_t leave = ballot64(ended || wide);
     if (leave | (more ? ballot64(!active) : 0ull)) {
-      const int32_t cells = over_group<S>((int32_t)c.cnt, [](int32_t a, int32_t b) { return a + b; });
+      auto add = [](int32_t a, int32_t b) { return a + b; };
+      const uint64_t cells = count_of((uint32_t)over_group<S>((int32_t)(c.cnt & 0xffffu), add),
+                                      (uint32_t)over_group<S>((int32_t)(c.cnt >> 16), add));
       if (ended && first) {
         ExtOut o;
         o.best = c.thr - (d + 1);
         o.bi = bi;
         o.bj = dstar - bi;
         o.flags = kExtDone;
-        o.cells = (uint32_t)cells;
+        o.cells = cells;
         wk.done(it.e, o);
       }
       if (ballot64(wide)) {
@@ -118,7 +120,8 @@ __device__ __forceinline__ void run(Work& wk, uint32_t* lds, const Chunk* planes
         if (wide && dst) {
           c.save_words(s, (uint8_t*)dst);
           if (first) {
-            StateHead h = {d, base, c.thr, bi, dstar, (uint32_t)cells, (uint32_t)(S * W), 0u};
+            StateHead h = {d, base, c.thr, bi, dstar, (uint32_t)cells, (uint32_t)(S * W),
+                           (uint32_t)(cells >> 32)};
             *(StateHead*)dst = h;
           }
         }
@@ -200,7 +203,7 @@ __device__ __forceinline__ void run(Work& wk, uint32_t* lds, const Chunk* planes
             bi = h.bi;
             dstar = h.dstar;
             c.thr = h.thr;
-            c.cnt = first ? h.cells : 0u;
+            c.cnt = count_part<S>(h, s);
           }
           active = fresh = true;
           if constexpr (S == 1 && !Work::kResumes) {

@@ -385,7 +385,7 @@ __device__ __forceinline__ void write_planes(const uint32_t* ring, uint8_t* dst)
   }
   if (lane == 0) {
     xd::lane::StateHead h = {H->d, H->base, H->thr - xd::kBias0, H->bi, H->dstar,
-                             (uint32_t)H->cells, (uint32_t)Q / 32, 0u};
+                             (uint32_t)H->cells, (uint32_t)Q / 32, (uint32_t)(H->cells >> 32)};
     *(xd::lane::StateHead*)dst = h;
   }
 }
