@@ -185,19 +185,23 @@ struct Scratch {
   int32_t* band;      // [blocks][3][cap] rows of the band tier
   BandGeom geom;
 };
-// ctr layout
-constexpr int kOvfCount = 0;   // [0..4] sizes of ovf[0..4]
-constexpr int kHead = 5;       // [5..9] work heads of tiers 0..4
-constexpr int kSeg = 10;       // [10..22] queue starts of the segments, then 2n, and the
+// ctr layout.  The segments have a line (128 bytes) to themselves: waves read
+// their bounds after every extension, and reads of the work heads' line held up
+// the heads' atomics (40 ns an extension for the whole chip; 6,000 pairs of 1.3
+// kbp reads at X = 25, one per wavefront: 0.73 ms, 0.45 so).
+constexpr int kOvfCount = 0;  // [0..4] sizes of ovf[0..4]
+constexpr int kLaneOvf = 5;   // [5..8] sizes of the lane tiers' lists 0..3
+constexpr int kResumed = 9;   // [9..12] moves out of windows 0..3 that carried their state
+constexpr int kLaneResumed = kLaneOvf + kResumed;  // [14..17] as kResumed, out of lane tiers
+constexpr int kSegHead1 = 13;  // work head of the 128-cell window's queue segment (batched form)
+constexpr int kLaneHead = 18;  // [18..26] work heads of tiers kTLane on
+constexpr int kHead = 27;      // [27..31] work heads of tiers 0..4
+constexpr int kSeg = 32;       // [32..44] queue starts of the segments, then 2n, and the
                                // workgroups of split extensions (k_bin_scan)
-constexpr int kBandHead = 23;  // work head of the band tier
-constexpr int kResumed = 24;   // [24..27] moves out of windows 0..3 that carried their state
-constexpr int kSegHead1 = 28;  // work head of the 128-cell window's queue segment (batched form)
-constexpr int kLaneOvf = 29;   // [29..32] sizes of the lane tiers' lists 0..3
-constexpr int kLaneHead = 33;  // [33..41] work heads of tiers kTLane on
-constexpr int kLaneResumed = kLaneOvf + kResumed;  // [53..56] as kResumed, out of lane tiers
+constexpr int kBandHead = 63;  // work head of the band tier (it has no segment)
 constexpr int kCtrWords = 64;
-static_assert(kSeg + kSegWords <= kBandHead && kLaneResumed + 4 <= kCtrWords, "counters");
+static_assert(kLaneResumed + 4 <= kLaneHead && kHead + 5 <= kSeg && kSeg + kSegWords <= kBandHead,
+              "counters");
 constexpr int kTierArgsBytes = 8 * 256;  // >= sizeof(TierPack), checked below
 constexpr uint64_t kFixedBytes = (kBins * 4 + kCtrWords * 4 + kTierArgsBytes + 255) & ~255ull;
 
@@ -249,6 +253,7 @@ Scratch scratch_carve(char* base, uint64_t n, const BandGeom& g) {
 // their queue segments or the rows of the window that takes a list.
 enum { kT64 = 0, kT128, kT256, kT512, kT1024, kTBand, kTSeg128, kTLane, kTNarrow, kTWide,
        kTSplit, kTWideSplit, kTL128, kTL256, kTL512, kTL1024, kTiers };
+static_assert(kLaneHead + (kTiers - kTLane) <= kHead, "work heads");
 
 // Arguments of a persistent tier.  A list's entry k is at list[k * step]: with
 // lane tiers theirs fill a list array from the front and the other tiers'
