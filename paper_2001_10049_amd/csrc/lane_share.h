@@ -69,14 +69,17 @@ XD_HD uint32_t bin_key(const BinRule& R, int32_t X, uint32_t cost) {
 // the fewer share a wavefront the sooner a step is done and the more
 // instructions it costs.  A CU runs one workgroup of single lanes or of split
 // extensions, and the wavefronts of the longest beside it, ahead of it in
-// priority.  In issue slots of a SIMD (vector instructions):
+// priority.  The narrow class's lanes alone come after its longest, in a launch
+// of their own, so its times add up.  In issue slots of a SIMD (vector
+// instructions; a wavefront's share from timing 12,500 to 100,000 pairs of 1.3 to
+// 20 kbp reads with shares of 9 to 12):
 struct LaneCost {
   float lane_step, split_step, solo_step;  // from one step of an extension to the next
   float solo;                              // one step's share of the instructions
   uint32_t split_group;                    // split extensions a workgroup holds
 };
 XD_HD LaneCost lane_cost(uint32_t cls) {
-  return cls == kClsNarrow ? LaneCost{82.f, 120.f, 25.f, 12.f, 128u}
+  return cls == kClsNarrow ? LaneCost{82.f, 120.f, 25.f, 10.5f, 128u}
          : cls == kClsLane ? LaneCost{160.f, 120.f, 25.f, 12.f, 128u}
                            : LaneCost{260.f, 130.f, 45.f, 20.f, 64u};
 }
@@ -118,14 +121,15 @@ XD_HD void class_bins(const uint32_t* h, int kind, ClassBins& x) {
   }
 }
 
-// Estimated end of a class whose first s1 length bins run alone and whose next
-// s2 - s1 run split, and the workgroups the latter get of cus: as many as
+// Estimated end of a class (kind) whose first s1 length bins run alone and whose
+// next s2 - s1 run split, and the workgroups the latter get of cus: as many as
 // hold those longer than half the longest at once, and make the average load
 // no more than the longest one's, at least one and not all of them (infinite
 // where that is no number).
-XD_HD float split_time(const ClassBins& x, uint32_t s1, uint32_t s2, const LaneCost& c, float cus,
+XD_HD float split_time(const ClassBins& x, int kind, uint32_t s1, uint32_t s2, float cus,
                        float& groups) {
   constexpr uint32_t N = kCostBins;
+  const LaneCost c = lane_cost(cls_of(kind));
   auto longest = [&](uint32_t from, uint32_t to) -> float {
     const uint32_t q = x.next[from];
     return q < to ? bin_end(N - 1 - q) : 0.f;
@@ -142,6 +146,7 @@ XD_HD float split_time(const ClassBins& x, uint32_t s1, uint32_t s2, const LaneC
   if (any && groups < 1.f) return INFINITY;
   const float t1 = any ? fmaxf(l1, split / (groups * (float)c.split_group)) : 0.f;
   const float t2 = fmaxf(l2, rest / (256.f * (cus - groups)));
+  if (kind == 0) return fmaxf(l0 * c.solo_step, t1 * c.split_step + solo) + t2 * c.lane_step;
   return fmaxf(l0 * c.solo_step, fmaxf(t1 * c.split_step, t2 * c.lane_step) + solo);
 }
 
@@ -152,7 +157,7 @@ XD_HD uint64_t share_rank(const ClassBins& x, int kind, uint32_t q, uint32_t cus
   const uint32_t s1 = q / (kCostBins + 1), s2 = q % (kCostBins + 1);
   if (s1 > s2) return ~0ull;
   float g;
-  const float e = split_time(x, s1, s2, lane_cost(cls_of(kind)), (float)cus, g);
+  const float e = split_time(x, kind, s1, s2, (float)cus, g);
   return (uint64_t)__builtin_bit_cast(uint32_t, e) << 32 | q;
 }
 
@@ -165,14 +170,15 @@ struct Shares {
     const uint32_t q = (uint32_t)rank;
     alone[kind] = q / (kCostBins + 1);
     split[kind] = q % (kCostBins + 1);
-    time[kind] = split_time(x, alone[kind], split[kind], lane_cost(cls_of(kind)), (float)cus,
-                            groups[kind]);
+    time[kind] = split_time(x, kind, alone[kind], split[kind], (float)cus, groups[kind]);
   }
-  // The narrow class's lanes run after the 64-row class's, in a launch of their
-  // own; when that would take longer than running them all in 64 rows (two
-  // chains of steps instead of one), the two are one class.  32,000 pairs at X
-  // of 7 and 25: 4.0 ms against 5.8.
-  XD_HD bool merged() const { return time[0] > 0.f && time[1] > 0.f && time[3] < time[0] + time[1]; }
+  // The narrow class's lanes run after the 64-row class's and its own longest, in a
+  // launch of their own; when that would take longer than running them all in 64
+  // rows (two chains of steps instead of one), they join that class.  32,000 pairs
+  // of 10 kbp at X of 7 and 25: 4.0 ms against 5.8; at X = 7, with the times added
+  // up and without (and the packed kernels): 4.0, 4.6 (4.7), 16,000 pairs 3.4, 4.2
+  // (3.1).
+  XD_HD bool merged() const { return time[0] > 0.f && time[3] < time[0] + time[1]; }
 };
 
 // where bin b comes in the queue (a permutation of the bins)

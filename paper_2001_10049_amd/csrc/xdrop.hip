@@ -1537,7 +1537,8 @@ struct Route {
   bool queue;            // the device queue (batched form)
   bool packed;           // two extensions per wavefront in the 64-, 128- and 256-cell windows
   bool solo;             // match = 1, too few extensions for that: one per wavefront
-  uint32_t lane_blocks;  // workgroups of the lane tiers (0: none)
+  uint32_t lane_blocks;  // workgroups of single and split lanes (0: no lane tiers)
+  uint32_t solo_blocks;  // more for the longest (with 96 rows, lane_blocks less)
 };
 
 // Extensions from which the lane tiers run: they hold 65,536 at once, and a
@@ -1546,6 +1547,10 @@ struct Route {
 // 3.02 / 4.11 / 2.90 ms, 16,000 3.16 / 4.30 / 3.11, 32,000 5.83 / 4.86 / 3.95;
 // at X = 50, one per wavefront / lanes: 8,000 4.78 / 4.90, 16,000 5.97 / 5.03.
 constexpr uint64_t kLaneMin = 24576;
+// Extensions up to which the lane tiers get a workgroup more per CU for those that
+// run one per wavefront: such a batch may run whole so, and the single lanes'
+// workgroups leave at once (12,500 pairs of 10 kbp at X = 25 2.99 -> 2.61 ms).
+constexpr uint64_t kLaneFill = 65536;
 // Extensions up to which the batched form runs one per wavefront: their time
 // is the longest one's chain of steps, about 40 ns a step with a wavefront to
 // itself and 90 ns in a packed one.  64 pairs at X of 7 and 25: 1.59 -> 1.15 ms
@@ -1575,9 +1580,12 @@ bool plain_queue(const BatchArgs& A, uint64_t n_ext, const Tuned& tu) {
 }
 
 Route batch_route(const xd::Scoring& sc, uint64_t n_ext, bool queue, bool planes) {
-  Route r = {queue, false, false, 0u};
+  Route r = {queue, false, false, 0u, 0u};
   if (!queue) return r;
-  if (planes && lane_ok(sc) && n_ext >= kLaneMin) r.lane_blocks = (uint32_t)device_cus();
+  if (planes && lane_ok(sc) && n_ext >= kLaneMin) {
+    r.lane_blocks = (uint32_t)device_cus();
+    r.solo_blocks = (n_ext < kLaneFill ? 4 : 3) * r.lane_blocks;
+  }
   if (pair_ok(sc)) {
     r.solo = n_ext <= kSoloMax;
     r.packed = !r.solo;
@@ -1680,8 +1688,9 @@ void launch_wide(const Scratch& S, uint32_t blocks, hipStream_t stream, const Ro
   const xd::pair::Shared* pz = &S.targs->pz;
   if (R.lane_blocks) {
     const uint32_t n = R.lane_blocks;
-    hipLaunchKernelGGL((k_lane_tier<7, 3>), dim3(3 * n), dim3(256), 0, stream, ga, ta + kTWide,
-                       ta + kTWideSplit, ta + kTSeg128, S.ctr + kSeg + kWideSplitBlocks, n);
+    hipLaunchKernelGGL((k_lane_tier<7, 3>), dim3(R.solo_blocks), dim3(256), 0, stream, ga,
+                       ta + kTWide, ta + kTWideSplit, ta + kTSeg128,
+                       S.ctr + kSeg + kWideSplitBlocks, n);
     hipLaunchKernelGGL((k_lane_list<4>), dim3(4 * n), dim3(256), 0, stream, ga, ta + kTL128);
     hipLaunchKernelGGL((k_lane_list<8>), dim3(4 * n), dim3(256), 0, stream, ga, ta + kTL256);
     hipLaunchKernelGGL((k_lane_list<16>), dim3(4 * n), dim3(256), 0, stream, ga, ta + kTL512);
@@ -1715,11 +1724,12 @@ void launch_pair(const Scratch& S, uint32_t blocks, hipStream_t stream) {
                      &S.targs->A, S.targs->t + kT64, &S.targs->pz);
 }
 
-void launch_lane(const Scratch& S, uint32_t n, hipStream_t stream) {
+void launch_lane(const Scratch& S, const Route& R, hipStream_t stream) {
+  const uint32_t n = R.lane_blocks;
   const TaskArgs* ga = &S.targs->A;
   const TierArgs* ta = S.targs->t;
-  hipLaunchKernelGGL((k_lane_tier<6, 2>), dim3(4 * n), dim3(256), 0, stream, ga, ta + kTLane,
-                     ta + kTSplit, ta + kT64, S.ctr + kSeg + kSplitBlocks, n);
+  hipLaunchKernelGGL((k_lane_tier<6, 2>), dim3(n + R.solo_blocks), dim3(256), 0, stream, ga,
+                     ta + kTLane, ta + kTSplit, ta + kT64, S.ctr + kSeg + kSplitBlocks, n);
   hipLaunchKernelGGL((k_lane_tier<5, 1>), dim3(n), dim3(256), 0, stream, ga, ta + kTNarrow,
                      ta + kTNarrow, ta + kT64, S.ctr + kSeg + kSplitBlocks, n);
 }
@@ -1760,7 +1770,7 @@ void launch_persistent_ext(const BatchArgs& A, const Scratch& S, uint64_t n_ext,
   uint32_t blocks = (uint32_t)device_cus() * (uint32_t)tu.waves_per_cu / 4u;
   if (blocks < 1) blocks = 1;
   if (Rt.lane_blocks)
-    launch_lane(S, Rt.lane_blocks, stream);
+    launch_lane(S, Rt, stream);
   else if (Rt.packed)
     launch_pair(S, blocks, stream);
   else if (UNIT && Rt.solo)

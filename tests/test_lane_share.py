@@ -38,6 +38,16 @@ def test_random_batches(cus):
         check(np.concatenate(x), np.concatenate(cost), cus=cus, by_cost=int(rng.integers(2)))
 
 
+def test_narrow_class_alone():
+    # its lanes run after its longest, so thousands of long ones do not wait
+    # for a launch of lanes: 16,000 pairs of 10 kbp at X = 7
+    rng = np.random.default_rng(1)
+    length = np.exp(rng.normal(9.1, 0.47, 32_000)).clip(3000, 50_000)
+    cost = (1.4 * length * rng.random(32_000)).astype(np.uint32) + 2
+    s = check(np.full(32_000, 7), cost)
+    assert s["solo"] + s["split"] > 8000, s
+
+
 def test_one_workgroup_splits_nothing():
     s = check(np.full(5000, 50), np.full(5000, 20_000), cus=1)
     assert s["split"] == s["wide_split"] == 0, s
