@@ -111,9 +111,10 @@ int xd_store_info(const xd_store* store, uint64_t* device_bytes, uint32_t* n_rea
 /* ---- batch alignment ----------------------------------------------------- */
 
 /* Aligns n tasks, one launch sequence per call (the plain form): in task order
- * one wavefront per extension for batches of less than 3,000 tasks, else (and
- * where x_scalar asks for a wider first window) through the device queue of
- * the batched form with its default tuning.
+ * one wavefront per extension for batches of less than 3,000 tasks and stores
+ * of short reads (less than 2,500 bases on average), else (and where x_scalar
+ * asks for a wider first window) through the device queue of the batched form
+ * with its default tuning.
  *
  * Device pointers, caller-owned, valid until the stream reaches the work:
  *   pairs  uint32[2n]  (ra, rb) per task

@@ -8,8 +8,8 @@
 // truncated.
 //
 // Plain form (xd_align_batch), stream-ordered on the caller's stream, for
-// small batches (plain_queue; others go through the queue
-// below):
+// small batches and short reads (xd::plain_queue; others go through the
+// queue below):
 //   k_reset      zero the counters and the histogram
 //   k_ext_first  one wavefront per extension (2 per task: left, right) with
 //                the 64-cell window
@@ -42,6 +42,7 @@
 
 #include "xdrop.h"
 #include "scan.h"
+#include "batch_route.h"
 #include "store_view.h"
 #include "band_pair.h"
 #include "xdrop_device.h"
@@ -52,6 +53,7 @@
 #include "pair_device.h"
 
 using xd::ExtOut;
+using xd::Route;
 
 // Per-wave busy intervals of the extension kernels, compiled in only with
 // -DXD_WAVE_STAMPS (the instrumented build libxdrop_stamps.so).  Each wave
@@ -1532,31 +1534,6 @@ xd::pair::Shared pair_shared(const xd::Scoring& sc) {
   return z;
 }
 
-// Which kernels a batch runs in.
-struct Route {
-  bool queue;            // the device queue (batched form)
-  bool packed;           // two extensions per wavefront in the 64-, 128- and 256-cell windows
-  bool solo;             // match = 1, too few extensions for that: one per wavefront
-  uint32_t lane_blocks;  // workgroups of single and split lanes (0: no lane tiers)
-  uint32_t solo_blocks;  // more for the longest (with 96 rows, lane_blocks less)
-};
-
-// Extensions from which the lane tiers run: they hold 65,536 at once, and a
-// batch of half as many leaves most of them to wavefronts of their own.  Read
-// pairs of 10 kbp at X = 25, one per wavefront / packed / lanes: 8,000 pairs
-// 3.02 / 4.11 / 2.90 ms, 16,000 3.16 / 4.30 / 3.11, 32,000 5.83 / 4.86 / 3.95;
-// at X = 50, one per wavefront / lanes: 8,000 4.78 / 4.90, 16,000 5.97 / 5.03.
-constexpr uint64_t kLaneMin = 24576;
-// Extensions up to which the lane tiers get a workgroup more per CU for those that
-// run one per wavefront: such a batch may run whole so, and the single lanes'
-// workgroups leave at once (12,500 pairs of 10 kbp at X = 25 2.99 -> 2.61 ms).
-constexpr uint64_t kLaneFill = 65536;
-// Extensions up to which the batched form runs one per wavefront: their time
-// is the longest one's chain of steps, about 40 ns a step with a wavefront to
-// itself and 90 ns in a packed one.  64 pairs at X of 7 and 25: 1.59 -> 1.15 ms
-// as a plan; the figures above cross at about 24,000 pairs.
-constexpr uint64_t kSoloMax = kLaneMin - 1;
-
 // X up to which extensions start in a window whose limit is tier.  A cell k
 // rows off the best one on its antidiagonal has lost about k (gap + match /
 // 2); the default limits are for scores 1/-1/-1, where that is 1.5 k, and grow
@@ -1567,30 +1544,19 @@ int32_t x_limit(const Tuned& tu, const xd::Scoring& sc, int32_t tier) {
   return tu.x_given ? tier : tier * (sc.M - 2 * sc.G) / 3;
 }
 
-// Whether a plain batch goes through the device queue all the same: from 6,000
-// extensions on (longest first; read pairs of 10 kbp at X = 25, without / with
-// the queue: 2,000 pairs 1.58 / 1.64 ms, 4,000 2.30 / 2.08, 100,000 17.9 / 5.6;
-// 20,011 pairs at X = 50 and 2/-3/-2: 6.9 / 5.1), or when X is known to need a
-// wider first window than 64 cells, which would otherwise be run and given up
-// (2,000 pairs at X = 50: 5.2 / 2.7 ms).
-constexpr uint64_t kQueueMin = 6000;
-
-bool plain_queue(const BatchArgs& A, uint64_t n_ext, const Tuned& tu) {
-  return n_ext >= kQueueMin || (!A.x && A.x_scalar > x_limit(tu, A.sc, tu.x_tier1));
-}
-
-Route batch_route(const xd::Scoring& sc, uint64_t n_ext, bool queue, bool planes) {
-  Route r = {queue, false, false, 0u, 0u};
-  if (!queue) return r;
-  if (planes && lane_ok(sc) && n_ext >= kLaneMin) {
-    r.lane_blocks = (uint32_t)device_cus();
-    r.solo_blocks = (n_ext < kLaneFill ? 4 : 3) * r.lane_blocks;
-  }
-  if (pair_ok(sc)) {
-    r.solo = n_ext <= kSoloMax;
-    r.packed = !r.solo;
-  }
-  return r;
+Route batch_route(const BatchArgs& A, bool batched, uint32_t mean_len, const Tuned& tu) {
+  xd::BatchShape b;
+  b.batched = batched;
+  b.pair_ok = pair_ok(A.sc);
+  b.lane_ok = A.st.planes && lane_ok(A.sc);
+  b.x_known = !A.x;
+  b.x = A.x_scalar;
+  b.n_ext = 2 * (uint64_t)A.n;
+  b.mean_len = mean_len;
+  b.tier1 = x_limit(tu, A.sc, tu.x_tier1);
+  b.tier2 = x_limit(tu, A.sc, tu.x_tier2);
+  b.cus = (uint32_t)device_cus();
+  return xd::batch_route(b);
 }
 
 // tier arguments: tier 0 (64 cells, batched form), tiers 1..4 (128, 256, 512,
@@ -1759,8 +1725,7 @@ void launch_persistent_ext(const BatchArgs& A, const Scratch& S, uint64_t n_ext,
                            const Tuned& tu, const Route& Rt, hipEvent_t* ev,
                            hipStream_t stream) {
   const uint32_t grid = (uint32_t)((n_ext + 255) / 256);
-  BinRule R = {x_limit(tu, A.sc, tu.x_tier1), x_limit(tu, A.sc, tu.x_tier2),
-               tu.order == 1 ? 1 : 0, Rt.lane_blocks};
+  BinRule R = {Rt.tier1, Rt.tier2, tu.order == 1 ? 1 : 0, Rt.lane_blocks};
   hipLaunchKernelGGL(k_bin_hist, dim3(grid), dim3(256), 0, stream, A, R, (uint32_t)n_ext,
                      S.hist);
   hipLaunchKernelGGL(k_bin_scan, dim3(1), dim3(kBins), 0, stream, S.hist, S.ctr + kSeg, R,
@@ -1894,7 +1859,7 @@ struct xd_store {
   uint64_t n_chunks = 0;
   uint64_t n_words = 0;
   uint32_t n_reads = 0;
-  uint32_t max_len = 0;
+  uint32_t max_len = 0, mean_len = 0;
   int device = 0;
   std::vector<uint32_t> host_len;
 };
@@ -1972,12 +1937,12 @@ int make_args(const xd_store* store, const uint32_t* pairs, const uint32_t* seed
   return XD_OK;
 }
 
-// Enqueues the whole batch on `stream`.  persistent: batched form.
-int enqueue(BatchArgs A, const Scratch& S, bool persistent, const Tuned& tu,
+// Enqueues the whole batch on `stream`.  batched: the form asked for; mean_len: of
+// the store's reads.
+int enqueue(BatchArgs A, const Scratch& S, bool batched, uint32_t mean_len, const Tuned& tu,
             hipStream_t stream, bool allow_profile) {
   A.ext = S.ext;
   const uint64_t n_ext = 2 * (uint64_t)A.n;
-  persistent = persistent || plain_queue(A, n_ext, tu);
   const bool prof = allow_profile && g_prof_on.load(std::memory_order_relaxed) != 0;
   ProfRecord rec = {};
   if (prof) {
@@ -1986,10 +1951,10 @@ int enqueue(BatchArgs A, const Scratch& S, bool persistent, const Tuned& tu,
                           hipHostMallocDefault));
     rec.n_ext = n_ext;
   }
-  const Route R = batch_route(A.sc, n_ext, persistent, A.st.planes != nullptr);
+  const Route R = batch_route(A, batched, mean_len, tu);
   hipLaunchKernelGGL(k_reset, dim3(1), dim3(256), 0, stream, S.ctr, S.hist,
                      make_pack(A, S, R), (uint32_t*)S.targs);
-  if (persistent) {
+  if (R.queue) {
     if (prof) HIP_TRY(hipEventRecord(rec.ev[0], stream));
     if (unit_scoring(A.sc))
       launch_persistent_ext<true>(A, S, n_ext, tu, R, prof ? rec.ev : nullptr, stream);
@@ -2015,12 +1980,12 @@ int enqueue(BatchArgs A, const Scratch& S, bool persistent, const Tuned& tu,
   return XD_OK;
 }
 
-int batch_async(const BatchArgs& A, uint32_t max_len, bool persistent, const Tuned& tu,
+int batch_async(const BatchArgs& A, const xd_store* store, bool batched, const Tuned& tu,
                 hipStream_t stream) {
-  const BandGeom g = band_geom(max_len, (uint32_t)tu.band_blocks);
+  const BandGeom g = band_geom(store->max_len, (uint32_t)tu.band_blocks);
   char* mem = nullptr;
   HIP_TRY(xd_internal_malloc_async((void**)&mem, scratch_bytes(A.n, g), stream));
-  int rc = enqueue(A, scratch_carve(mem, A.n, g), persistent, tu, stream, true);
+  int rc = enqueue(A, scratch_carve(mem, A.n, g), batched, store->mean_len, tu, stream, true);
   hipError_t fe = hipFreeAsync(mem, stream);
   if (rc) return rc;
   if (fe != hipSuccess) return hip_fail(fe, "hipFreeAsync");
@@ -2178,6 +2143,7 @@ int xd_store_create(const uint32_t* words, uint64_t n_words, const uint64_t* wor
   if (n_reads && (!word_off || !len)) return fail(XD_EINVAL, "xd_store_create: null arrays");
   if (n_words && !words) return fail(XD_EINVAL, "xd_store_create: words is null");
   uint32_t max_len = 0;
+  uint64_t bases = 0;
   for (uint32_t r = 0; r < n_reads; ++r) {
     if (len[r] > XD_READ_MAX)
       return fail(XD_EINVAL, "read %u has %u bases (limit %u)", r, len[r], XD_READ_MAX);
@@ -2186,6 +2152,7 @@ int xd_store_create(const uint32_t* words, uint64_t n_words, const uint64_t* wor
       return fail(XD_EINVAL, "read %u ends at word %llu past n_words %llu", r,
                   (unsigned long long)need, (unsigned long long)n_words);
     if (len[r] > max_len) max_len = len[r];
+    bases += len[r];
   }
   std::vector<uint64_t> plane_off(n_reads ? n_reads : 1);
   uint64_t n_chunks = xd::lane::kGuard;
@@ -2198,6 +2165,7 @@ int xd_store_create(const uint32_t* words, uint64_t n_words, const uint64_t* wor
   s->n_words = n_words;
   s->n_reads = n_reads;
   s->max_len = max_len;
+  s->mean_len = n_reads ? (uint32_t)(bases / n_reads) : 0u;
   s->host_len.assign(len, len + n_reads);
   hipError_t e = hipGetDevice(&s->device);
   const uint64_t wb = (n_words ? n_words : 1) * sizeof(uint32_t);
@@ -2288,7 +2256,7 @@ int xd_align_batch(const xd_store* store, const uint32_t* pairs, const uint32_t*
   if (n == 0) return XD_OK;
   Tuned tu;
   check_tuning(nullptr, tu);
-  return batch_async(A, store->max_len, false, tu, (hipStream_t)hip_stream);
+  return batch_async(A, store, false, tu, (hipStream_t)hip_stream);
 }
 
 int xd_align_batch_noalloc(const xd_store* store, const uint32_t* pairs, const uint32_t* seeds,
@@ -2314,7 +2282,8 @@ int xd_align_batch_noalloc(const xd_store* store, const uint32_t* pairs, const u
   char* mem = nullptr;
   rc = noalloc_scratch(&mem);
   if (rc) return rc;
-  return enqueue(A, scratch_carve(mem, n, g), false, tu, (hipStream_t)hip_stream, false);
+  return enqueue(A, scratch_carve(mem, n, g), false, store->mean_len, tu, (hipStream_t)hip_stream,
+                 false);
 }
 
 int xd_align_batch_persistent(const xd_store* store, const uint32_t* pairs,
@@ -2331,7 +2300,7 @@ int xd_align_batch_persistent(const xd_store* store, const uint32_t* pairs,
   rc = check_tuning(tuning, tu);
   if (rc) return rc;
   if (n == 0) return XD_OK;
-  return batch_async(A, store->max_len, true, tu, (hipStream_t)hip_stream);
+  return batch_async(A, store, true, tu, (hipStream_t)hip_stream);
 }
 
 int xd_align_pairs(const xd_store* store, uint64_t n_pairs, const uint32_t* pairs,
@@ -2414,7 +2383,7 @@ int xd_align_pairs(const xd_store* store, uint64_t n_pairs, const uint32_t* pair
                     P.t_score, P.t_beg, P.t_end, P.t_status, P.t_cells, A);
     if (rc2 == XD_OK) {
       A.flags = P.t_flags;
-      rc2 = enqueue(A, scratch_carve(q, S, g), true, tu, stream, true);
+      rc2 = enqueue(A, scratch_carve(q, S, g), true, store->mean_len, tu, stream, true);
     }
   }
   if (rc2 == XD_OK)
@@ -2597,7 +2566,7 @@ int xd_plan_create(const xd_store* store, const uint32_t* pairs, const uint32_t*
     xd_plan_destroy(p);
     return rc;
   }
-  rc = enqueue(A, p->scratch, true, tu, p->cap, false);
+  rc = enqueue(A, p->scratch, true, store->mean_len, tu, p->cap, false);
   e = hipStreamEndCapture(p->cap, &p->graph);
   if (rc == XD_OK && e != hipSuccess) rc = hip_fail(e, "hipStreamEndCapture");
   if (rc == XD_OK) {
