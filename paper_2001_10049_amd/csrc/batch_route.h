@@ -28,8 +28,16 @@ struct Route {
 };
 
 // Extensions from which the lane tiers run: they hold 65,536 at once, and a
-// batch of half as many leaves most of them to wavefronts of their own.
+// batch of half as many leaves most of them to wavefronts of their own.  Read
+// pairs, ms one per wavefront / packed / in lanes: 12,500 at X = 25 2.4 / 2.9 / 2.6
+// (10 kbp), 0.76 / 0.79 / 0.72 (1.3 kbp), 16,000 3.0 / 3.2 / 2.9, 32,000 5.5 / 4.8
+// / 3.8; at X = 50 12,500 4.7 / 4.4 / 3.7.
 constexpr uint64_t kLaneMin = 24576;
+// X up to 14 gains later in long reads, because the narrow windows' lanes run in a
+// launch after its longest: 20,000 pairs of 10 kbp at X = 7 3.5 / 3.3 / 3.6, 24,000
+// 4.0 / 3.7 / 3.8, 32,000 5.3 / 4.7 / 4.0.
+constexpr uint64_t kNarrowMin = 49152;
+constexpr int32_t kNarrowX = 14;
 // Extensions up to which the lane tiers get a workgroup more per CU for those that
 // run one per wavefront: such a batch may run whole so, and the single lanes'
 // workgroups leave at once (12,500 pairs of 10 kbp at X = 25 2.99 -> 2.61 ms).
@@ -37,8 +45,12 @@ constexpr uint64_t kLaneFill = 65536;
 // Extensions up to which the batched form runs one per wavefront: their time
 // is the longest one's chain of steps, about 40 ns a step with a wavefront to
 // itself and 90 ns in a packed one.  64 pairs at X of 7 and 25: 1.59 -> 1.15 ms
-// as a plan.
-constexpr uint64_t kSoloMax = kLaneMin - 1;
+// as a plan.  The packed kernels catch up at 18,000 to 20,000 pairs when all start
+// in 64 cells (one per wavefront / packed, X = 25: 16,000 of 10 kbp 3.0 / 3.2, 20,000
+// 3.6 / 3.4, of 3.5 kbp 1.38 / 1.42, 1.68 / 1.63), sooner when they start wider (X =
+// 50: 12,000 of 10 kbp 4.5 / 4.9, 16,000 5.7 / 5.3, 6,000 of 3.5 kbp 1.18 / 1.26,
+// 9,000 1.62 / 1.43); when the host does not know X, at the lane tiers' line.
+constexpr uint64_t kSoloMax = kLaneMin - 1, kSoloMaxKnown = 36000, kSoloMaxWide = 15000;
 
 // Whether a plain batch goes through the device queue all the same.  One
 // wavefront per extension in task order has two launches and no sort before it;
@@ -77,12 +89,16 @@ inline Route batch_route(const BatchShape& b) {
     r.tier1 = (int32_t)(6ll * b.tier1 / 5);
     r.tier2 = (int32_t)(6ll * b.tier2 / 5);
   }
-  if (b.lane_ok && b.n_ext >= kLaneMin) {
+  const bool longer = b.mean_len >= 5000;
+  const bool narrow = longer && b.x_known && b.x <= kNarrowX;
+  if (b.lane_ok && b.n_ext >= (narrow ? kNarrowMin : kLaneMin)) {
     r.lane_blocks = b.cus;
     r.solo_blocks = (b.n_ext < kLaneFill ? 4 : 3) * b.cus;
   }
   if (b.pair_ok) {
-    r.solo = b.n_ext <= kSoloMax;
+    const uint64_t solo_max = !b.x_known ? kSoloMax
+                              : b.x <= r.tier1 ? kSoloMaxKnown : longer ? kSoloMax : kSoloMaxWide;
+    r.solo = !r.lane_blocks && b.n_ext <= solo_max;
     r.packed = !r.solo;
   }
   return r;

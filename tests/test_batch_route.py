@@ -58,7 +58,23 @@ def test_batched(route):
     assert (large["queue"], large["packed"], large["lane_blocks"]) == (1, 1, 256)
     assert (small["tier1"], small["tier2"]) == (32, 80)
     assert large["solo_blocks"] == 1024 and route(32_768, batched=True)["solo_blocks"] == 768
-    other = route(12_288, 25, batched=True, lane=False)
+    other = route(18_001, 25, batched=True, lane=False)
     assert (other["packed"], other["lane_blocks"]) == (1, 0)
     general = route(50_000, 25, batched=True, pair=False, lane=False)
     assert (general["queue"], general["packed"], general["solo"]) == (1, 0, 0)
+
+
+@pytest.mark.parametrize("n,x,mean,lane,kernels", [
+    (18_000, 7, 10_000, True, "solo"), (18_001, 7, 10_000, True, "packed"),
+    (24_575, 14, 5_000, True, "packed"), (24_576, 14, 5_000, True, "lanes"),
+    (12_288, 14, 4_999, True, "lanes"), (12_288, 15, 10_000, True, "lanes"),
+    (12_288, None, 10_000, True, "lanes"), (12_287, None, 10_000, True, "solo"),
+    (12_288, None, 10_000, False, "packed"), (18_000, 32, 10_000, False, "solo"),
+    (18_001, 32, 10_000, False, "packed"), (12_287, 33, 5_000, True, "solo"),
+    (7_500, 33, 4_999, True, "solo"), (7_501, 33, 4_999, True, "packed"),
+    (12_288, 33, 4_999, True, "lanes"),
+])
+def test_batched_kernels(route, n, x, mean, lane, kernels):
+    r = route(n, x, mean, batched=True, lane=lane)
+    got = "lanes" if r["lane_blocks"] else "solo" if r["solo"] else "packed"
+    assert got == kernels and r["packed"] == (not r["solo"]), r
