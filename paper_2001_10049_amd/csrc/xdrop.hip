@@ -2442,8 +2442,10 @@ int xd_banded_batch(const xd_store* store, const uint32_t* pairs, const uint32_t
     // Two tasks to a wavefront wherever a mismatch costs (the floor in 16 bits
     // rests on that): 50,000 pairs of 10 kbp reads, w = 32, 11.6 -> 6.25 ms
     // against one to a wavefront, 500 of them 2.10 -> 1.42 (its antidiagonals
-    // are the shorter chain too).
-    if (mismatch < 0) {
+    // are the shorter chain too).  Where most tasks pass 16 bits, which k_banded_pair
+    // runs one after another, one to a wavefront (17,000 pairs of 40 kbp at 2/-3/-2
+    // 30.7 -> 19.9 ms, 1,000 of them 11.4 -> 6.1).
+    if (mismatch < 0 && (uint64_t)match * store->mean_len <= xd::pair_band::kMaxH) {
       const uint32_t per = pair_tasks(n), np = (nb + per - 1) / per;
       if (match == 1)
         hipLaunchKernelGGL((k_banded_pair<true>), dim3(np), dim3(64), 0, stream, A, nb, per);
