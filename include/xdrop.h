@@ -92,8 +92,8 @@ int xd_pack_reads(const uint8_t* codes, const uint64_t* off, const uint32_t* len
 
 /* Copies a packed read set (host pointers, store layout) to the current HIP
  * device, and lays it out there a second time in bit planes (2 bits a base too),
- * which the lane kernels read (where the memory does not hold both, the planes
- * and those kernels are left out).  The store owns its device memory until xd_store_destroy().  It is
+ * which the lane kernels read (where that would take more than an eighth of the
+ * memory left free, the planes and those kernels are left out).  The store owns its device memory until xd_store_destroy().  It is
  * read-only afterwards and may be used from several streams at once. */
 int xd_store_create(const uint32_t* words, uint64_t n_words, const uint64_t* word_off,
                     const uint32_t* len, uint32_t n_reads, xd_store** out);

@@ -2178,17 +2178,21 @@ int xd_store_create(const uint32_t* words, uint64_t n_words, const uint64_t* wor
     e = hipMemcpy(s->word_off, word_off, n_reads * 8ull, hipMemcpyHostToDevice);
   if (e == hipSuccess && n_reads)
     e = hipMemcpy(s->len, len, n_reads * 4ull, hipMemcpyHostToDevice);
-  if (e == hipSuccess) {
+  // the planes, where they leave seven eighths of the free memory to scratch and to
+  // the caller: else a store without them, and no lane tiers
+  size_t free_mem = 0, total_mem = 0;
+  if (e == hipSuccess) e = hipMemGetInfo(&free_mem, &total_mem);
+  if (e == hipSuccess && n_chunks * sizeof(xd::lane::Chunk) + 8ull * n_reads <= free_mem / 8) {
     hipError_t pe = hipMalloc((void**)&s->planes, n_chunks * sizeof(xd::lane::Chunk));
     if (pe == hipSuccess) pe = hipMalloc((void**)&s->plane_off, (n_reads ? n_reads : 1) * 8ull);
-    if (pe != hipSuccess) {  // no room for the planes: a store without them, and no lane tiers
+    if (pe != hipSuccess) {
       (void)hipGetLastError();
       (void)hipFree(s->planes);
       s->planes = nullptr;
       s->plane_off = nullptr;
-      s->n_chunks = 0;
     }
   }
+  if (!s->planes) s->n_chunks = 0;
   if (e == hipSuccess && s->planes && n_reads)
     e = hipMemcpy(s->plane_off, plane_off.data(), n_reads * 8ull, hipMemcpyHostToDevice);
   if (e == hipSuccess && s->planes && n_reads) {
@@ -2238,7 +2242,7 @@ int xd_store_info(const xd_store* s, uint64_t* device_bytes, uint32_t* n_reads,
                   uint32_t* max_len) {
   if (!s) return fail(XD_EINVAL, "xd_store_info: store is null");
   if (device_bytes)
-    *device_bytes = s->n_words * 4 + (uint64_t)s->n_reads * 20 +
+    *device_bytes = s->n_words * 4 + (uint64_t)s->n_reads * (s->planes ? 20 : 12) +
                     s->n_chunks * sizeof(xd::lane::Chunk);
   if (n_reads) *n_reads = s->n_reads;
   if (max_len) *max_len = s->max_len;
