@@ -29,7 +29,6 @@ namespace pair2 {
 using pair::kBase;
 using pair::kNegPat;
 using pair::kPat;
-using pair::kThrMax;
 using pair::kCWords;
 using pair::Shared;
 using pair::kGo;
@@ -594,7 +593,8 @@ __device__ void run(Work& W, uint32_t* lds, const Shared* Zp) {
   const int32_t g = (int32_t)pair::uni((uint32_t)Zp->g);
   // groups between rebases (as in pair::run) and counter flushes (each
   // group adds at most 2 GS a lane: 64 groups stay below 2048)
-  const int32_t stretch = min(32, (kThrMax - kBase - g) / (GS * (g + 1)) - 1);
+  const int32_t stretch = pair::stretch_groups(GS, g, 32);
+  static_assert(pair::stretches_fit(GS), "room for a group between rebases");
   bool more = true;
   for (;;) {
     if (!A.active && more) {

@@ -29,7 +29,6 @@ namespace pair4 {
 using pair::kBase;
 using pair::kNegPat;
 using pair::kPat;
-using pair::kThrMax;
 using pair::kCWords;
 using pair::Shared;
 using pair::kGo;
@@ -608,7 +607,8 @@ __device__ void run(Work& W, uint32_t* lds, const Shared* Zp) {
   const int32_t g = (int32_t)pair::uni((uint32_t)Zp->g);
   // groups between rebases (thr may rise by GS (g + 1) a group and must stay
   // below 2048) and counter flushes (each group adds at most R GS a lane)
-  const int32_t stretch = min(2048 / (R * GS) - 1, (kThrMax - kBase - g) / (GS * (g + 1)) - 1);
+  const int32_t stretch = pair::stretch_groups(GS, g, 2048 / (R * GS) - 1);
+  static_assert(pair::stretches_fit(GS), "room for a group between rebases");
   bool more = true;
   for (;;) {
     if (!A.active && more) {

@@ -86,6 +86,21 @@ constexpr uint32_t kNegPat = 0xE000u;  // pattern of -v is kNegPat + v (1024 <= 
 constexpr int32_t kXMax = 4096;
 constexpr int32_t kGapMax = 48;
 
+// Groups of G antidiagonals between rebases, at most `cap`: thr starts a stretch
+// at or below 1024 + g and may rise by G (g + 1) a group while it must stay below
+// 2048.  At least one, which every g this tier takes leaves room for: with none a
+// run would go round its general path for good.
+constexpr int32_t stretch_groups(int32_t G, int32_t g, int32_t cap) {
+  const int32_t fit = (kThrMax - kBase - g) / (G * (g + 1)) - 1;
+  return fit < 1 ? 1 : fit < cap ? fit : cap;
+}
+constexpr bool stretches_fit(int32_t G) {
+  for (int32_t g = 1; g <= kGapMax; ++g)
+    if (kBase + g + stretch_groups(G, g, 64) * G * (g + 1) > kThrMax) return false;
+  return true;
+}
+static_assert(stretches_fit(GS), "room for a group between rebases");
+
 typedef __attribute__((address_space(3))) uint8_t lds_u8;
 typedef __attribute__((address_space(3))) uint32_t lds_u32;
 
@@ -755,10 +770,9 @@ __device__ void run(Work& W, uint32_t* lds, const Shared* Zp) {
   const uint32_t ONE = 0xBC00BC00u;  // binary16 -1.0 in both halves
   const uint32_t G1 = uni(Zp->G1), GB1 = uni(Zp->GB1);
   const int32_t g = (int32_t)uni((uint32_t)Zp->g);
-  // groups between rebases: thr starts a stretch at or below 1024 + g and may
-  // rise by GS (g + 1) a group while it must stay below 2048; and at most 64
-  // groups between flushes of the binary16 counters (each adds <= GS a lane)
-  const int32_t stretch = min(64, (kThrMax - kBase - g) / (GS * (g + 1)) - 1);
+  // groups between rebases, and at most 64 between flushes of the binary16
+  // counters (each adds <= GS a lane)
+  const int32_t stretch = stretch_groups(GS, g, 64);
   bool more = true;
   for (;;) {
     // ---- general path ----
