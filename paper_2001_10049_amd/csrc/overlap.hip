@@ -69,7 +69,7 @@ __device__ __forceinline__ uint64_t bloom_word(uint64_t h, uint64_t W) {
 }
 
 // Neighbouring k-mers share the smallest hash `mh` of their m-mers, three of them
-// or so, and the filters are laid out by it.
+// or so, and the filters are laid out by it (RUNS), up to 2^27 words of filter A.
 //
 // Filter A: all k-mers of one mh lie in one word, so that a run of them in a
 // thread takes one atomic.  Atomics are what bounds pass 1: the counters show
@@ -78,7 +78,11 @@ __device__ __forceinline__ uint64_t bloom_word(uint64_t h, uint64_t W) {
 // evenly than by the k-mer's own hash: the m-mers have to outnumber the
 // words by eight, which keeps false repeats to 1 % of the k-mers (0.25 % by the
 // k-mer's own hash; 2.8 % with four to a word, 18 % with half a one to a word),
-// and filters of more than 2^27 words (1 GB) are too many for a 32-bit mh.
+// and filters of more than 2^27 words (1 GB) are too many for a 32-bit mh.  Those,
+// and their filter B, go by the k-mer's own hash, a k-mer at a time: without runs
+// the m-mers and eight k-mers in flight only cost (0.7 Gbp, both strands, k = 31:
+// 105 ms before the runs, 116 with B in lines and eight in flight, 104 so; one
+// strand, k = 17: 217, 197, 184).
 __device__ __forceinline__ uint64_t run_word(uint32_t mh, uint64_t W) {
   return ((uint64_t)(mh * 0x9e3779b1u) * W) >> 32;
 }
@@ -90,7 +94,9 @@ constexpr uint64_t kRunWords = 1ull << 27;
 // (2.73 -> 2.1 ms; 2.63 with a line for every k-mer).
 constexpr uint64_t kLine = 16;
 
+template <bool RUNS>
 __device__ __forceinline__ uint64_t line_word(uint32_t mh, uint64_t h, uint64_t W) {
+  if (!RUNS) return bloom_word(h, W);
   const uint32_t lines = (uint32_t)(W / kLine);
   return (uint64_t)__umulhi(mh * 0x9e3779b1u, lines) * kLine + ((h >> 18) & (kLine - 1));
 }
@@ -126,7 +132,8 @@ struct Kmer {
 // code, strand 0.  Both strands: the smaller of the code and its reverse
 // complement's code (the complement 3 - b of each base, in reverse order),
 // strand 1 when the reverse complement is the smaller; the m-mers likewise.
-template <int AHEAD, class F>
+// MERS: find mh (else 0).
+template <int AHEAD, bool MERS, class F>
 __device__ __forceinline__ void for_kmers(const KmerScan& s, uint64_t c, F&& f) {
   uint32_t lo = 0, hi = s.n_reads - 1;  // the last read whose first chunk is <= c
   while (lo < hi) {
@@ -158,6 +165,7 @@ __device__ __forceinline__ void for_kmers(const KmerScan& s, uint64_t c, F&& f) 
     rcode = (rcode >> 2) | ((3ull - b) << top);
   };
   auto add_hash = [&]() {
+    if (!MERS) return;
     uint64_t v = code & s.mmask;
     if (s.both) v = min(v, rcode >> mtop);
     for (int i = kWindow - 1; i > 0; --i) h[i] = h[i - 1];
@@ -176,8 +184,8 @@ __device__ __forceinline__ void for_kmers(const KmerScan& s, uint64_t c, F&& f) 
         add_hash();
       }
       const bool flip = s.both && rcode < code;
-      uint32_t mh = h[0];
-      for (int q = 1; q < kWindow; ++q) mh = q < window ? min(mh, h[q]) : mh;
+      uint32_t mh = MERS ? h[0] : 0u;
+      for (int q = 1; MERS && q < kWindow; ++q) mh = q < window ? min(mh, h[q]) : mh;
       km[i] = Kmer{flip ? rcode : code, flip ? 1u : 0u, mh};
     }
     f(r, p, km, n);
@@ -200,11 +208,11 @@ template <bool RUNS>
 __global__ __launch_bounds__(kThreads) void k_bloom(KmerScan s, unsigned long long* A,
                                                     uint64_t WA, unsigned long long* B,
                                                     uint64_t WB, unsigned long long* ctr) {
-  constexpr int kAhead = 8;
+  constexpr int kAhead = RUNS ? 8 : 1;
   const uint64_t c = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
   uint32_t rep = 0, fresh = 0;
   if (c < s.n_chunks) {
-    for_kmers<kAhead>(s, c, [&](uint32_t, uint32_t, const Kmer* km, int n) {
+    for_kmers<kAhead, RUNS>(s, c, [&](uint32_t, uint32_t, const Kmer* km, int n) {
       // each k-mer's bits, with those of the run's k-mers after it, and what the
       // word held before it
       unsigned long long bits[kAhead], all[kAhead], old[kAhead];
@@ -225,7 +233,7 @@ __global__ __launch_bounds__(kThreads) void k_bloom(KmerScan s, unsigned long lo
         if ((old[q] & bits[q]) == bits[q]) {
           const uint64_t h2 = fmix64(km[q].code ^ kSaltB);
           const unsigned long long b2 = bloom_bits(h2);
-          const unsigned long long old2 = atomicOr(&B[line_word(km[q].mh, h2, WB)], b2);
+          const unsigned long long old2 = atomicOr(&B[line_word<RUNS>(km[q].mh, h2, WB)], b2);
           ++rep;
           fresh += (old2 & b2) != b2;
         }
@@ -256,18 +264,19 @@ struct Table {
 
 // pass 2: the k-mers in B into the table; ctr[2] = 1 when a key found no slot
 // within kMaxProbe probes (the host then doubles the table and reruns the pass)
+template <bool RUNS>
 __global__ __launch_bounds__(kThreads) void k_table(KmerScan s, const unsigned long long* B,
                                                     uint64_t WB, Table t,
                                                     unsigned long long* ctr) {
   const uint64_t c = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
   if (c >= s.n_chunks) return;
   constexpr int kAhead = 4;
-  for_kmers<kAhead>(s, c, [&](uint32_t r, uint32_t p, const Kmer* km, int n) {
+  for_kmers<kAhead, RUNS>(s, c, [&](uint32_t r, uint32_t p, const Kmer* km, int n) {
     unsigned long long bits[kAhead], have[kAhead];
     for (int q = 0; q < kAhead; ++q) {
       const uint64_t h2 = fmix64(km[q].code ^ kSaltB);
       bits[q] = bloom_bits(h2);
-      have[q] = B[line_word(km[q].mh, h2, WB)];
+      have[q] = B[line_word<RUNS>(km[q].mh, h2, WB)];
     }
     for (int q = 0; q < kAhead; ++q) {
       if (q >= n || (have[q] & bits[q]) != bits[q]) continue;
@@ -695,12 +704,10 @@ int find_overlaps(const xd_store* store, int32_t k, uint32_t m, uint32_t bloom_b
     OV_TRY(hipMemsetAsync(A, 0, WA * 8, st));
     OV_TRY(hipMemsetAsync(B, 0, WB * 8, st));
     OV_TRY(hipMemsetAsync(ctr, 0, 4 * 8, st));
-    // up to kWindow m-mers to a k-mer, and eight to a word of the filters that go
-    // by them (3.0 Gbp, where that is B alone: 626 ms with a third of one to a
-    // word of B, 611 so, 608 by the k-mer's own hash)
+    // up to kWindow m-mers to a k-mer, and eight to a word
     const bool runs = WA <= kRunWords;
     int32_t mm = 1;
-    while (mm < 16 && (1ull << (2 * mm)) < 8 * (runs ? WA : WB)) ++mm;
+    while (mm < 16 && (1ull << (2 * mm)) < 8 * WA) ++mm;
     mm = std::min(k, std::max(k - kWindow + 1, mm));
     KmerScan ks{sv.words, sv.word_off, sv.len, d_chunk, n_chunks, sv.n_reads, k,
                 k == 32 ? ~0ull : (1ull << (2 * k)) - 1, strands == 2 ? 1 : 0, mm,
@@ -739,7 +746,8 @@ int find_overlaps(const xd_store* store, int32_t k, uint32_t m, uint32_t bloom_b
       OV_TRY(hipMemsetAsync(t.keys, 0, cap * 8, st));
       OV_TRY(hipMemsetAsync(t.cnt, 0, cap * 4, st));
       OV_TRY(hipMemsetAsync(ctr + 2, 0, 8, st));
-      hipLaunchKernelGGL(k_table, dim3(grid_for(n_chunks, kThreads)), dim3(kThreads), 0, st, ks, B, WB, t,
+      hipLaunchKernelGGL(runs ? k_table<true> : k_table<false>,
+                         dim3(grid_for(n_chunks, kThreads)), dim3(kThreads), 0, st, ks, B, WB, t,
                          ctr);
       unsigned long long full = 0;
       if ((rc = fetch(st, ctr + 2, &full))) return rc;
