@@ -36,8 +36,6 @@ PEAK_INT32_TOPS = 256 * 64 * 2.4e9 / 1e12
 # costs one int32 lane.  The lane tiers hold 32 rows of a window in the bits of a register,
 # so a lane's operation works on up to 32 cells and `frac` can pass 1.
 OPS_PER_CELL = 8
-FIRST_TIER = "k_lane_tier<6, 2> (one extension per lane, 64 rows in bit planes)"
-KERNEL_NAMES = {"plain": FIRST_TIER, "persistent": FIRST_TIER, "plan": FIRST_TIER}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_c2.json")
 
 WORKLOAD_DESC = {
@@ -58,12 +56,25 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
+def first_tiers(n_tasks: int, x, form: str) -> str:
+    """The kernels a batch's extensions start in (scores 1/-1/-1, long reads)."""
+    if n_tasks < 3000 and form == "plain":
+        return "k_ext_first<1, 16, true> (one extension per wavefront)"
+    if n_tasks < 12288:
+        return "k_ext_tier<1, 16, true, 4, true, false> (one extension per wavefront, queue)"
+    lanes = [name for lo, hi, name in ((0, 14, "<5, 1>"), (15, 30, "<6, 2>"), (31, 62, "<7, 3>"))
+             if ((x >= lo) & (x <= hi)).any()]
+    names = ["k_lane_tier" + name for name in lanes]
+    names += ["packed windows"] if (x > 62).any() else []
+    return " + ".join(names) + " (one extension per lane, rows in bit planes)"
+
+
 def kernel_source_hash() -> str:
     """Hash of the sources the extension kernels and their launches are built from."""
     h = hashlib.sha256()
     d = os.path.join(ROOT, "paper_2001_10049_amd", "csrc")
-    for f in ("xdrop.hip", "xdrop_device.h", "lane_core.h", "lane_device.h", "lane_share.h", "pair_device.h",
-              "pair2_device.h", "pair4_device.h"):
+    for f in ("xdrop.hip", "xdrop_device.h", "lane_core.h", "lane_device.h", "lane_share.h",
+              "pair_device.h", "pair2_device.h", "pair4_device.h"):
         h.update(open(os.path.join(d, f), "rb").read())
     return h.hexdigest()[:16]
 
@@ -237,15 +248,15 @@ def main():
     gcups = results[head]["gcups"]
     prof = profs.get(head) or next(iter(profs.values()))
 
-    # dominant kernel: the 64-row first tier; its algorithmic work is every
-    # cell it completes (all cells when no extension moved to a wider tier)
+    # dominant kernel: the first tier; its algorithmic work is every cell it
+    # completes (all cells when no extension moved to a wider tier)
     launches = max(prof["batches"], 1)
     if prof["to_tier2"] == 0 and (head == "plain" or w.x.max() <= 32):
         k_ms = prof["ms_tier1"] / launches
-        kernel = KERNEL_NAMES.get(head, head)
+        kernel = first_tiers(n, w.x, head)
     else:
         k_ms = (prof["ms_tier1"] + prof["ms_wide"]) / launches
-        kernel = KERNEL_NAMES.get(head, head) + " + wide tiers"
+        kernel = first_tiers(n, w.x, head) + " + wide tiers"
     achieved = OPS_PER_CELL * cells_per_step / (k_ms / 1e3) / 1e12
     roofline = {"bound": "alu", "achieved": round(achieved, 3),
                 "peak": round(PEAK_INT32_TOPS, 3), "unit": "TOP/s",
@@ -263,7 +274,7 @@ def main():
     if pp is not None and pp["to_tier2"] == 0 and int(w.x.max()) <= tuning.get("x_tier1", 32):
         f_ms = pp["ms_tier1"] / max(pp["batches"], 1)
         f_ach = OPS_PER_CELL * cells_per_step / (f_ms / 1e3) / 1e12
-        first = {"kernel": KERNEL_NAMES["persistent"], "ms_per_launch": round(f_ms, 4),
+        first = {"kernel": first_tiers(n, w.x, "persistent"), "ms_per_launch": round(f_ms, 4),
                  "kernel_gcups": round(cells_per_step / (f_ms / 1e3) / 1e9, 2),
                  "achieved": round(f_ach, 3), "unit": "TOP/s",
                  "frac_int32_peak": round(f_ach / PEAK_INT32_TOPS, 4)}

@@ -795,9 +795,9 @@ struct LaneWork {
 // two or four lanes; the others the longest ones, one per wavefront.  Which
 // extension runs how: see xd::queue::split_time.
 // Bound by vector issue: 127 instructions a step for 64 extensions of 64 rows
-// (P = 6), 65 for 32 rows (P = 5), 207 for 96 rows (P = 7), 87 for 32 extensions
-// of 64 rows in two lanes each, against 6.2 a step and extension in the packed
-// 64-cell kernel.  100,000 pairs of 10 kbp at X = 25: 13.48 -> 5.6 ms; 400,000
+// (P = 6), 65 for 32 rows (P = 5), 207 for 96 rows (P = 7), 87 for the 32 extensions
+// that a wavefront holds of 64 rows in two lanes each (so 2.0 and 2.7 a step and
+// extension, P = 6), against 6.2 in the packed 64-cell kernel.  100,000 pairs of 10 kbp at X = 25: 13.48 -> 5.6 ms; 400,000
 // seeds at X of 7, 25 and 50: 83.3 -> 27.2 ms.  One workgroup per CU: a lane's
 // step then takes about 0.25 us, and with two it takes twice that for the same
 // rate, so the longest extensions end later.
@@ -1560,9 +1560,11 @@ Route batch_route(const BatchArgs& A, bool batched, uint32_t mean_len, const Tun
 }
 
 // tier arguments: tier 0 (64 cells, batched form), tiers 1..4 (128, 256, 512,
-// 1024 cells) and the band tier, each with its queue segment (batched form;
-// segments 0..2 hold the extensions whose X picks that first tier) and the
-// overflow list of the tier below
+// 1024 cells) and the band tier, each with its queue segment (batched form:
+// kSeg64, kSeg128 and kSeg256 hold the extensions whose X picks that first tier;
+// with lane tiers kSeg64 and kSegLong their longest, and the lane tiers have the
+// five segments between kSeg64 and kSeg128) and the overflow list of the tier
+// below
 TierPack make_pack(const BatchArgs& A, const Scratch& S, const Route& R) {
   uint32_t* c = S.ctr;
   TierPack p = {};
@@ -1738,8 +1740,8 @@ void launch_persistent_ext(const BatchArgs& A, const Scratch& S, uint64_t n_ext,
     launch_lane(S, Rt, stream);
   else if (Rt.packed)
     launch_pair(S, blocks, stream);
-  else if (UNIT && Rt.solo)
-    launch_tier0<UNIT, 16, true>(S, blocks, stream);
+  else if (Rt.solo)  // (whose scores are UNIT ones)
+    launch_tier0<true, 16, true>(S, blocks, stream);
   else if (tu.group_steps == 4)
     launch_tier0<UNIT, 4, false>(S, blocks, stream);
   else if (tu.group_steps == 16)
