@@ -187,24 +187,31 @@ struct Scratch {
   int32_t* band;      // [blocks][3][cap] rows of the band tier
   BandGeom geom;
 };
-// ctr layout.  The segments have a line (128 bytes) to themselves: waves read
-// their bounds after every extension, and reads of the work heads' line held up
-// the heads' atomics (40 ns an extension for the whole chip; 6,000 pairs of 1.3
-// kbp reads at X = 25, one per wavefront: 0.73 ms, 0.45 so).
-constexpr int kOvfCount = 0;  // [0..4] sizes of ovf[0..4]
-constexpr int kLaneOvf = 5;   // [5..8] sizes of the lane tiers' lists 0..3
-constexpr int kResumed = 9;   // [9..12] moves out of windows 0..3 that carried their state
-constexpr int kLaneResumed = kLaneOvf + kResumed;  // [14..17] as kResumed, out of lane tiers
-constexpr int kSegHead1 = 13;  // work head of the 128-cell window's queue segment (batched form)
-constexpr int kLaneHead = 18;  // [18..26] work heads of tiers kTLane on
-constexpr int kHead = 27;      // [27..31] work heads of tiers 0..4
-constexpr int kSeg = 32;       // [32..44] queue starts of the segments, then 2n, and the
-                               // workgroups of split extensions (k_bin_scan)
-constexpr int kBandHead = 63;  // work head of the band tier (it has no segment)
-constexpr int kCtrWords = 64;
-static_assert(kLaneResumed + 4 <= kLaneHead && kHead + 5 <= kSeg && kSeg + kSegWords <= kBandHead,
-              "counters");
-constexpr int kTierArgsBytes = 8 * 256;  // >= sizeof(TierPack), checked below
+// ctr layout, lines of 128 bytes.  An atomic holds up what else goes to its line, so
+// what is used side by side lies on different ones:
+//  the segments, whose bounds waves read after every extension, and the work heads
+//   (on one line 40 ns an extension for the whole chip; 6,000 pairs of 1.3 kbp reads
+//   at X = 25, one per wavefront, 0.73 ms, 0.45 so);
+//  the heads of the lanes and of the wavefronts that run one extension, which
+//   all start at once (40,000 pairs of 1.3 kbp: 0.757 ms on one line, 0.735 so);
+//  the lists' sizes and the counts of states kept, both raised by each extension that
+//   leaves a window (k_lane_list<4>, 2.2 M extensions of which 1.9 M leave:
+//   44.7 ms on one line, 27.5 so).
+constexpr int kLineWords = 32;
+constexpr int kSeg = 0;         // queue starts of the segments, then 2n, and the
+                                // workgroups of split extensions (k_bin_scan)
+constexpr int kHead = 32;       // [32..36] work heads of tiers 0..4
+constexpr int kSegHead1 = 37;   // work head of the 128-cell window's queue segment (batched form)
+constexpr int kBandHead = 38;   // work head of the band tier
+constexpr int kOvfCount = 64;   // [64..68] sizes of ovf[0..4]
+constexpr int kLaneOvf = 69;    // [69..72] sizes of the lane tiers' lists 0..3
+constexpr int kResumed = 96;    // [96..99] moves out of windows 0..3 that carried their state
+constexpr int kToResumed = kResumed - kOvfCount;  // from a list's size to its count of those
+constexpr int kLaneHead = 105;  // [105..113] work heads of tiers kTLane on
+constexpr int kCtrWords = 128;
+static_assert(kSegWords <= kLineWords && kBandHead < kOvfCount && kOvfCount + 5 <= kLaneOvf &&
+              kLaneOvf + 4 <= kResumed && kLaneOvf + kToResumed + 4 <= kLaneHead, "counters");
+constexpr int kTierArgsBytes = 7 * 256;  // >= sizeof(TierPack), checked below
 constexpr uint64_t kFixedBytes = (kBins * 4 + kCtrWords * 4 + kTierArgsBytes + 255) & ~255ull;
 
 uint64_t state_bytes(uint64_t n, int t) {
@@ -255,7 +262,7 @@ Scratch scratch_carve(char* base, uint64_t n, const BandGeom& g) {
 // their queue segments or the rows of the window that takes a list.
 enum { kT64 = 0, kT128, kT256, kT512, kT1024, kTBand, kTSeg128, kTLane, kTNarrow, kTWide,
        kTSplit, kTWideSplit, kTL128, kTL256, kTL512, kTL1024, kTiers };
-static_assert(kLaneHead + (kTiers - kTLane) <= kHead, "work heads");
+static_assert(kLaneHead + (kTiers - kTLane) <= kCtrWords, "work heads");
 
 // Arguments of a persistent tier.  A list's entry k is at list[k * step]: with
 // lane tiers theirs fill a list array from the front and the other tiers'
@@ -424,7 +431,7 @@ __device__ __forceinline__ void overflow_to(const TaskArgs& A, const TierArgs& R
       uint32_t* dst = (uint32_t*)at;
       for (uint32_t w = xd::lane_id(); w < R.out_rec / 4; w += 64) dst[w] = ring[w];
     }
-    if (xd::lane_id() == 0) atomicAdd(R.out_count + (kResumed - kOvfCount), 1u);
+    if (xd::lane_id() == 0) atomicAdd(R.out_count + kToResumed, 1u);
   }
   if (xd::lane_id() == 0) R.out_list[(int64_t)slot * R.out_step] = e | (keep ? kResumeFlag : 0u);
 }
@@ -785,7 +792,7 @@ struct LaneWork {
     const bool keep = slot < pp->out_cap;
     pp->out_list[slot] = e | (keep ? kResumeFlag : 0u);
     if (!keep) return nullptr;
-    atomicAdd(pp->out_count + (kResumed - kOvfCount), 1u);
+    atomicAdd(pp->out_count + kToResumed, 1u);
     return pp->out_state + (uint64_t)slot * pp->out_rec;
   }
 };
@@ -2664,7 +2671,7 @@ int xd_profile_read(xd_profile* out, int reset) {
     g_prof_sum.to_tier5 += r.counters[kOvfCount + 3] + r.counters[kLaneOvf + 3];
     g_prof_sum.to_band += r.counters[kOvfCount + 4];
     for (int t = 0; t < 4; ++t) 
-      g_prof_sum.resumed += r.counters[kResumed + t] + r.counters[kLaneResumed + t];
+      g_prof_sum.resumed += r.counters[kResumed + t] + r.counters[kLaneOvf + kToResumed + t];
     g_prof_sum.ms_tier1 += t1;
     g_prof_sum.ms_wide += t2;
     g_prof_sum.ms_combine += t3;
