@@ -97,8 +97,12 @@ __device__ __forceinline__ void run(Work& wk, uint32_t* lds, const Chunk* planes
     const uint64_t leave = ballot64(ended || wide);
     if (leave | (more ? ballot64(!active) : 0ull)) {
       auto add = [](int32_t a, int32_t b) { return a + b; };
-      const uint64_t cells = count_of((uint32_t)over_group<S>((int32_t)(c.cnt & 0xffffu), add),
-                                      (uint32_t)over_group<S>((int32_t)(c.cnt >> 16), add));
+      uint64_t cells;
+      if constexpr (kWholeCount<S>)
+        cells = (uint32_t)over_group<S>((int32_t)c.cnt, add);
+      else
+        cells = count_of((uint32_t)over_group<S>((int32_t)(c.cnt & 0xffffu), add),
+                         (uint32_t)over_group<S>((int32_t)(c.cnt >> 16), add));
       if (ended && first) {
         ExtOut o;
         o.best = c.thr - (d + 1);
@@ -203,7 +207,7 @@ __device__ __forceinline__ void run(Work& wk, uint32_t* lds, const Chunk* planes
             bi = h.bi;
             dstar = h.dstar;
             c.thr = h.thr;
-            c.cnt = count_part<S>(h, s);
+            c.cnt = kWholeCount<S> ? (first ? h.cells : 0u) : count_part<S>(h, s);
           }
           active = fresh = true;
           if constexpr (S == 1 && !Work::kResumes) {
