@@ -70,9 +70,11 @@ XD_HD uint32_t bin_key(const BinRule& R, int32_t X, uint32_t cost) {
 // instructions it costs.  A CU runs one workgroup of single lanes or of split
 // extensions, and the wavefronts of the longest beside it, ahead of it in
 // priority.  The narrow class's lanes alone come after its longest, in a launch
-// of their own, so its times add up.  In issue slots of a SIMD (vector
-// instructions; a wavefront's share from timing 12,500 to 100,000 pairs of 1.3 to
-// 20 kbp reads with shares of 9 to 12):
+// of their own, so its times add up; where the 64-row class runs beside its
+// longest (x.beside), what they issue is not hidden behind the longest's chain
+// either (400,000 tasks of 10 kbp at X of 7 and 25: 15.4 ms, 14.8 so).  In issue
+// slots of a SIMD (vector instructions; a wavefront's share from timing 12,500 to
+// 100,000 pairs of 1.3 to 20 kbp reads with shares of 9 to 12):
 struct LaneCost {
   float lane_step, split_step, solo_step;  // from one step of an extension to the next
   float solo;                              // one step's share of the instructions
@@ -97,6 +99,7 @@ XD_HD uint32_t cls_of(int kind) {
 struct ClassBins {
   uint32_t next[kCostBins + 1], before[kCostBins + 1];
   uint64_t sum[kCostBins + 1];
+  uint32_t beside;  // (narrow class) extensions of the 64-row class
 };
 
 XD_HD void class_bins(const uint32_t* h, int kind, ClassBins& x) {
@@ -114,6 +117,9 @@ XD_HD void class_bins(const uint32_t* h, int kind, ClassBins& x) {
   }
   x.sum[N] = v;
   x.before[N] = n;
+  x.beside = 0;
+  if (kind == 0)
+    for (uint32_t q = 0; q < N; ++q) x.beside += h[kClsLane * N + q];
   x.next[N] = N;
   for (uint32_t q = N; q-- > 0;) {
     if (count(q)) nx = q;
@@ -146,6 +152,8 @@ XD_HD float split_time(const ClassBins& x, int kind, uint32_t s1, uint32_t s2, f
   if (any && groups < 1.f) return INFINITY;
   const float t1 = any ? fmaxf(l1, split / (groups * (float)c.split_group)) : 0.f;
   const float t2 = fmaxf(l2, rest / (256.f * (cus - groups)));
+  if (kind == 0 && x.beside)
+    return fmaxf(l0 * c.solo_step, t1 * c.split_step + solo + t2 * c.lane_step);
   if (kind == 0) return fmaxf(l0 * c.solo_step, t1 * c.split_step + solo) + t2 * c.lane_step;
   return fmaxf(l0 * c.solo_step, fmaxf(t1 * c.split_step, t2 * c.lane_step) + solo);
 }

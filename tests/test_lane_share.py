@@ -48,6 +48,16 @@ def test_narrow_class_alone():
     assert s["solo"] + s["split"] > 8000, s
 
 
+def test_narrow_class_beside_another():
+    # where a 64-row class fills the chip, the narrow one's wavefronts of one
+    # extension take its issue slots: 400,000 tasks at X of 7 and 25
+    rng = np.random.default_rng(1)
+    length = np.exp(rng.normal(9.1, 0.47, 800_000)).clip(1000, 50_000)
+    cost = (1.6 * length * rng.random(800_000)).astype(np.uint32) + 2
+    s = check(rng.choice([7, 25], 800_000), cost)
+    assert s["narrow"] and s["solo"] < 1000, s
+
+
 def test_one_workgroup_splits_nothing():
     s = check(np.full(5000, 50), np.full(5000, 20_000), cus=1)
     assert s["split"] == s["wide_split"] == 0, s
